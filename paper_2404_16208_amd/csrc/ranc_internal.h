@@ -136,6 +136,21 @@ struct ResidentArgs {
     int num_ticks;
 };
 
+// One launch of the multi-tick MFMA form of a feed-forward network
+// (kern_mfma_ticks.hip): cores order[first, first + count), a core of level l
+// running block step - l of the segment's ticks [k0, k0 + ticks) (positions in
+// the call), `block` ticks per block.
+struct BlockArgs {
+    const int32_t *order;       // cores by ascending level [C]
+    const int32_t *level;       // level of each core [C]
+    int first, count;
+    int step, block, k0, ticks;
+    const uint32_t *ext_base;   // external input as in ResidentArgs, or nullptr
+    long long ext_sstride;
+    long long tick_words;
+};
+constexpr int MFMA_BLOCK_TICKS_MAX = 32;
+
 // Grid synchronization words of the state-resident loop: arrival counter and
 // give-up flag (zeroed before each launch), and the longest wait, in ticks of
 // the device's constant-rate wall clock.
@@ -255,6 +270,10 @@ int sparse_row_align();          // entries each slice's rows are aligned to
 // compact: B tiles built from the compact crossbar (R_BSRC), else read from the planes
 hipError_t launch_integrate_mfma(const DevNet &n, const TickArgs &a, int two_planes, int samples_per_wg, int compact,
                                  hipStream_t st);
+// Several ticks per launch for feed-forward networks; counts go straight into
+// the totals.
+hipError_t launch_integrate_mfma_ticks(const DevNet &n, const BlockArgs &a, int two_planes, hipStream_t st);
+bool mfma_ticks_supported(int A, int N, int two_planes);
 // State-resident MFMA tick loop (N = 256 in one slice, A <= 256, at most
 // resident_max_cores_per_wg() cores per workgroup): zeroes the sync words,
 // then launches `grid` workgroups cooperatively.

@@ -51,7 +51,10 @@ enum Region {
     R_RSYNC,
     // MFMA path: the compact B source, uploaded at load as well; kept past
     // the state regions so that their placement does not depend on it
-    R_BSRC, R_NREG
+    R_BSRC,
+    // MFMA path, feed-forward networks: cores by level, then each core's
+    // level; uploaded at load
+    R_ORDER, R_NREG
 };
 
 struct Plan {
@@ -64,6 +67,12 @@ struct Plan {
     long long ell_words; // u32 words of the wave-interleaved routing table
     long long ecsr_entries; // sparse path: row entries, each slice's rows padded to sparse_row_align()
     size_t off[R_NREG], size[R_NREG], params_bytes, total;
+    // MFMA path, feed-forward networks (kern_mfma_ticks.hip): cores by
+    // ascending level, each core's level, the levels' first positions in
+    // `order` (levels + 1 entries), and the ticks a segment of a call may run
+    // at most (the history ring holds D more). No levels: tick by tick.
+    int levels = 0, seg_ticks = 1;
+    std::vector<int32_t> order, level, level_first;
 };
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -189,7 +198,58 @@ bool neuron_model_ext(const ranc_net_desc *d)
     return false;
 }
 
-ranc_status make_plan(const ranc_net_desc *d, int32_t S, int32_t RT, int32_t path, Plan &p)
+// Levels of the cores when no spike can come back to the core it left
+// (directly or through others): a core's level is the longest path to it from
+// a core without sources. More than MAX_LEVELS levels, or a cycle: none.
+constexpr int MAX_LEVELS = 64;
+bool feed_forward_levels(const ranc_net_desc *d, Plan &p)
+{
+    const int C = p.C, N = p.N;
+    std::vector<uint32_t> indeg(C, 0);
+    auto dest = [&](size_t i) {
+        const int c = (int)(i / N);
+        return (c % d->grid_w + d->dest_dx[i]) + (c / d->grid_w + d->dest_dy[i]) * d->grid_w;
+    };
+    for (size_t i = 0; i < (size_t)C * N; ++i)
+        if (d->dest_kind[i] == RANC_DEST_CORE)
+            ++indeg[dest(i)];
+    std::vector<int32_t> ready, level(C, 0);
+    for (int c = 0; c < C; ++c)
+        if (!indeg[c])
+            ready.push_back(c);
+    int top = 0;
+    for (size_t r = 0; r < ready.size(); ++r) {
+        const int c = ready[r];
+        top = std::max(top, level[c]);
+        if (top >= MAX_LEVELS)
+            return false;
+        for (size_t i = (size_t)c * N; i < (size_t)(c + 1) * N; ++i)
+            if (d->dest_kind[i] == RANC_DEST_CORE) {
+                const int t = dest(i);
+                level[t] = std::max(level[t], level[c] + 1);
+                if (--indeg[t] == 0)
+                    ready.push_back(t);
+            }
+    }
+    if ((int)ready.size() != C)
+        return false;
+    p.levels = top + 1;
+    p.level_first.assign(p.levels + 1, 0);
+    for (int c = 0; c < C; ++c)
+        ++p.level_first[level[c] + 1];
+    for (int l = 0; l < p.levels; ++l)
+        p.level_first[l + 1] += p.level_first[l];
+    p.order.resize(C);
+    std::vector<int32_t> at(p.level_first.begin(), p.level_first.end() - 1);
+    for (int c = 0; c < C; ++c)
+        p.order[at[level[c]]++] = c;
+    p.level = std::move(level);
+    return true;
+}
+
+// blocks: lay out a feed-forward MFMA network for several ticks per launch
+// (a longer history ring); without, as for any other network.
+ranc_status make_plan(const ranc_net_desc *d, int32_t S, int32_t RT, int32_t path, Plan &p, bool blocks = true)
 {
     ranc_status st = validate(d, S, RT, path);
     if (st != RANC_OK)
@@ -217,6 +277,12 @@ ranc_status make_plan(const ranc_net_desc *d, int32_t S, int32_t RT, int32_t pat
     if (path == RANC_PATH_SPARSE && !sparse_shape_supported(p.A, p.N, p.G))
         return fail(RANC_EUNSUPPORTED, "sparse path does not support N=%d with G=%d", p.N, p.G);
     p.path = path;
+    // segments of at most 32 ticks: the history ring then takes about as much
+    // memory as the potentials (one bit per tick against 32)
+    if (blocks && path == RANC_PATH_MFMA && RT > 1 && mfma_ticks_supported(p.A, p.N, p.two) && feed_forward_levels(d, p)) {
+        p.seg_ticks = std::min(RT, MFMA_BLOCK_TICKS_MAX);
+        p.Q = p.D + p.seg_ticks;
+    }
     p.slices = path == RANC_PATH_MFMA ? mfma_slices(p.A, p.N, p.two)
              : path == RANC_PATH_SPARSE ? p.N / sparse_slice_width(p.N) : 1;
     p.cnt_rows = path == RANC_PATH_PLAIN ? p.N / 64 : p.slices;
@@ -341,6 +407,7 @@ ranc_status make_plan(const ranc_net_desc *d, int32_t S, int32_t RT, int32_t pat
     p.size[R_OUTPOS] = tiled ? 0 : std::max<size_t>((size_t)p.Nout, 1) * 4;
     p.size[R_LINKD] = (size_t)4 * C * p.S64 * 8;
     p.size[R_RSYNC] = mf ? 8 : 0;   // state-resident loop: arrival counter, give-up flag
+    p.size[R_ORDER] = p.levels ? 2 * C * 4 : 0;
     size_t off = 0;
     for (int r = 0; r < R_NREG; ++r) {
         if (r == R_PARAMS_END)
@@ -702,7 +769,7 @@ struct Batch {
 };
 
 struct ranc_net {
-    Plan p;
+    Plan p{};
     uint64_t uid = 0;   // unique per loaded handle
     Batch batch;
     std::vector<CapturedLoop> loops;
@@ -791,6 +858,81 @@ static hipError_t prof_collect(ranc_net *net)
     return hipSuccess;
 }
 
+// How a call's segment of T ticks of a feed-forward network runs: `block`
+// ticks per launch and core (0: tick by tick), the levels one after another
+// (each the whole segment) or, `skewed`, all levels in each launch with level
+// l one block behind level l - 1.
+struct BlockPlan {
+    int block = 0;
+    bool skewed = false;
+};
+
+// The cheapest form by the time of its launches, in microseconds.
+static BlockPlan choose_blocks(const Plan &p, int T)
+{
+    BlockPlan best;
+    if (!p.levels || T < 2)
+        return best;
+    const long long tiles = p.S64 / 64;
+    auto rounds = [&](long long cores) { return (cores * p.slices * tiles + 255) / 256; };
+    const double launch = 4.0, setup = 4.0, tick = 2.0, single = 7.0;
+    double cost = T * (launch + single * std::max(1.0, (double)p.C * p.slices * tiles / 256.0));
+    double seq = 0;
+    for (int l = 0; l < p.levels; ++l)
+        seq += launch + rounds(p.level_first[l + 1] - p.level_first[l]) * (setup + T * tick);
+    if (seq < cost) {
+        cost = seq;
+        best.block = T;
+    }
+    for (int b = 2; b < T && p.levels > 1; b *= 2) {
+        const int nb = (T + b - 1) / b;
+        double skew = 0;
+        for (int s = 0; s < nb + p.levels - 1; ++s) {
+            const int lo = std::max(0, s - nb + 1), hi = std::min(s, p.levels - 1);
+            skew += launch + rounds(p.level_first[hi + 1] - p.level_first[lo]) * (setup + b * tick);
+        }
+        if (skew < cost) {
+            cost = skew;
+            best.block = b;
+            best.skewed = true;
+        }
+    }
+    return best;
+}
+
+// Queue ticks [k0, k0 + T) of the call (T <= seg_ticks) in blocks.
+static hipError_t queue_blocks(ranc_net *net, const uint32_t *base, int num_ticks, int k0, int T, const BlockPlan &bp,
+                               hipStream_t s, bool timed)
+{
+    const Plan &p = net->p;
+    BlockArgs a;
+    a.order = (const int32_t *)(net->ws + p.off[R_ORDER]);
+    a.level = a.order + p.C;
+    a.block = bp.block;
+    a.k0 = k0;
+    a.ticks = T;
+    a.ext_base = base;
+    a.tick_words = (long long)p.Cin * p.W;
+    a.ext_sstride = (long long)num_ticks * a.tick_words;
+    const int nb = (T + bp.block - 1) / bp.block;
+    const int steps = bp.skewed ? nb + p.levels - 1 : p.levels;
+    hipError_t e = hipSuccess;
+    for (int st = 0; e == hipSuccess && st < steps; ++st) {
+        // levels of the launch: every level whose block of this step exists
+        const int lo = bp.skewed ? std::max(0, st - nb + 1) : st, hi = bp.skewed ? std::min(st, p.levels - 1) : st;
+        a.first = p.level_first[lo];
+        a.count = p.level_first[hi + 1] - a.first;
+        a.step = st;
+        int slot = -1;
+        e = timed ? prof_begin(net, 0, s, &slot) : hipSuccess;
+        if (e == hipSuccess)
+            e = launch_integrate_mfma_ticks(net->dn, a, p.two, s);
+        if (e == hipSuccess && timed)
+            e = prof_end(net, slot, s);
+    }
+    return e;
+}
+
 // Queue num_ticks ticks on stream s: per tick the integration (and on the
 // plain path the router), then the device tick advance. With `timed`, HIP
 // event pairs are recorded around each launch while profiling is on.
@@ -799,7 +941,19 @@ static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_tick
     const Plan &p = net->p;
     const size_t tick_words = (size_t)p.Cin * p.W;
     timed = timed && net->prof.on;
-    for (int k = 0; k < num_ticks; ++k) {
+    // Feed-forward networks on the MFMA path run in segments of several ticks
+    // per launch (counts go straight into the totals); counting packets per
+    // link reads every tick's spikes as they stand after that tick.
+    const BlockPlan bp = net->links_on ? BlockPlan() : choose_blocks(p, std::min(num_ticks, p.seg_ticks));
+    for (int k = 0; bp.block && k < num_ticks; k += p.seg_ticks) {
+        const int T = std::min(p.seg_ticks, num_ticks - k);
+        BlockPlan b = bp;
+        b.block = std::min(b.block, T);
+        hipError_t e = queue_blocks(net, base, num_ticks, k, T, b, s, timed);
+        if (e != hipSuccess)
+            return hip_fail(e, "launching integration (several ticks)");
+    }
+    for (int k = 0; !bp.block && k < num_ticks; ++k) {
         TickArgs ta;
         ta.k = k;
         ta.ext_t = base ? base + (size_t)k * tick_words : nullptr;
@@ -840,7 +994,7 @@ static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_tick
                 return hip_fail(e, "launching the mesh link count");
         }
     }
-    hipError_t e = launch_fold_counts(net->dn, num_ticks, s);
+    hipError_t e = bp.block ? hipSuccess : launch_fold_counts(net->dn, num_ticks, s);
     if (e == hipSuccess)
         e = launch_advance_tick(net->dn, num_ticks, s);
     if (e != hipSuccess)
@@ -1446,7 +1600,7 @@ ranc_status ranc_workspace_bytes(const ranc_net_desc *desc, int32_t num_samples,
 {
     if (!bytes)
         return fail(RANC_EINVAL, "bytes is NULL");
-    Plan p;
+    Plan p{};
     ranc_status st = make_plan(desc, num_samples, max_ticks_per_call, path, p);
     if (st != RANC_OK)
         return st;
@@ -1460,7 +1614,7 @@ ranc_status ranc_load_network(const ranc_net_desc *desc, int32_t num_samples, in
     if (!out)
         return fail(RANC_EINVAL, "out is NULL");
     *out = nullptr;
-    Plan p;
+    Plan p{};
     ranc_status st = make_plan(desc, num_samples, max_ticks_per_call, path, p);
     if (st != RANC_OK)
         return st;
@@ -1468,6 +1622,14 @@ ranc_status ranc_load_network(const ranc_net_desc *desc, int32_t num_samples, in
         return fail(RANC_EINVAL, "workspace is NULL");
     if ((uintptr_t)workspace % 256)
         return fail(RANC_EINVAL, "workspace must be 256-byte aligned");
+    if (workspace_bytes < p.total && p.levels) {
+        // a workspace sized for the tick-by-tick layout
+        Plan q;
+        st = make_plan(desc, num_samples, max_ticks_per_call, path, q, false);
+        if (st != RANC_OK)
+            return st;
+        p = std::move(q);
+    }
     if (workspace_bytes < p.total)
         return fail(RANC_ENOMEM, "workspace has %zu bytes, needs %zu", workspace_bytes, p.total);
     ranc_net *net = new (std::nothrow) ranc_net();
@@ -1542,6 +1704,11 @@ ranc_status ranc_load_network(const ranc_net_desc *desc, int32_t num_samples, in
         pack_bsrc(desc, p, bsrc);
         e = hipMemcpyAsync(reg(R_BSRC), bsrc.data(), bsrc.size(), hipMemcpyHostToDevice, s);
     }
+    if (e == hipSuccess && p.levels) {
+        e = hipMemcpyAsync(reg(R_ORDER), p.order.data(), (size_t)p.C * 4, hipMemcpyHostToDevice, s);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(reg(R_ORDER) + (size_t)p.C * 4, p.level.data(), (size_t)p.C * 4, hipMemcpyHostToDevice, s);
+    }
     if (e == hipSuccess)
         e = launch_reset_state(n, net->lk, s);
     if (e == hipSuccess)
@@ -1580,8 +1747,8 @@ ranc_status ranc_load_network_static(const ranc_net_desc *desc, int32_t num_samp
     if (!out)
         return fail(RANC_EINVAL, "out is NULL");
     *out = nullptr;
-    Plan p;
-    ranc_status st = make_plan(desc, num_samples, max_ticks_per_call, path, p);
+    Plan p{};
+    ranc_status st = make_plan(desc, num_samples, max_ticks_per_call, path, p, false);
     if (st != RANC_OK)
         return st;
     if (p.total > RANC_STATIC_WORKSPACE_BYTES)
