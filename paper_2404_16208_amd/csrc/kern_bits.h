@@ -16,20 +16,42 @@ __device__ inline int sigma32(int b) { return 8 * ((b & 15) >> 2) + 4 * (b >> 4)
 // inverse of sigma32.
 __device__ inline int sigma32_inv(int i) { return 16 * ((i & 7) >> 2) + 4 * (i >> 3) + (i & 3); }
 
+// x of lane ^ K within each row of 16 lanes, as a data-parallel primitive
+// (vector pipe only: no LDS round trip, whose latency the five dependent
+// stages of a transpose would each pay).
+template <int K> __device__ inline uint32_t lane_xor(uint32_t x)
+{
+    static_assert(K == 1 || K == 2 || K == 4 || K == 8, "within a row of 16 lanes");
+    constexpr int QUAD_XOR1 = 0xB1, QUAD_XOR2 = 0x4E, QUAD_XOR3 = 0x1B, HALF_MIRROR = 0x141, ROR8 = 0x128;
+    if constexpr (K == 4) {   // lane ^ 7, then lane ^ 3
+        x = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, HALF_MIRROR, 0xF, 0xF, true);
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, QUAD_XOR3, 0xF, 0xF, true);
+    } else {
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, K == 1 ? QUAD_XOR1 : K == 2 ? QUAD_XOR2 : ROR8, 0xF, 0xF,
+                                                     true);
+    }
+}
+
 // One stage of a recursive bit-matrix transpose: lanes whose index has bit K
 // clear exchange the bits with index bit K set for their partner's (lane ^ K)
 // bits with index bit K clear.
 template <int K>
 __device__ inline uint32_t transpose_stage(uint32_t x, int lane)
 {
-    constexpr uint32_t M = K == 16 ? 0x0000FFFFu : K == 8 ? 0x00FF00FFu : K == 4 ? 0x0F0F0F0Fu
-                         : K == 2  ? 0x33333333u : 0x55555555u;
-    // ds_swizzle bit-mask mode: partner = lane ^ K within each 32-lane half
-    const uint32_t p = (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, 0x1F | (K << 10));
     const bool up = (lane & K) != 0;
-    const uint32_t r = __builtin_rotateright32(p, up ? K : 32 - K);
-    const uint32_t keep = up ? ~M : M;
-    return (x & keep) | (r & ~keep);
+    if constexpr (K == 16) {
+        // even[l], odd[l]: x of the even and the odd row of 16 lanes of l's half
+        const auto sw = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        const uint32_t even = (uint32_t)sw[0], odd = (uint32_t)sw[1];
+        return __builtin_amdgcn_perm(odd, even, up ? 0x07060302u : 0x05040100u);
+    } else if constexpr (K == 8) {
+        return __builtin_amdgcn_perm(lane_xor<8>(x), x, up ? 0x03070105u : 0x06020400u);
+    } else {
+        constexpr uint32_t M = K == 4 ? 0x0F0F0F0Fu : K == 2 ? 0x33333333u : 0x55555555u;
+        const uint32_t r = __builtin_rotateright32(lane_xor<K>(x), up ? K : 32 - K);
+        const uint32_t keep = up ? ~M : M;
+        return (x & keep) | (r & ~keep);
+    }
 }
 
 // 32 x 32 bit transpose within each half-wave: lane i of a half receives, as

@@ -14,388 +14,539 @@
 // from and to HBM (8 bytes per neuron, sample and tick; 1.07 GB per tick on
 // the 512-core net at 1024 samples, 5.4 TB/s, the HBM read-modify-write
 // limit). Here potentials move once per block, and a tick is bound by issue:
-// per wavefront about 300 vector instructions and 32 MFMA of 32 cycles.
-// Measured on that net, 32 ticks per call: 220 -> 84 us per tick at 1024
-// samples (whole pass 7.77 -> 3.15 ms, of it 0.62 ms raster packing), 35 ->
-// 11 us at 100 samples (1.17 -> 0.38 ms).
+// per wavefront about 230 vector instructions and 32 MFMA of 32 cycles.
+// Measured on that net, 32 ticks per call: 220 -> 66 us per tick at 1024
+// samples, of it 55 per further tick and 11 for moving the potentials and
+// setting up (whole pass 7.77 -> 2.65 ms, of it 0.62 ms raster packing); 35 ->
+// 10 us at 100 samples (1.17 -> 0.33 ms).
 //
-// Mapping: one workgroup of 8 wavefronts per (core, neuron slice, 64-sample
-// tile); wave w owns the 32 neurons of block w % (slice / 32). Its B tiles
-// (int8 planes), its potentials (32 registers per lane at 256-neuron slices)
-// and its source-row addresses stay in registers for the block. Per tick:
-//   A. the tick's axon words (LDS) OR external input, expanded to the int8
-//      tile; the next tick's history bits, loaded a tick ahead, transposed to
-//      axon words in LDS; the loads for the tick after are issued;
-//   B. one LDS barrier (both LDS buffers are doubled);
-//   C. products and potential update as in kern_mfma.hip, in place;
-//   D. the loads of A are waited for, then the spike words are stored, so
-//      that no wait ever covers a store of the same tick.
-// The two 32-sample halves of a neuron's 16-bit fire masks are joined by one
-// v_permlane32_swap: lane (h, j) then holds the word of sub-tile h.
-// Spike counts are kept as vertical counters (bit plane i of a lane holds bit
-// i of the count of each of its 32 samples; ten bitwise operations per tick
-// and lane) and turned into per-sample totals once per block, where the
-// per-tick kernel transposes every tick's words.
+// Mapping: one workgroup per (core, neuron slice, 32-sample group), of 4
+// wavefronts that own 64 neurons each (two 32-neuron blocks; 32 neurons each
+// in 128-neuron slices and, on 8 wavefronts, with 512 axons). A wavefront's B
+// tiles (int8 planes) and potentials stay in registers for the block of ticks:
+// 128 + 32 of the 256 registers that two workgroups per CU leave a lane, so
+// the axon operands come from LDS in two halves, and what is only summed over
+// the block (spike words, axon spike counts) lives in LDS: a register spilled
+// to memory in the loop makes its reload wait for the history loads in flight
+// (794 us per level of 128 cores, 1024 samples and 32 ticks, against 566).
+// One workgroup of 8 wavefronts per 64 samples, whose barrier stops the whole
+// CU, took 587.
+// The MFMA chain of one neuron block (16 of 32 cycles each) and the vector
+// work of the other are independent, so the loop pairs them and the two pipes
+// of a SIMD run side by side; with one barrier per tick:
+//   first half   products of block 1, tick k; update of block 0, tick k;
+//                expansion of tick k + 1 to the int8 tile; axon words of tick
+//                k + 2 into LDS;
+//   barrier      (LDS only; the int8 tile and the axon words are doubled)
+//   second half  products of block 0, tick k + 1; update of block 1 and spike
+//                words of tick k; history bits of tick k + 3 transposed, those
+//                of tick k + 4 and the input of tick k + 3 loaded.
+// (One block per wavefront: products of tick k + 1 beside the update of tick
+// k.) Stores are issued after the loads of the same half, so no wait for a
+// load covers a store of its tick.
+// The two halves of a neuron's 16-bit fire masks are joined by one
+// v_permlane32_swap: lane (h, j) then holds the word of neuron j of block h.
+// Spike counts come from the lane's spike words at the end of the block, by
+// vertical counters (bit plane p of a lane holds bit p of the count of each of
+// its 32 samples), synaptic events from the axons' spike counts; the per-tick
+// kernel transposes and multiplies every tick's words for them.
+#include <type_traits>
+
 #include "kern_mfma_unit.h"
 
 namespace ranc {
 
 // Bit planes of the vertical counters: a block runs at most 2^6 - 1 ticks.
 static constexpr int TICK_PLANES = 6;
+// scheduling fence that scalar and memory instructions may cross
+static constexpr int SCHED_MEMORY_MAY_CROSS = 0x4 | 0x10 | 0x80;
+static constexpr uint32_t NO_SOURCE = 0xFFFFFFFFu;   // (a source entry is below 2^27)
 static_assert(MFMA_BLOCK_TICKS_MAX < (1 << TICK_PLANES), "vertical counters overflow");
 
-template <int A_, int N_, bool TWO, bool EXT>
-__global__ __launch_bounds__(512) void k_integrate_mfma_ticks(DevNet n, BlockArgs ba)
+// Four rows' compare, select and spike bit: v[i] = u[i] >= th ? r[i] : v[i],
+// f = 2 f + fire for i = 3 down to 0. Written out because the compiler turns
+// the spike bit into a select and a shift (two instructions); the compare's
+// lane mask is the carry of one add. Four compares come first, so each mask is
+// read at least three instructions after it was written (two are required).
+__device__ __forceinline__ void fire_rows(uint32_t &f, int32_t &v0, int32_t &v1, int32_t &v2, int32_t &v3, int32_t u0,
+                                          int32_t u1, int32_t u2, int32_t u3, int32_t r0, int32_t r1, int32_t r2,
+                                          int32_t r3, int32_t th)
 {
-    typedef MfmaLds<A_, N_> L;
-    constexpr int NB = N_ / 32;          // 32-neuron blocks (4 or 8)
-    constexpr int KS = A_ / 32;          // 32-axon k-steps
-    constexpr int PL = TWO ? 2 : 1;      // B planes
-    constexpr int STW = NB / 4;          // 32-sample sub-tiles per wave
-    constexpr int W_ = A_ / 32;          // axon words
-    constexpr int ROWB = L::ROWB;
-    constexpr int WPW = (W_ + 7) / 8;    // axon words expanded per wave
-    constexpr int APW = A_ / 64;         // 64-axon blocks of the gather
-    constexpr int GPW = APW == 8 ? 2 : 1;  // 32-sample groups gathered per wave
-    constexpr int FMAX = 4;              // sources per axon kept in registers
-    typedef typename RawWord<GPW == 2>::type RawT;
-    static_assert(NB == 4 || NB == 8, "N must be 128 or 256");
-    static_assert(!(TWO && A_ == 512), "the plane split has no block form");
+    uint64_t m1, m2, m3;
+    asm volatile("v_cmp_ge_i32_e64 %7, %11, %16\n\t"
+        "v_cmp_ge_i32_e64 %6, %10, %16\n\t"
+        "v_cmp_ge_i32_e64 %5, %9, %16\n\t"
+        "v_cmp_ge_i32_e32 vcc, %8, %16\n\t"
+        "v_cndmask_b32_e64 %4, %4, %15, %7\n\t"
+        "v_cndmask_b32_e64 %3, %3, %14, %6\n\t"
+        "v_cndmask_b32_e64 %2, %2, %13, %5\n\t"
+        "v_cndmask_b32_e32 %1, %1, %12, vcc\n\t"
+        "v_addc_co_u32_e64 %0, %7, %0, %0, %7\n\t"
+        "v_addc_co_u32_e64 %0, %6, %0, %0, %6\n\t"
+        "v_addc_co_u32_e64 %0, %5, %0, %0, %5\n\t"
+        "v_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
+        : "+v"(f), "+v"(v0), "+v"(v1), "+v"(v2), "+v"(v3), "=&s"(m1), "=&s"(m2), "=&s"(m3)
+        : "v"(u0), "v"(u1), "v"(u2), "v"(u3), "v"(r0), "v"(r1), "v"(r2), "v"(r3), "v"(th)
+        : "vcc");
+}
+// (the same with u = v and one reset value)
+__device__ __forceinline__ void fire_rows(uint32_t &f, int32_t &v0, int32_t &v1, int32_t &v2, int32_t &v3, int32_t rs,
+                                          int32_t th)
+{
+    uint64_t m1, m2, m3;
+    asm volatile("v_cmp_ge_i32_e64 %7, %4, %9\n\t"
+        "v_cmp_ge_i32_e64 %6, %3, %9\n\t"
+        "v_cmp_ge_i32_e64 %5, %2, %9\n\t"
+        "v_cmp_ge_i32_e32 vcc, %1, %9\n\t"
+        "v_cndmask_b32_e64 %4, %4, %8, %7\n\t"
+        "v_cndmask_b32_e64 %3, %3, %8, %6\n\t"
+        "v_cndmask_b32_e64 %2, %2, %8, %5\n\t"
+        "v_cndmask_b32_e32 %1, %1, %8, vcc\n\t"
+        "v_addc_co_u32_e64 %0, %7, %0, %0, %7\n\t"
+        "v_addc_co_u32_e64 %0, %6, %0, %0, %6\n\t"
+        "v_addc_co_u32_e64 %0, %5, %0, %0, %5\n\t"
+        "v_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
+        : "+v"(f), "+v"(v0), "+v"(v1), "+v"(v2), "+v"(v3), "=&s"(m1), "=&s"(m2), "=&s"(m3)
+        : "v"(rs), "v"(th)
+        : "vcc");
+}
 
-    __shared__ __attribute__((aligned(16))) typename L::ATile a_lds[2];
-    __shared__ typename L::XTile x_lds[2];
-    __shared__ unsigned s_cnt[CNT_N][MFMA_TS];
+// Wavefronts per workgroup and 32-neuron blocks per wavefront.
+template <int A_, int N_> struct TicksShape {
+    static constexpr int NPB = N_ == 256 && A_ <= 256 ? 2 : 1;
+    static constexpr int WAVES = N_ / 32 / NPB;
+};
+
+// MULTI: some axon has several sources (FMAX in registers, the rest read from
+// the table every tick).
+template <int A_, int N_, bool TWO, bool EXT, bool MULTI>
+__global__ __launch_bounds__((64 * TicksShape<A_, N_>::WAVES), (A_ == 512 && N_ == 128 ? 1 : 2)) void k_integrate_mfma_ticks(DevNet n, BlockArgs ba)
+{
+    constexpr int NPB = TicksShape<A_, N_>::NPB;
+    constexpr int WAVES = TicksShape<A_, N_>::WAVES;
+    constexpr int KS = A_ / 32;                // 32-axon k-steps
+    constexpr int KC = KS > 8 ? 8 : (TWO && NPB == 2 && KS > 4) ? 4 : KS;        // k-steps whose operands are held at a time
+    constexpr int PL = TWO ? 2 : 1;            // B planes
+    constexpr int W_ = A_ / 32;                // axon words
+    constexpr int ROWB = A_ + 16;              // padded LDS row of the int8 tile (bytes)
+    constexpr int WPW = (W_ + 2 * WAVES - 1) / (2 * WAVES);   // axon words expanded per lane
+    constexpr int APW = A_ / 64;               // 64-axon blocks of the gather
+    constexpr int GB = (APW + WAVES - 1) / WAVES;   // of them per wavefront
+    constexpr int FMAX = MULTI ? 4 : 1;        // sources per axon kept in registers
+    constexpr int THREADS = 64 * WAVES;
+    constexpr int TS = 32;                     // samples per workgroup
+
+    __shared__ __attribute__((aligned(16))) int8_t a_lds[2][TS * ROWB];
+    __shared__ uint32_t x_lds[2][TS][W_ + 1];
+    __shared__ unsigned s_cnt[CNT_N][TS];
+    // per lane: the spike word of every tick, and the spikes of each axon of
+    // the lane's words so far, one byte per axon
+    __shared__ uint32_t word_lds[MFMA_BLOCK_TICKS_MAX][THREADS];
+    __shared__ uint32_t spike_lds[WPW * 8][THREADS];
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    const int tiles = n.S64 / MFMA_TS;
+    const int groups = (n.S + TS - 1) / TS;
     int ci_, v;
-    core_unit_of(blockIdx.x, ba.count, n.slices * tiles, ci_, v);
+    core_unit_of(blockIdx.x, ba.count, n.slices * groups, ci_, v);
     const int c = ba.order[ba.first + ci_];
     const int slice = v % n.slices;
-    const int tile = v / n.slices;
-    const int s0 = tile * MFMA_TS;
+    const int grp = v / n.slices;
+    const int s0 = grp * TS;
     const int kb = ba.k0 + (ba.step - ba.level[c]) * ba.block;   // first tick (position in the call)
     const int ke = min(kb + ba.block, ba.k0 + ba.ticks);
     if (kb < ba.k0 || kb >= ke)
         return;   // whole workgroups, before any barrier
     const int h = lane >> 5, jj = lane & 31;
     const int sig = sigma32(jj);
-    const int nb = wave % NB;
-    const int stg = wave / NB;
-    const bool live = N_ == 256 || slice * NB + nb < n.NW;   // see integrate_mfma_unit
-    const int nbu = live ? nb : 0;
-    const int nbc = slice * NB + nbu;
+    // 32-neuron blocks of the core that this wavefront owns; 64-neuron cores
+    // run as a 128-neuron slice whose upper two blocks are dead (wave-uniform)
+    const int nb0 = slice * (N_ / 32) + wave * NPB;
+    const bool live = N_ == 256 || nb0 < n.NW;
+    const int nbu = live ? nb0 : 0;
 
-    for (int i = threadIdx.x; i < CNT_N * MFMA_TS; i += blockDim.x)
+    for (int i = threadIdx.x; i < CNT_N * TS; i += THREADS)
         (&s_cnt[0][0])[i] = 0u;
+#pragma unroll
+    for (int q = 0; q < WPW * 8; ++q)
+        spike_lds[q][threadIdx.x] = 0u;
 
-    // ---- sources of the gather's axon (lane = axon)
-    const bool gatherer = wave < 2 * APW;   // wave-uniform
-    const int axb = wave % APW;
-    const int grp = GPW == 2 ? 0 : wave / APW;
-    uint32_t e_beg = 0, e_end = 0;
-    if (gatherer) {
-        const int ga = axb * 64 + lane;
-        e_beg = n.rtx_ptr[(size_t)c * A_ + ga];
-        e_end = n.rtx_ptr[(size_t)c * A_ + ga + 1];
-    }
+    // ---- sources of the gather's axons (lane = axon of block wave + WAVES g)
+    const bool gatherer = APW >= WAVES || wave < APW;   // wave-uniform
     const size_t HG = (size_t)n.S64 / 64;
     const size_t CN = (size_t)n.C * n.N;
-    const size_t slot_words = CN * HG;       // history words per slot
-    int q_now = (n.tick[0] + kb) % n.Q, r_row = (n.tick[1] + kb) % n.RT;
-    const uint64_t *src_base[FMAX];          // slot 0 row of the source (neuron 0 where unused)
-    int src_slot[FMAX];                      // slot read for the next load
-    RawT src_mask[FMAX];                     // all ones where the source exists
+    const int Q = n.Q;
+    // (the ring is below 4 GiB: offsets into it fit 32 bits)
+    const uint32_t slot_bytes = (uint32_t)(CN * HG * 8), ring_bytes = (uint32_t)Q * slot_bytes;
+    const int q0 = (n.tick[0] + kb) % Q, r0 = (n.tick[1] + kb) % n.RT;
+    const char *hist_g = reinterpret_cast<const char *>(n.hist) + 4 * grp;   // the group's half words
+    // the first source as the offset of its word of the next tick to load
+    // (neuron 0 where the axon has none), the others as table entries
+    uint32_t src0[GB], mask0[GB], ents[GB][FMAX], e_beg[GB] = {}, e_end[GB] = {};
+    int delay0[GB];
+    bool long_lists = false;   // wave-uniform
 #pragma unroll
-    for (int k = 0; k < FMAX; ++k) {
-        const bool used = e_beg + k < e_end;
-        const uint32_t ent = used ? n.rtx_ent[e_beg + k] : 0u;
-        int slot = q_now - (int)(ent & 15u) - 1;
-        src_slot[k] = slot < 0 ? slot + n.Q : slot;
-        src_base[k] = n.hist + (size_t)(ent >> 4) * HG + tile;
-        src_mask[k] = used ? ~(RawT)0 : (RawT)0;
+    for (int g = 0; g < GB; ++g) {
+        if (gatherer) {
+            const int ga = (wave + WAVES * g) * 64 + lane;
+            e_beg[g] = n.rtx_ptr[(size_t)c * A_ + ga];
+            e_end[g] = n.rtx_ptr[(size_t)c * A_ + ga + 1];
+        }
+        const bool any = e_beg[g] < e_end[g];
+        const uint32_t ent0 = any ? n.rtx_ent[e_beg[g]] : 0u;
+        delay0[g] = (int)(ent0 & 15u) + 1;
+        src0[g] = (ent0 >> 4) * (uint32_t)(HG * 8) + (uint32_t)(q0 - delay0[g] + (q0 < delay0[g] ? Q : 0)) * slot_bytes;
+        mask0[g] = any ? ~0u : 0u;
+#pragma unroll
+        for (int k = 1; k < FMAX; ++k)
+            ents[g][k] = e_beg[g] + k < e_end[g] ? n.rtx_ent[e_beg[g] + k] : NO_SOURCE;
+        long_lists |= __ballot(e_end[g] - e_beg[g] > FMAX) != 0;
     }
-    const bool multi = __ballot(e_end - e_beg > 1) != 0;          // wave-uniform
-    const bool long_lists = __ballot(e_end - e_beg > FMAX) != 0;  // wave-uniform
-    auto raw_word = [&](const uint64_t *w) -> RawT {
-        if constexpr (GPW == 2)
-            return *w;
-        else
-            return reinterpret_cast<const uint32_t *>(w)[grp];
+    // History words of the next tick in order (q_load: its slot). Loads past
+    // the block read a slot of the ring that is never used.
+    int q_load = q0;
+    auto word_of = [&](uint32_t ent) -> uint32_t {
+        const int slot = q_load - (int)(ent & 15u) - 1;
+        return *reinterpret_cast<const uint32_t *>(hist_g + ((ent >> 4) * (uint32_t)(HG * 8) +
+                                                             (uint32_t)(slot < 0 ? slot + Q : slot) * slot_bytes));
     };
-    auto next_word = [&](int k) -> RawT {
-        const RawT w = raw_word(src_base[k] + (size_t)(unsigned)src_slot[k] * slot_words);
-        src_slot[k] = src_slot[k] + 1 == n.Q ? 0 : src_slot[k] + 1;
-        return w;
-    };
-    // history words of the next tick in order (called for kb, kb + 1, ...;
-    // q: that tick's slot). Loads past the block read a slot of the ring that
-    // is never used.
-    auto load_mask = [&](int q, RawT (&raw)[FMAX]) {
-        raw[0] = next_word(0);
-        if (multi) {
+    auto load_mask = [&](uint32_t (&raw)[GB][FMAX]) {
 #pragma unroll
-            for (int k = 1; k < FMAX; ++k)
-                raw[k] = next_word(k);
-            for (uint32_t e = e_beg + FMAX; long_lists && e < e_end; ++e) {
-                const uint32_t ent = n.rtx_ent[e];
-                int slot = q - (int)(ent & 15u) - 1;
-                if (slot < 0)
-                    slot += n.Q;
-                // (a lane with this source has all FMAX register sources)
-                raw[1] |= raw_word(n.hist + ((size_t)slot * CN + (ent >> 4)) * HG + tile);
+        for (int g = 0; g < GB; ++g)
+            raw[g][0] = *reinterpret_cast<const uint32_t *>(hist_g + src0[g]);
+        if constexpr (MULTI) {
+#pragma unroll
+            for (int g = 0; g < GB; ++g) {
+#pragma unroll
+                for (int k = 1; k < FMAX; ++k) {
+                    raw[g][k] = 0;
+                    if (ents[g][k] != NO_SOURCE)
+                        raw[g][k] = word_of(ents[g][k]);
+                }
+                for (uint32_t e = e_beg[g] + FMAX; long_lists && e < e_end[g]; ++e)
+                    raw[g][1] |= word_of(n.rtx_ent[e]);
             }
         }
+        q_load = q_load + 1 == Q ? 0 : q_load + 1;
+        // (sources of delay q_load go on from slot Q - 1 to slot 0)
+#pragma unroll
+        for (int g = 0; g < GB; ++g)
+            src0[g] += slot_bytes - (delay0[g] == q_load ? ring_bytes : 0);
     };
-    auto mask_of = [&](const RawT (&raw)[FMAX]) -> RawT {
-        RawT m = raw[0] & src_mask[0];
-        if (multi) {
+    // lane (h, j): bits of axon 32 h + j of the 64-axon block; after the
+    // transpose lane (h, i) holds the block's axon word h of the sample of bit i
+    auto words_of = [&](const uint32_t (&raw)[GB][FMAX], uint32_t (&t)[GB]) {
+#pragma unroll
+        for (int g = 0; g < GB; ++g) {
+            uint32_t m = raw[g][0] & mask0[g];
 #pragma unroll
             for (int k = 1; k < FMAX; ++k)
-                m |= raw[k] & src_mask[k];
+                m |= raw[g][k];
+            t[g] = transpose32(m, lane);
         }
-        return m;
     };
-    auto transpose_store = [&](RawT m, int buf) {
+    auto store_words = [&](const uint32_t (&t)[GB], int buf) {
 #pragma unroll
-        for (int g = 0; g < GPW; ++g) {
-            const uint32_t t = transpose32((uint32_t)(m >> (32 * g)), lane);
-            x_lds[buf][32 * (GPW == 2 ? g : grp) + sig][2 * axb + h] = t;
-        }
+        for (int g = 0; g < GB; ++g)
+            x_lds[buf][sig][2 * (wave + WAVES * g) + h] = t[g];
     };
+    // external input words of the next tick in order: lane (h, j) takes words
+    // 2 (wave + WAVES w) + h of sample s0 + j (a row of zeros where the core
+    // takes none); the last tick of the block is loaded again past its end
     const int ci = n.in_index[c];
-    const bool svalid = s0 + lane < n.S;
-    const uint32_t *ext_s =
-        (ba.ext_base != nullptr && ci >= 0)
-            ? ba.ext_base + (size_t)min(s0 + lane, n.S - 1) * ba.ext_sstride + (size_t)kb * ba.tick_words + (size_t)ci * W_
-            : nullptr;
-    uint32_t xe[WPW];
+    const bool has_ext = ba.ext_base != nullptr && ci >= 0;
+    const uint32_t svalid = s0 + jj < n.S ? ~0u : 0u;
+    const uint32_t *ext_t = has_ext ? ba.ext_base + (size_t)s0 * ba.ext_sstride + (size_t)kb * ba.tick_words + (size_t)ci * W_
+                                    : reinterpret_cast<const uint32_t *>(n.hist_zero);   // uniform
+    const uint32_t ext_s = has_ext ? (uint32_t)(min(jj, n.S - 1 - s0) * ba.ext_sstride) : 0u;
+    const long long ext_step = has_ext ? ba.tick_words : 0;
+    int k_ext = kb;
+    uint32_t xe[WPW], xn[WPW];
+    auto load_ext = [&]() {
 #pragma unroll
-    for (int k = 0; k < WPW; ++k)
-        xe[k] = 0u;
-    auto load_ext = [&]() {   // external input words of the next tick in order
-        if (!ext_s)
-            return;
-#pragma unroll
-        for (int k = 0; k < WPW; ++k) {
-            const int wi = wave + 8 * k;
-            if (wi < W_)
-                xe[k] = ext_s[wi];
-        }
-        ext_s += ba.tick_words;
+        for (int w = 0; w < WPW; ++w)
+            xe[w] = ext_t[ext_s + min(2 * (wave + WAVES * w) + h, W_ - 1)];
+        ++k_ext;
+        ext_t += k_ext < ke ? ext_step : 0;
     };
-    RawT raw[FMAX] = {};
-    if (gatherer)
-        load_mask(q_now, raw);
+    auto take_ext = [&]() {   // the loaded words are waited for here
+#pragma unroll
+        for (int w = 0; w < WPW; ++w) {
+            xn[w] = xe[w];
+            asm volatile("" : "+v"(xn[w]));
+        }
+    };
+    uint32_t raw0[GB][FMAX] = {}, raw1[GB][FMAX] = {}, raw2[GB][FMAX] = {};
+    if (gatherer) {
+        load_mask(raw0);
+        load_mask(raw1);
+        load_mask(raw2);
+    }
     load_ext();
 
-    // ---- what stays in registers for the block
-    v4i breg[KS][PL];
-    {
-        const v4i *planes = reinterpret_cast<const v4i *>(n.planes);
+    // ---- what stays in registers for the block of ticks
+    v4i breg[NPB][KS][PL];
+    const v4i *planes = reinterpret_cast<const v4i *>(n.planes);
+#pragma unroll
+    for (int t = 0; t < NPB; ++t)
 #pragma unroll
         for (int k = 0; k < KS; ++k)
 #pragma unroll
             for (int p = 0; p < PL; ++p)
-                breg[k][p] = planes[((((size_t)c * n.NW + nbc) * KS + k) * PL + p) * 64 + lane];
-    }
-    const size_t cj = (size_t)c * n.N + slice * N_ + nbu * 32 + jj;
-    const int32_t lk = n.leak[cj], th = n.thr[cj], rs = n.rst[cj];
+                breg[t][k][p] = planes[((((size_t)c * n.NW + nbu + t) * KS + k) * PL + p) * 64 + lane];
+    const size_t cj = (size_t)c * n.N + nbu * 32 + jj;   // neuron of block 0
     const int32_t vmin = n.vmin, vmax = n.vmax;
-    int32_t fl = vmin;
-    bool lin = false;
-    if constexpr (EXT) {
-        fl = n.floor[cj];
-        lin = (n.linmask[cj >> 5] >> (cj & 31)) & 1u;
-    }
-    const int oi = n.outidx[cj];
-    const uint32_t cm32 = n.coremask[(size_t)c * n.NW + nbc];
-    const uint32_t om32 = n.outmask[(size_t)c * n.NW + nbc];
-    const size_t dg = (size_t)c * n.slices + slice;
-    uint32_t degl[WPW][8], degh[WPW][8];
-    bool any_hi = false;
+    int32_t lk[NPB], th[NPB], rs[NPB], fl[NPB];
+    bool lin[NPB];
 #pragma unroll
-    for (int k = 0; k < WPW; ++k) {
-        const int wi = wave + 8 * k;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            degl[k][q] = wi < W_ ? n.degb[(dg * 2 + 0) * (A_ / 4) + wi * 8 + q] : 0u;
-            degh[k][q] = wi < W_ ? n.degb[(dg * 2 + 1) * (A_ / 4) + wi * 8 + q] : 0u;
-            any_hi |= degh[k][q] != 0u;
+    for (int t = 0; t < NPB; ++t) {
+        lk[t] = n.leak[cj + 32 * t];
+        th[t] = n.thr[cj + 32 * t];
+        rs[t] = n.rst[cj + 32 * t];
+        fl[t] = vmin;
+        lin[t] = false;
+        if constexpr (EXT) {
+            fl[t] = n.floor[cj + 32 * t];
+            lin[t] = (n.linmask[(cj >> 5) + t] >> jj) & 1u;
         }
     }
-    v4i *vb = reinterpret_cast<v4i *>(n.V) + ((size_t)c * n.NW + nbc) * (2 * HG) * 256 + lane;
-    v4i vr[STW][4];   // potentials: element (t, q, e) = row 8q + 4h + e of sub-tile stg * STW + t
+    v4i *vb = reinterpret_cast<v4i *>(n.V) + (((size_t)c * n.NW + nbu) * (2 * HG) + grp) * 256 + lane;
+    const size_t vb_step = 2 * HG * 256;   // to the next neuron block
+    v4i vr[NPB][4];   // potentials: element (t, q, e) = neuron j of block t, sample 8q + 4h + e
 #pragma unroll
-    for (int t = 0; t < STW; ++t)
+    for (int t = 0; t < NPB; ++t)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            vr[t][q] = __builtin_nontemporal_load(vb + ((size_t)(2 * tile + stg * STW + t) * 4 + q) * 64);
+            vr[t][q] = __builtin_nontemporal_load(vb + t * vb_step + q * 64);
 
-    // sub-tiles whose samples end before their 32 rows: rows that exist
-    uint32_t vm[STW];
-#pragma unroll
-    for (int t = 0; t < STW; ++t) {
-        vm[t] = 0;
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-            vm[t] |= (uint32_t)(s0 + 32 * (stg * STW + t) + 8 * (r >> 2) + 4 * h + (r & 3) < n.S) << r;
-    }
-    // the lane's 32-sample half-word of its neuron's history and raster words
-    // (two sub-tiles per wave: lane half h stores sub-tile h)
-    const int half = STW == 2 ? h : stg;
-    const bool writer = live && (STW == 2 || h == 0);
-    uint32_t *hist_w = reinterpret_cast<uint32_t *>(n.hist + cj * HG + tile) + half;
-    uint32_t *rast_w = oi >= 0 ? reinterpret_cast<uint32_t *>(reinterpret_cast<uint64_t *>(n.raster) + (size_t)oi * HG + tile) + half
-                               : nullptr;
-    const size_t rast_row = 2 * (size_t)n.Nout * HG;   // u32 words per raster row
+    // spike-word bits whose samples exist
+    uint32_t vmask = 0;
+    for (int b = 0; b < 32; ++b)
+        vmask |= (uint32_t)(s0 + sigma32(b) < n.S) << b;
+    // the lane's neuron when spike words are written (two blocks: lane half h
+    // writes block h) and its history and raster words of the group
+    const int tw_ = NPB == 2 ? h : 0;
+    const size_t cw = cj + 32 * tw_;
+    const bool writer = live && (NPB == 2 || h == 0);
+    const uint32_t hist_o = (uint32_t)(cw * (HG * 8)) + 4 * grp;
+    const int oi = n.outidx[cw];
+    const uint32_t rast_o = (uint32_t)(oi >= 0 ? oi : 0) * (uint32_t)(HG * 8) + 4 * grp;   // (a row is below 4 GiB)
+    const size_t row_bytes = (size_t)n.Nout * HG * 8;
+    int q_now = q0, r_row = r0;
+    unsigned pdl = 0;          // delivered spikes in the lane's words
 
-    uint32_t plane[TICK_PLANES];
+    // axon words of tick i of the block (i < ticks: on = ~0, else 0) to int8
+    auto expand = [&](int i, uint32_t on) {
 #pragma unroll
-    for (int i = 0; i < TICK_PLANES; ++i)
-        plane[i] = 0u;
-    unsigned pev = 0, pevh = 0, pdl = 0;   // events (by low and high degree bytes), delivered, of sample s0 + lane
-
-    RawT m = 0;
-    if (gatherer) {
-        transpose_store(mask_of(raw), 0);
-        load_mask(q_now + 1 == n.Q ? 0 : q_now + 1, raw);
-        m = mask_of(raw);
-    }
-    lds_barrier();
-
-#pragma unroll 1
-    for (int k = kb; k < ke; ++k) {
-        const int buf = (k - kb) & 1;
-        int8_t *A = a_lds[buf];
-        // A. expansion of tick k, then the words of tick k + 1 into LDS and
-        //    the loads for tick k + 2 (history) and k + 1 (input)
-#pragma unroll
-        for (int i = 0; i < WPW; ++i) {
-            const int wi = wave + 8 * i;
-            if (wi < W_) {
-                const uint32_t xd = x_lds[buf][lane][wi];
-                const uint32_t x = xd | (svalid ? xe[i] : 0u);
+        for (int w = 0; w < WPW; ++w) {
+            const int wi = 2 * (wave + WAVES * w) + h;
+            if (2 * WAVES * (w + 1) <= W_ || wave + WAVES * w < W_ / 2) {   // wave-uniform
+                const uint32_t xd = x_lds[i & 1][jj][wi] & on;
+                const uint32_t x = xd | (xn[w] & svalid & on);
                 pdl += (unsigned)__popc(xd);
                 uint32_t d[8];
 #pragma unroll
                 for (int q = 0; q < 8; ++q) {
+                    // nibble b3b2b1b0 -> bytes: bit i moves to bit 8i, no carries
                     d[q] = (((x >> (4 * q)) & 0xFu) * 0x00204081u) & 0x01010101u;
-                    pev = __builtin_amdgcn_udot4(d[q], degl[i][q], pev, false);
-                    if (any_hi)
-                        pevh = __builtin_amdgcn_udot4(d[q], degh[i][q], pevh, false);
+                    atomicAdd(&spike_lds[8 * w + q][threadIdx.x], d[q]);
                 }
-                v4i *dst = reinterpret_cast<v4i *>(&A[lane * ROWB + 32 * wi]);
+                v4i *dst = reinterpret_cast<v4i *>(&a_lds[i & 1][jj * ROWB + 32 * wi]);
                 dst[0] = v4i{(int)d[0], (int)d[1], (int)d[2], (int)d[3]};
                 dst[1] = v4i{(int)d[4], (int)d[5], (int)d[6], (int)d[7]};
             }
         }
-        const bool more = k + 1 < ke;
-        if (more) {
-            if (gatherer) {
-                transpose_store(m, buf ^ 1);
-                int q2 = q_now + 2;
-                load_mask(q2 >= n.Q ? q2 - n.Q : q2, raw);
-            }
-            load_ext();
+    };
+    // axon operands of k-steps [k, k + KC) of tick i of the block
+    v4i ax[KC];
+    auto load_axons = [&](int i, int k) {
+        const int8_t *arow = &a_lds[i & 1][jj * ROWB + 16 * h];
+#pragma unroll
+        for (int s = 0; s < KC; ++s)
+            ax[s] = *reinterpret_cast<const v4i *>(arow + 32 * (k + s));
+    };
+    // leak, threshold and reset of samples 8q + 4h + [0, 4) of block t from
+    // their input plus leak; f = fire bits so far, doubled per row
+    auto update_rows = [&](const v16i &a, int t, int q, uint32_t &f) {
+        int32_t u[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            u[e] = __builtin_elementwise_add_sat(vr[t][q][e], a[4 * q + e]);
+            if constexpr (EXT)
+                u[e] = min(max(u[e], vmin), vmax);
         }
+        if constexpr (EXT) {
+            int32_t v[4], r[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                v[e] = max(u[e], fl[t]);
+                r[e] = lif_reset(u[e], th[t], rs[t], vmax, lin[t]);
+            }
+            fire_rows(f, v[0], v[1], v[2], v[3], u[0], u[1], u[2], u[3], r[0], r[1], r[2], r[3], th[t]);
+            vr[t][q] = v4i{v[0], v[1], v[2], v[3]};
+        } else {
+            fire_rows(f, u[0], u[1], u[2], u[3], rs[t], th[t]);
+            vr[t][q] = v4i{u[0], u[1], u[2], u[3]};
+        }
+    };
+    // Products of block tp on the loaded operands (tick i of the block of
+    // ticks), plus leak, into `out`, beside the update of block tu from `in`
+    // (tu < 0: none); returns the update's fire bits. Two planes go through
+    // one accumulator: the high plane's sums are shifted up in place and the
+    // low plane's added on (16 registers fewer than two sums). The scheduling
+    // fences keep the update spread over the first plane's products; the
+    // second plane's run beside what follows.
+    auto products = [&](auto tp_, auto tu_, int i, v16i &out, const v16i &in) -> uint32_t {
+        constexpr int tp = decltype(tp_)::value, tu = decltype(tu_)::value;
+        uint32_t f = 0;
+        v16i a;
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            a[r] = TWO ? 0 : lk[tp];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+#pragma unroll
+            for (int s = q * KS / 4; s < (q + 1) * KS / 4; ++s) {
+                if (KS > KC && s > 0 && s % KC == 0)
+                    load_axons(i, s);
+                a = __builtin_amdgcn_mfma_i32_32x32x32_i8(ax[s % KC], breg[tp][s][0], a, 0, 0, 0);
+            }
+            if constexpr (tu >= 0) {
+                update_rows(in, tu, 3 - q, f);
+                __builtin_amdgcn_sched_barrier(SCHED_MEMORY_MAY_CROSS);
+            }
+        }
+        if constexpr (TWO) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                a[r] = a[r] * 128 + lk[tp];
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                if (KS > KC && s % KC == 0)
+                    load_axons(i, s);
+                a = __builtin_amdgcn_mfma_i32_32x32x32_i8(ax[s % KC], breg[tp][s][1], a, 0, 0, 0);
+            }
+            if (KS > KC && NPB == 2 && tp == 0)
+                load_axons(i, 0);   // for block 1
+        }
+        out = a;
+        return f;
+    };
+    constexpr std::integral_constant<int, 0> blk0{};
+    constexpr std::integral_constant<int, NPB - 1> blk1{};
+    constexpr std::integral_constant<int, -1> no_update{};
+
+    uint32_t tw[GB] = {};   // axon words of the tick two ahead
+    if (gatherer) {
+        words_of(raw0, tw);
+        store_words(tw, 0);
+        words_of(raw1, tw);
+        store_words(tw, 1);
+        words_of(raw2, tw);
+        load_mask(raw0);
+    }
+    lds_barrier();
+    const int ticks = ke - kb;
+    take_ext();
+    load_ext();
+    expand(0, ~0u);
+    take_ext();
+    load_ext();
+    lds_barrier();
+    v16i acc0, acc1;
+    load_axons(0, 0);
+    products(blk0, no_update, 0, acc0, acc0);
+
+#pragma unroll 1
+    for (int i = 0; i < ticks; ++i) {
+        // first half
+        uint32_t hb[NPB];
+        if constexpr (NPB == 2)
+            hb[0] = products(blk1, blk0, i, acc1, acc0);
+        expand(i + 1, i + 1 < ticks ? ~0u : 0u);
+        if (gatherer)
+            store_words(tw, i & 1);
         lds_barrier();
 
-        // C. products and potential update
-        uint32_t hb[STW];
-        if (live) {
-#pragma unroll
-            for (int t = 0; t < STW; ++t) {
-                v16i acc_lo, acc_hi;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    acc_lo[r] = lk;
-                    acc_hi[r] = 0;
-                }
-                const int8_t *arow = &A[((stg * STW + t) * 32 + jj) * ROWB + 16 * h];
-#pragma unroll
-                for (int s = 0; s < KS; ++s) {
-                    const v4i a = *reinterpret_cast<const v4i *>(arow + 32 * s);
-                    if constexpr (TWO) {
-                        acc_hi = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, breg[s][0], acc_hi, 0, 0, 0);
-                        acc_lo = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, breg[s][1], acc_lo, 0, 0, 0);
-                    } else {
-                        acc_lo = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, breg[s][0], acc_lo, 0, 0, 0);
-                    }
-                }
-                uint32_t f = 0;
-#pragma unroll
-                for (int r = 15; r >= 0; --r) {
-                    const int32_t in_leak = TWO ? acc_lo[r] + acc_hi[r] * 128 : acc_lo[r];
-                    int32_t u = __builtin_elementwise_add_sat(vr[t][r >> 2][r & 3], in_leak);
-                    if constexpr (EXT)
-                        u = min(max(u, vmin), vmax);
-                    const bool fire = u >= th;
-                    if constexpr (EXT)
-                        vr[t][r >> 2][r & 3] = fire ? lif_reset(u, th, rs, vmax, lin) : max(u, fl);
-                    else
-                        vr[t][r >> 2][r & 3] = fire ? rs : u;
-                    f = f + f + (uint32_t)fire;
-                }
-                hb[t] = f & vm[t];
-            }
+        // second half
+        load_axons(i + 1, 0);
+        if (gatherer) {
+            words_of(raw0, tw);
+            load_mask(raw0);
         }
-        // D. wait for the loads of A, then store the spike words
-        if (gatherer && more)
-            m = mask_of(raw);
-        asm volatile("" : "+v"(m));
-#pragma unroll
-        for (int i = 0; i < WPW; ++i)
-            asm volatile("" : "+v"(xe[i]));
-        if (live) {
-            // lane (h, j), two sub-tiles: fire bits of rows 4h' of sub-tile h,
-            // h' = 0 in lo, 1 in hi; one sub-tile: both halves the same
-            const auto sw = __builtin_amdgcn_permlane32_swap(hb[0], hb[STW - 1], false, false);
-            const uint32_t word = (uint32_t)sw[0] | ((uint32_t)sw[1] << 16);
-            if (writer) {
-                hist_w[(size_t)(unsigned)q_now * (2 * slot_words)] = word;
-                if (rast_w)
-                    rast_w[(size_t)(unsigned)r_row * rast_row] = word;
-            }
-            uint32_t carry = word;
-#pragma unroll
-            for (int i = 0; i < TICK_PLANES; ++i) {
-                const uint32_t up = plane[i] & carry;
-                plane[i] ^= carry;
-                carry = up;
-            }
+        take_ext();
+        load_ext();
+        if constexpr (NPB == 2) {
+            hb[1] = products(blk0, blk1, i + 1, acc0, acc1);
+        } else {
+            hb[0] = products(blk0, blk0, i + 1, acc1, acc0);
+            acc0 = acc1;
         }
-        q_now = q_now + 1 == n.Q ? 0 : q_now + 1;
+        // lane (h, j), two blocks: fire bits of samples 4h' of neuron j of
+        // block h, h' = 0 in the low half, 1 in the high; one block: its word
+        // in both lane halves
+        const auto sw = __builtin_amdgcn_permlane32_swap(hb[0], hb[NPB - 1], false, false);
+        const uint32_t word = ((uint32_t)sw[0] | ((uint32_t)sw[1] << 16)) & vmask;
+        word_lds[i][threadIdx.x] = word;
+        if (writer) {
+            *reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(n.hist) + (size_t)(unsigned)q_now * slot_bytes + hist_o) = word;
+            if (oi >= 0)
+                *reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(n.raster) + (unsigned)r_row * row_bytes + rast_o) = word;
+        }
+        q_now = q_now + 1 == Q ? 0 : q_now + 1;
         r_row = r_row + 1 == n.RT ? 0 : r_row + 1;
     }
 
     // ---- end of the block: potentials back, counts into the totals
     if (live) {
 #pragma unroll
-        for (int t = 0; t < STW; ++t)
+        for (int t = 0; t < NPB; ++t)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                __builtin_nontemporal_store(vr[t][q], vb + ((size_t)(2 * tile + stg * STW + t) * 4 + q) * 64);
+                __builtin_nontemporal_store(vr[t][q], vb + t * vb_step + q * 64);
+        const uint32_t cm32 = n.coremask[(size_t)c * n.NW + nbu + tw_], om32 = n.outmask[(size_t)c * n.NW + nbu + tw_];
+        // vertical counters over the block's spike words: bit plane p of a lane
+        // holds bit p of the count of each of its 32 samples
+        uint32_t plane[TICK_PLANES] = {};
+        for (int i = 0; i < ticks; ++i) {
+            uint32_t carry = word_lds[i][threadIdx.x];
+#pragma unroll
+            for (int p = 0; p < TICK_PLANES; ++p) {
+                const uint32_t up = plane[p] & carry;
+                plane[p] ^= carry;
+                carry = up;
+            }
+        }
         unsigned em = 0, ro = 0, ou = 0;
 #pragma unroll
-        for (int i = 0; i < TICK_PLANES; ++i) {
-            const uint32_t sw = transpose32(plane[i], lane);
-            em += (unsigned)__popc(sw) << i;
-            ro += (unsigned)__popc(sw & cm32) << i;
-            ou += (unsigned)__popc(sw & om32) << i;
+        for (int p = 0; p < TICK_PLANES; ++p) {
+            const uint32_t sw = transpose32(plane[p], lane);
+            em += (unsigned)__popc(sw) << p;
+            ro += (unsigned)__popc(sw & cm32) << p;
+            ou += (unsigned)__popc(sw & om32) << p;
         }
-        if (STW == 2 || h == 0) {
-            const int sl = 32 * half + sig;
-            atomicAdd(&s_cnt[CNT_EMITTED][sl], em);
-            atomicAdd(&s_cnt[CNT_ROUTED][sl], ro);
-            atomicAdd(&s_cnt[CNT_OUT][sl], ou);
+        if (NPB == 2 || h == 0) {
+            atomicAdd(&s_cnt[CNT_EMITTED][sig], em);
+            atomicAdd(&s_cnt[CNT_ROUTED][sig], ro);
+            atomicAdd(&s_cnt[CNT_OUT][sig], ou);
         }
     }
-    atomicAdd(&s_cnt[CNT_EVENTS][lane], pev + (pevh << 8));
-    atomicAdd(&s_cnt[CNT_DELIVERED][lane], pdl);
+    // synaptic events: each axon's spikes times its connected neurons
+    unsigned pev = 0, pevh = 0;
+    const size_t dg = (size_t)c * n.slices + slice;
+#pragma unroll
+    for (int w = 0; w < WPW; ++w) {
+        const int wi = min(2 * (wave + WAVES * w) + h, W_ - 1);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            pev = __builtin_amdgcn_udot4(spike_lds[8 * w + q][threadIdx.x], n.degb[(dg * 2 + 0) * (A_ / 4) + wi * 8 + q], pev, false);
+            pevh = __builtin_amdgcn_udot4(spike_lds[8 * w + q][threadIdx.x], n.degb[(dg * 2 + 1) * (A_ / 4) + wi * 8 + q], pevh, false);
+        }
+    }
+    atomicAdd(&s_cnt[CNT_EVENTS][jj], pev + (pevh << 8));
+    atomicAdd(&s_cnt[CNT_DELIVERED][jj], pdl);
     lds_barrier();
-    if (threadIdx.x < MFMA_TS && s0 + (int)threadIdx.x < n.S) {
+    if (threadIdx.x < TS && s0 + (int)threadIdx.x < n.S) {
         unsigned long long *cp = n.cnt + (((size_t)c * n.cnt_rows + slice) * n.S + s0 + threadIdx.x) * CNT_N;
 #pragma unroll
         for (int i = 0; i < CNT_N; ++i)
@@ -407,10 +558,13 @@ __global__ __launch_bounds__(512) void k_integrate_mfma_ticks(DevNet n, BlockArg
 template <int A_, int N_, bool TWO>
 static void launch_ticks_k(const DevNet &n, const BlockArgs &a, unsigned grid, hipStream_t st)
 {
-    if (n.model_ext)
-        hipLaunchKernelGGL((k_integrate_mfma_ticks<A_, N_, TWO, true>), dim3(grid), dim3(512), 0, st, n, a);
-    else
-        hipLaunchKernelGGL((k_integrate_mfma_ticks<A_, N_, TWO, false>), dim3(grid), dim3(512), 0, st, n, a);
+    const dim3 block(64 * TicksShape<A_, N_>::WAVES);
+    switch ((n.model_ext ? 2 : 0) + (a.multi ? 1 : 0)) {
+    case 0: hipLaunchKernelGGL((k_integrate_mfma_ticks<A_, N_, TWO, false, false>), dim3(grid), block, 0, st, n, a); break;
+    case 1: hipLaunchKernelGGL((k_integrate_mfma_ticks<A_, N_, TWO, false, true>), dim3(grid), block, 0, st, n, a); break;
+    case 2: hipLaunchKernelGGL((k_integrate_mfma_ticks<A_, N_, TWO, true, false>), dim3(grid), block, 0, st, n, a); break;
+    default: hipLaunchKernelGGL((k_integrate_mfma_ticks<A_, N_, TWO, true, true>), dim3(grid), block, 0, st, n, a); break;
+    }
 }
 
 template <int A_, int N_>
@@ -431,13 +585,21 @@ bool mfma_ticks_supported(int A, int N, int two_planes)
     return mfma_shape_supported(A, N, two_planes) && A * (two_planes ? 2 : 1) <= 512;
 }
 
+// Offsets into the history ring, a raster row and a group's inputs fit 32 bits.
+bool mfma_ticks_offsets_fit(int C, int N, int S64, int Q, int Nout, long long ext_sstride)
+{
+    const unsigned long long word = (unsigned long long)S64 / 64 * 8, lim = 1ull << 32;
+    return (unsigned long long)C * N * word * Q < lim && (unsigned long long)Nout * word < lim &&
+           (unsigned long long)ext_sstride * 32 < lim / 4;
+}
+
 hipError_t launch_integrate_mfma_ticks(const DevNet &n, const BlockArgs &a, int two, hipStream_t st)
 {
-    const long long grid = (long long)a.count * n.slices * (n.S64 / MFMA_TS);
+    const long long grid = (long long)a.count * n.slices * ((n.S + 31) / 32);   // 32 samples per workgroup
     if (!mfma_ticks_supported(n.A, n.N, two) || n.slices != mfma_slices(n.A, n.N, two) || n.cnt_rows != n.slices ||
         n.vlayout != VLAYOUT_BRICK || n.S64 % MFMA_TS || n.S > n.S64 || !n.planes || !a.order || !a.level ||
         a.first < 0 || a.count < 1 || a.first + a.count > n.C || a.block < 1 || a.block > MFMA_BLOCK_TICKS_MAX ||
-        a.ticks < 1 || a.ticks + n.D > n.Q || a.k0 < 0 || a.k0 + a.ticks > n.RT || grid > INT32_MAX)
+        a.ticks < 1 || a.ticks + n.D > n.Q || !mfma_ticks_offsets_fit(n.C, n.N, n.S64, n.Q, n.Nout, a.ext_sstride) || a.k0 < 0 || a.k0 + a.ticks > n.RT || grid > INT32_MAX)
         return hipErrorInvalidValue;
     const int w = mfma_width(n.A, n.N, two);
     switch (n.A * 2 + (w == 256 ? 1 : 0)) {

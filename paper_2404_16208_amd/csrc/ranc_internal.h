@@ -145,6 +145,7 @@ struct BlockArgs {
     const int32_t *level;       // level of each core [C]
     int first, count;
     int step, block, k0, ticks;
+    int multi;                  // some axon has several sources
     const uint32_t *ext_base;   // external input as in ResidentArgs, or nullptr
     long long ext_sstride;
     long long tick_words;
@@ -274,6 +275,7 @@ hipError_t launch_integrate_mfma(const DevNet &n, const TickArgs &a, int two_pla
 // the totals.
 hipError_t launch_integrate_mfma_ticks(const DevNet &n, const BlockArgs &a, int two_planes, hipStream_t st);
 bool mfma_ticks_supported(int A, int N, int two_planes);
+bool mfma_ticks_offsets_fit(int C, int N, int S64, int Q, int Nout, long long ext_sstride);
 // State-resident MFMA tick loop (N = 256 in one slice, A <= 256, at most
 // resident_max_cores_per_wg() cores per workgroup): zeroes the sync words,
 // then launches `grid` workgroups cooperatively.

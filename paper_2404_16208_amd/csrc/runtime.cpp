@@ -72,6 +72,7 @@ struct Plan {
     // `order` (levels + 1 entries), and the ticks a segment of a call may run
     // at most (the history ring holds D more). No levels: tick by tick.
     int levels = 0, seg_ticks = 1;
+    bool multi_source = false;   // some axon has several sources
     std::vector<int32_t> order, level, level_first;
 };
 
@@ -233,6 +234,14 @@ bool feed_forward_levels(const ranc_net_desc *d, Plan &p)
     }
     if ((int)ready.size() != C)
         return false;
+    std::vector<bool> taken((size_t)C * d->num_axons, false);
+    p.multi_source = false;
+    for (size_t i = 0; i < (size_t)C * N && !p.multi_source; ++i)
+        if (d->dest_kind[i] == RANC_DEST_CORE) {
+            const size_t at = (size_t)dest(i) * d->num_axons + d->dest_axon[i];
+            p.multi_source = taken[at];
+            taken[at] = true;
+        }
     p.levels = top + 1;
     p.level_first.assign(p.levels + 1, 0);
     for (int c = 0; c < C; ++c)
@@ -278,10 +287,15 @@ ranc_status make_plan(const ranc_net_desc *d, int32_t S, int32_t RT, int32_t pat
         return fail(RANC_EUNSUPPORTED, "sparse path does not support N=%d with G=%d", p.N, p.G);
     p.path = path;
     // segments of at most 32 ticks: the history ring then takes about as much
-    // memory as the potentials (one bit per tick against 32)
-    if (blocks && path == RANC_PATH_MFMA && RT > 1 && mfma_ticks_supported(p.A, p.N, p.two) && feed_forward_levels(d, p)) {
-        p.seg_ticks = std::min(RT, MFMA_BLOCK_TICKS_MAX);
-        p.Q = p.D + p.seg_ticks;
+    // memory as the potentials (one bit per tick against 32); and below 4 GiB
+    if (blocks && path == RANC_PATH_MFMA && RT > 1 && mfma_ticks_supported(p.A, p.N, p.two)) {
+        const long long slot = (long long)p.C * p.N * (p.S64 / 64) * 8;
+        const long long seg = std::min<long long>(std::min(RT, MFMA_BLOCK_TICKS_MAX), ((1LL << 32) - 1) / slot - p.D);
+        if (seg > 1 && mfma_ticks_offsets_fit(p.C, p.N, p.S64, p.D + (int)seg, p.C * p.N, (long long)RT * p.Cin * p.W) &&
+            feed_forward_levels(d, p)) {
+            p.seg_ticks = (int)seg;
+            p.Q = p.D + p.seg_ticks;
+        }
     }
     p.slices = path == RANC_PATH_MFMA ? mfma_slices(p.A, p.N, p.two)
              : path == RANC_PATH_SPARSE ? p.N / sparse_slice_width(p.N) : 1;
@@ -867,19 +881,24 @@ struct BlockPlan {
     bool skewed = false;
 };
 
-// The cheapest form by the time of its launches, in microseconds.
+// The cheapest form by the time of its launches, in microseconds. Measured on
+// 256 x 256 cores with 9-bit weights: a launch of the multi-tick kernel takes
+// about 8 us to set up and, per tick, 2.2 us while its workgroups (core,
+// slice, 32 samples) have a CU each and 3.5 us per further two per CU; a
+// tick-by-tick launch 4 us and 7 us per (core, slice, 64 samples) and CU.
 static BlockPlan choose_blocks(const Plan &p, int T)
 {
     BlockPlan best;
     if (!p.levels || T < 2)
         return best;
-    const long long tiles = p.S64 / 64;
-    auto rounds = [&](long long cores) { return (cores * p.slices * tiles + 255) / 256; };
-    const double launch = 4.0, setup = 4.0, tick = 2.0, single = 7.0;
-    double cost = T * (launch + single * std::max(1.0, (double)p.C * p.slices * tiles / 256.0));
+    auto launch = [&](long long cores, int ticks) {
+        const long long units = cores * p.slices * ((p.S + 31) / 32);
+        return units <= 256 ? 8.0 + 2.2 * ticks : 8.0 + (3.5 * ticks + 4.0) * ((units + 511) / 512);
+    };
+    double cost = T * (4.0 + 7.0 * std::max(1.0, (double)p.C * p.slices * (p.S64 / 64) / 256.0));
     double seq = 0;
     for (int l = 0; l < p.levels; ++l)
-        seq += launch + rounds(p.level_first[l + 1] - p.level_first[l]) * (setup + T * tick);
+        seq += launch(p.level_first[l + 1] - p.level_first[l], T);
     if (seq < cost) {
         cost = seq;
         best.block = T;
@@ -889,7 +908,7 @@ static BlockPlan choose_blocks(const Plan &p, int T)
         double skew = 0;
         for (int s = 0; s < nb + p.levels - 1; ++s) {
             const int lo = std::max(0, s - nb + 1), hi = std::min(s, p.levels - 1);
-            skew += launch + rounds(p.level_first[hi + 1] - p.level_first[lo]) * (setup + b * tick);
+            skew += launch(p.level_first[hi + 1] - p.level_first[lo], b);
         }
         if (skew < cost) {
             cost = skew;
@@ -911,6 +930,7 @@ static hipError_t queue_blocks(ranc_net *net, const uint32_t *base, int num_tick
     a.block = bp.block;
     a.k0 = k0;
     a.ticks = T;
+    a.multi = p.multi_source ? 1 : 0;
     a.ext_base = base;
     a.tick_words = (long long)p.Cin * p.W;
     a.ext_sstride = (long long)num_ticks * a.tick_words;
