@@ -32,6 +32,19 @@ template <int K> __device__ inline uint32_t lane_xor(uint32_t x)
     }
 }
 
+// Sum of a 32-bit value over the 64 lanes of a wavefront (every lane gets it).
+__device__ inline uint32_t wave_sum_dpp(uint32_t v)
+{
+    v += lane_xor<1>(v);
+    v += lane_xor<2>(v);
+    v += lane_xor<4>(v);
+    v += lane_xor<8>(v);
+    const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = (uint32_t)a[0] + (uint32_t)a[1];
+    const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return (uint32_t)b[0] + (uint32_t)b[1];
+}
+
 // One stage of a recursive bit-matrix transpose: lanes whose index has bit K
 // clear exchange the bits with index bit K set for their partner's (lane ^ K)
 // bits with index bit K clear.

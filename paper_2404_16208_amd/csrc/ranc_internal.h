@@ -42,6 +42,8 @@
 //              sparse: [C][N][S64] (a neuron's samples contiguous)
 //   plain path:
 //   ring     u32 [Q][S][C][W]  scheduler: slot t%Q holds the axon spikes of tick t
+//   ring8    u8 [Q][S][C][A]   the scheduler with a byte per axon (small networks; Q = D + 2 or
+//                              more): between calls it holds the scheduled spikes and ring none
 //   spk      u32 [S][C][NW]    spikes of the current tick
 //   raster   u32 [RT][S][Wout] output-bus spikes of tick t in row t%RT
 //   sparse path:
@@ -136,21 +138,33 @@ struct ResidentArgs {
     int num_ticks;
 };
 
-// One launch of the multi-tick MFMA form of a feed-forward network
-// (kern_mfma_ticks.hip): cores order[first, first + count), a core of level l
-// running block step - l of the segment's ticks [k0, k0 + ticks) (positions in
-// the call), `block` ticks per block.
+// One launch of the multi-tick forms of a feed-forward network
+// (kern_mfma_ticks.hip, k_plain_ticks): cores order[first, first + count), a
+// core of level l running block step - l of the segment's ticks [k0, k0 +
+// ticks) (positions in the call), `block` ticks per block. k_plain_ticks also
+// runs any network, one tick per launch: no order, no levels.
 struct BlockArgs {
     const int32_t *order;       // cores by ascending level [C]
     const int32_t *level;       // level of each core [C]
     int first, count;
     int step, block, k0, ticks;
-    int multi;                  // some axon has several sources
+    int multi;                  // MFMA: some axon has several sources
+    // plain path only:
+    uint8_t *ring8;             // byte ring [Q][S][C][A]
+    const uint32_t *dst;        // destination of each neuron [C][N]: (core * A + axon) << 4 | delay, or PLAIN_NO_DEST
+    const uint32_t *cols;       // crossbar columns with the axons sorted by type [C][G * sorted_words][N] ...
+    const uint16_t *pos;        // ... and the axon of each position [C][32 * G * sorted_words, a multiple of 64]
+                                // (bit 15: padding; the rest a valid axon)
+    int sorted_words;           // words per type; 0: natural order
+    int spw;                    // samples per workgroup (one with several ticks per block)
+    int want_spk;               // write the tick's spike words (the link count reads them)
     const uint32_t *ext_base;   // external input as in ResidentArgs, or nullptr
     long long ext_sstride;
     long long tick_words;
 };
 constexpr int MFMA_BLOCK_TICKS_MAX = 32;
+constexpr int PLAIN_WHOLE_NEURONS = 4096;
+constexpr uint32_t PLAIN_NO_DEST = 0xFFFFFFFFu;
 
 // Grid synchronization words of the state-resident loop: arrival counter and
 // give-up flag (zeroed before each launch), and the longest wait, in ticks of
@@ -257,12 +271,20 @@ struct RouteCfg {
     int samples_per_block;  // 1, 2, 4 or 8 spike bitmaps per block
     int blocks_per_group;   // blocks sharing one group of samples (split of the destination words)
     int stage;              // stage the bitmaps in LDS
-    int lanes;              // lanes per destination word: 1 (k_route, the fields above apply) or
-                            // route_split_lanes() (k_route_split: one sample per block row)
+    int lanes;              // 1 (k_route, the fields above apply) or route_fused_lanes()
+                            // (k_plain_ticks delivers the spikes itself)
 };
 
 // Launchers (return the first HIP error, hipSuccess otherwise).
 hipError_t launch_integrate_plain(const DevNet &n, const TickArgs &a, hipStream_t st);
+// integration and delivery of one tick, or of a block of a feed-forward network
+hipError_t launch_plain_ticks(const DevNet &n, const BlockArgs &a, hipStream_t st);
+int plain_sorted_words(int G, int longest);   // `longest`: axons of one type in a core, at most
+// all ticks of a call for a network that fits one CU (a.ticks from a.k0)
+hipError_t launch_plain_whole(const DevNet &n, const BlockArgs &a, hipStream_t st);
+bool plain_whole_supported(int C, int A, int N, int G, int D, int Cin, int sorted_words);
+// scheduled deliveries from the bit ring to the byte ring, or back
+hipError_t launch_move_ring(const DevNet &n, uint8_t *ring8, int to_bytes, hipStream_t st);
 hipError_t launch_integrate_sparse(const DevNet &n, const TickArgs &a, int samples_per_wg, hipStream_t st);
 bool sparse_shape_supported(int A, int N, int G);
 int sparse_max_samples_per_wg();
@@ -284,7 +306,7 @@ hipError_t launch_mfma_resident(const DevNet &n, const ResidentArgs &ra, const R
 int resident_blocks_per_cu(int A, int two_planes, int ext);   // 0: the shape is not built
 int resident_max_cores_per_wg();
 hipError_t launch_route(const DevNet &n, int k, const RouteCfg &cfg, hipStream_t st);
-hipError_t launch_reset_state(const DevNet &n, const LinkArgs &l, hipStream_t st);
+hipError_t launch_reset_state(const DevNet &n, const LinkArgs &l, uint8_t *ring8, hipStream_t st);   // ring8 or nullptr
 hipError_t launch_advance_tick(const DevNet &n, int num_ticks, hipStream_t st);
 hipError_t launch_fold_counts(const DevNet &n, int num_ticks, hipStream_t st);
 hipError_t launch_link_counts(const DevNet &n, const LinkArgs &l, int k, hipStream_t st);
@@ -319,9 +341,9 @@ hipError_t launch_integrate_mfma_cb(const DevNet &n, const TickArgs &a, int two_
 hipError_t launch_integrate_mfma_group_cb(const MfmaGroupArgs &g, int total, int k, int code, int ext,
                                           hipStream_t st);
 RouteCfg route_default_cfg(const DevNet &n);
-int route_split_lanes();
-// Lanes per word chosen for a configuration: the lane-split router when the
-// one-lane launch would have fewer blocks than the GPU has compute units.
+int route_fused_lanes();
+// The form chosen for a configuration: without a router when the one-lane
+// launch would have fewer blocks than the GPU has compute units.
 int route_auto_lanes(const DevNet &n, const RouteCfg &cfg);
 int route_dmax(int max_delay);
 int mfma_max_samples_per_wg();

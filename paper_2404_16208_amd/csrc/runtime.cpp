@@ -45,16 +45,18 @@ ranc_status hip_fail(hipError_t e, const char *what)
 enum Region {
     R_COLBITS, R_TYPEMASK, R_WTS, R_LEAK, R_THR, R_RST, R_VINIT, R_COREMASK, R_OUTMASK, R_OUTWORD,
     R_ININDEX, R_RTDCNT, R_RTGOFF, R_RTENT, R_DEGB, R_OUTIDX, R_PLANES, R_RTXPTR, R_RTXENT, R_HZERO,
-    R_FLOOR, R_LINMASK, R_ECSRPTR, R_ECSRENT, R_LINKREC, R_OUTCOL, R_OUTPOS, R_LINKPTR, R_LINKENT,
+    R_FLOOR, R_LINMASK, R_ECSRPTR, R_ECSRENT, R_LINKREC, R_OUTCOL, R_OUTPOS, R_LINKPTR, R_LINKENT, R_PLAINDST, R_SCOLS, R_SPOS,
     R_PARAMS_END,  // everything before this is uploaded once at load
     R_V = R_PARAMS_END, R_RING, R_SPK, R_HIST, R_RASTER, R_CNT, R_CRING, R_TICK, R_BATCH, R_EXT, R_LINKD,
     R_RSYNC,
     // MFMA path: the compact B source, uploaded at load as well; kept past
     // the state regions so that their placement does not depend on it
     R_BSRC,
-    // MFMA path, feed-forward networks: cores by level, then each core's
-    // level; uploaded at load
-    R_ORDER, R_NREG
+    // feed-forward networks (MFMA and plain paths): cores by level, then each
+    // core's level; uploaded at load
+    R_ORDER,
+    // plain path, small networks: the byte ring
+    R_RING8, R_NREG
 };
 
 struct Plan {
@@ -73,6 +75,7 @@ struct Plan {
     // at most (the history ring holds D more). No levels: tick by tick.
     int levels = 0, seg_ticks = 1;
     bool multi_source = false;   // some axon has several sources
+    int sorted_words = 0;        // plain path: words per axon type of the sorted columns, 0: none
     std::vector<int32_t> order, level, level_first;
 };
 
@@ -203,6 +206,19 @@ bool neuron_model_ext(const ranc_net_desc *d)
 // (directly or through others): a core's level is the longest path to it from
 // a core without sources. More than MAX_LEVELS levels, or a cycle: none.
 constexpr int MAX_LEVELS = 64;
+constexpr long long PLAIN_FUSED_MAX_NEURONS = 1 << 22;   // neurons times samples
+constexpr long long PLAIN_RING8_MAX_BYTES = 512 << 20;
+// The whole-network form (kern_plain_whole.hip) loads and stores everything
+// once per call: 18 us and 1.9 us per tick for 12 cores of 256 x 256, against
+// 5 us and 3.4 us per tick.
+constexpr int PLAIN_WHOLE_MIN_TICKS = 12;
+// Sorted columns (12 words instead of 8 for four types) are kept while they
+// stay in cache from tick to tick, and used by a one-tick launch that does
+// enough work to be bound by it (128 cores x 23 samples 10.3 us against 10.7)
+// rather than by the loads it waits for (45 cores of 512 axons, one sample 4.4
+// us against 3.9).
+constexpr long long PLAIN_SORTED_MAX_NEURONS = 1 << 18;
+constexpr long long PLAIN_SORTED_MIN_WORK = 1 << 18;     // neurons times samples
 bool feed_forward_levels(const ranc_net_desc *d, Plan &p)
 {
     const int C = p.C, N = p.N;
@@ -296,6 +312,30 @@ ranc_status make_plan(const ranc_net_desc *d, int32_t S, int32_t RT, int32_t pat
             p.seg_ticks = (int)seg;
             p.Q = p.D + p.seg_ticks;
         }
+    }
+    // plain path with few (core, sample) pairs: the byte ring, longer for a
+    // feed-forward network, at most 512 MB
+    const long long slot8 = (long long)p.C * p.A * S;
+    const bool ring8 = blocks && path == RANC_PATH_PLAIN && (long long)p.C * p.N * S <= PLAIN_FUSED_MAX_NEURONS &&
+                       slot8 * (p.D + 2) <= PLAIN_RING8_MAX_BYTES;
+    if (ring8) {
+        p.Q = p.D + 2;
+        const int seg = std::min(RT, MFMA_BLOCK_TICKS_MAX);
+        if (seg > 1 && slot8 * (p.D + 1 + seg) <= PLAIN_RING8_MAX_BYTES && feed_forward_levels(d, p)) {
+            p.seg_ticks = seg;
+            p.Q = p.D + 1 + seg;
+        }
+        // columns sorted by axon type, unless so large that they come from
+        // memory every tick
+        int longest = 0;
+        for (int c = 0; c < p.C; ++c) {
+            int count[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+            for (int a = 0; a < p.A; ++a)
+                longest = std::max(longest, ++count[d->axon_type[(size_t)c * p.A + a]]);
+        }
+        const int pw = plain_sorted_words(p.G, longest);
+        if (p.G * pw <= 2 * p.W && (long long)p.C * p.N <= PLAIN_SORTED_MAX_NEURONS)
+            p.sorted_words = pw;
     }
     p.slices = path == RANC_PATH_MFMA ? mfma_slices(p.A, p.N, p.two)
              : path == RANC_PATH_SPARSE ? p.N / sparse_slice_width(p.N) : 1;
@@ -419,6 +459,10 @@ ranc_status make_plan(const ranc_net_desc *d, int32_t S, int32_t RT, int32_t pat
     p.size[R_LINKENT] = tiled ? std::max<size_t>((size_t)4 * E, 1) * 4 : 0;
     p.size[R_OUTCOL] = tiled ? 0 : std::max<size_t>((size_t)p.Wout, 1) * 8;
     p.size[R_OUTPOS] = tiled ? 0 : std::max<size_t>((size_t)p.Nout, 1) * 4;
+    p.size[R_PLAINDST] = ring8 ? C * N * 4 : 0;
+    p.size[R_SCOLS] = C * G * p.sorted_words * N * 4;
+    p.size[R_SPOS] = C * ((G * p.sorted_words + 1) / 2 * 64) * 2;
+    p.size[R_RING8] = ring8 ? (size_t)p.Q * S * C * A : 0;
     p.size[R_LINKD] = (size_t)4 * C * p.S64 * 8;
     p.size[R_RSYNC] = mf ? 8 : 0;   // state-resident loop: arrival counter, give-up flag
     p.size[R_ORDER] = p.levels ? 2 * C * 4 : 0;
@@ -433,20 +477,44 @@ ranc_status make_plan(const ranc_net_desc *d, int32_t S, int32_t RT, int32_t pat
     return RANC_OK;
 }
 
-// Crossbar columns [C][A/32][N] (bit a % 32 of word a / 32 of neuron j: axon
-// a connects to j), into zeroed words, visiting the set crossbar bits only.
+// 32 x 32 bit transpose: bit i of word j becomes bit j of word i.
+static void transpose_bits(uint32_t (&a)[32])
+{
+    uint32_t m = 0x0000FFFFu;
+    for (int j = 16; j; j >>= 1, m ^= m << j)
+        for (int k = 0; k < 32; k = (k + j + 1) & ~j) {
+            const uint32_t t = ((a[k] >> j) ^ a[k + j]) & m;
+            a[k + j] ^= t;
+            a[k] ^= t << j;
+        }
+}
+
+// Crossbar columns of core c, words [positions/32][N]: bit p % 32 of word p / 32
+// of neuron j = the axon at position p connects to j. axon(p) < 0: none.
+template <typename Axon> static void pack_columns(const ranc_net_desc *d, const Plan &p, int c, int positions, uint32_t *col, Axon &&axon)
+{
+    const int N = p.N, NW = p.NW;
+    for (int p0 = 0; p0 < positions; p0 += 32) {
+        const uint32_t *row[32];
+        for (int i = 0; i < 32; ++i) {
+            const int a = axon(p0 + i);
+            row[i] = a < 0 ? nullptr : d->crossbar + ((size_t)c * p.A + a) * NW;
+        }
+        for (int w = 0; w < NW; ++w) {
+            uint32_t b[32];
+            for (int i = 0; i < 32; ++i)
+                b[i] = row[i] ? row[i][w] : 0u;
+            transpose_bits(b);
+            memcpy(col + (size_t)(p0 / 32) * N + 32 * w, b, sizeof b);
+        }
+    }
+}
+
+// Crossbar columns [C][A/32][N] with the axons in natural order.
 static void pack_columns(const ranc_net_desc *d, const Plan &p, uint32_t *col)
 {
-    const int C = p.C, A = p.A, N = p.N, W = p.W, NW = p.NW;
-    for (int c = 0; c < C; ++c)
-        for (int a = 0; a < A; ++a) {
-            const uint32_t *row = d->crossbar + ((size_t)c * A + a) * NW;
-            uint32_t *cw = col + ((size_t)c * W + a / 32) * N;
-            const uint32_t bit = 1u << (a % 32);
-            for (int w = 0; w < NW; ++w)
-                for (uint32_t b = row[w]; b; b &= b - 1u)
-                    cw[32 * w + __builtin_ctz(b)] |= bit;
-        }
+    for (int c = 0; c < p.C; ++c)
+        pack_columns(d, p, c, p.A, col + (size_t)c * p.W * p.N, [](int a) { return a; });
 }
 
 // Host-side packing of the MFMA path's compact B source (R_BSRC): column
@@ -649,6 +717,35 @@ void pack_params(const ranc_net_desc *d, const Plan &p, std::vector<uint8_t> &bu
                     db[(r * 2 + 1) * A + a] = (uint8_t)(k >> 8);
                 }
     }
+    if (p.size[R_PLAINDST]) {
+        // plain path: each neuron's scheduler byte and delay (C * A <= 2^26)
+        uint32_t *dst = (uint32_t *)at(R_PLAINDST);
+        for (size_t i = 0; i < (size_t)C * N; ++i) {
+            const int c = (int)(i / N);
+            const int dc = (c % d->grid_w + d->dest_dx[i]) + (c / d->grid_w + d->dest_dy[i]) * d->grid_w;
+            dst[i] = d->dest_kind[i] == RANC_DEST_CORE
+                         ? ((uint32_t)dc * A + d->dest_axon[i]) << 4 | (uint32_t)d->dest_delay[i]
+                         : PLAIN_NO_DEST;
+        }
+    }
+    if (p.size[R_SCOLS]) {
+        // axons sorted by type, sorted_words words per type
+        const int PW = p.sorted_words, SW = G * PW, P = (SW + 1) / 2 * 64;
+        uint32_t *sc = (uint32_t *)at(R_SCOLS);
+        uint16_t *sp = (uint16_t *)at(R_SPOS);
+        std::fill(sp, sp + (size_t)C * P, (uint16_t)0x8000);
+        for (int c = 0; c < C; ++c) {
+            int fill[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+            for (int a = 0; a < A; ++a) {
+                const int g = d->axon_type[(size_t)c * A + a];
+                sp[(size_t)c * P + 32 * PW * g + fill[g]++] = (uint16_t)a;
+            }
+            pack_columns(d, p, c, 32 * SW, sc + (size_t)c * SW * N, [&](int pos) {
+                const int a = sp[(size_t)c * P + pos];
+                return a < 0x8000 ? a : -1;
+            });
+        }
+    }
     {
         // mesh path ends of each neuron's packets (x first, then y; see
         // kern_links.hip): no hop is -1, else 2 * end core + (negative step)
@@ -828,6 +925,19 @@ static int mfma_compact(const ranc_net *net)
     return p.bsrc >= 0 ? p.bsrc : mfma_compact_b(net->dn, p.two, p.spw) ? 1 : 0;
 }
 
+// Plain path: the form without a router wherever the network has it (up to 2^22
+// neurons times samples, where it takes a third to two thirds of the time).
+static int auto_lanes(const ranc_net *net, const RouteCfg &rc)
+{
+    return net->p.size[R_RING8] ? route_fused_lanes() : route_auto_lanes(net->dn, rc);
+}
+
+// Every instance to its initial state.
+static hipError_t reset_state(ranc_net *net, hipStream_t s)
+{
+    return launch_reset_state(net->dn, net->lk, net->p.size[R_RING8] ? net->ws + net->p.off[R_RING8] : nullptr, s);
+}
+
 static hipError_t prof_begin(ranc_net *net, int kind, hipStream_t s, int *slot)
 {
     *slot = -1;
@@ -881,21 +991,11 @@ struct BlockPlan {
     bool skewed = false;
 };
 
-// The cheapest form by the time of its launches, in microseconds. Measured on
-// 256 x 256 cores with 9-bit weights: a launch of the multi-tick kernel takes
-// about 8 us to set up and, per tick, 2.2 us while its workgroups (core,
-// slice, 32 samples) have a CU each and 3.5 us per further two per CU; a
-// tick-by-tick launch 4 us and 7 us per (core, slice, 64 samples) and CU.
-static BlockPlan choose_blocks(const Plan &p, int T)
+// The cheapest form by the time of its launches, launch(cores, ticks)
+// microseconds each, against `cost` tick by tick.
+template <typename Launch> static BlockPlan cheapest_blocks(const Plan &p, int T, double cost, Launch &&launch)
 {
     BlockPlan best;
-    if (!p.levels || T < 2)
-        return best;
-    auto launch = [&](long long cores, int ticks) {
-        const long long units = cores * p.slices * ((p.S + 31) / 32);
-        return units <= 256 ? 8.0 + 2.2 * ticks : 8.0 + (3.5 * ticks + 4.0) * ((units + 511) / 512);
-    };
-    double cost = T * (4.0 + 7.0 * std::max(1.0, (double)p.C * p.slices * (p.S64 / 64) / 256.0));
     double seq = 0;
     for (int l = 0; l < p.levels; ++l)
         seq += launch(p.level_first[l + 1] - p.level_first[l], T);
@@ -919,7 +1019,49 @@ static BlockPlan choose_blocks(const Plan &p, int T)
     return best;
 }
 
+// Plain path (k_plain_ticks), measured on 256 x 256 cores: a launch takes about
+// 4 us and 1 us per tick of a block while its workgroups fit the GPU.
+static BlockPlan choose_plain_blocks(const Plan &p, int T)
+{
+    auto launch = [&](long long cores, int ticks) {
+        const double rounds = std::max(1.0, (double)cores * p.S * p.N / (256.0 * 1024));
+        return 4.0 + rounds * (1.0 * ticks + 1.0);
+    };
+    return cheapest_blocks(p, T, T * launch(p.C, 1), launch);
+}
+
+// MFMA path. Measured on
+// 256 x 256 cores with 9-bit weights: a launch of the multi-tick kernel takes
+// about 8 us to set up and, per tick, 2.2 us while its workgroups (core,
+// slice, 32 samples) have a CU each and 3.5 us per further two per CU; a
+// tick-by-tick launch 4 us and 7 us per (core, slice, 64 samples) and CU.
+static BlockPlan choose_blocks(const Plan &p, int T)
+{
+    if (!p.levels || T < 2)
+        return BlockPlan();
+    auto launch = [&](long long cores, int ticks) {
+        const long long units = cores * p.slices * ((p.S + 31) / 32);
+        return units <= 256 ? 8.0 + 2.2 * ticks : 8.0 + (3.5 * ticks + 4.0) * ((units + 511) / 512);
+    };
+    if (p.path == RANC_PATH_PLAIN)
+        return choose_plain_blocks(p, T);
+    double cost = T * (4.0 + 7.0 * std::max(1.0, (double)p.C * p.slices * (p.S64 / 64) / 256.0));
+    return cheapest_blocks(p, T, cost, launch);
+}
+
 // Queue ticks [k0, k0 + T) of the call (T <= seg_ticks) in blocks.
+static void set_plain_args(const ranc_net *net, BlockArgs &a)
+{
+    const Plan &p = net->p;
+    a.ring8 = net->ws + p.off[R_RING8];
+    a.dst = (const uint32_t *)(net->ws + p.off[R_PLAINDST]);
+    a.cols = (const uint32_t *)(net->ws + p.off[R_SCOLS]);
+    a.pos = (const uint16_t *)(net->ws + p.off[R_SPOS]);
+    a.sorted_words = p.sorted_words;
+    a.spw = 1;
+    a.want_spk = net->links_on ? 1 : 0;
+}
+
 static hipError_t queue_blocks(ranc_net *net, const uint32_t *base, int num_ticks, int k0, int T, const BlockPlan &bp,
                                hipStream_t s, bool timed)
 {
@@ -931,6 +1073,8 @@ static hipError_t queue_blocks(ranc_net *net, const uint32_t *base, int num_tick
     a.k0 = k0;
     a.ticks = T;
     a.multi = p.multi_source ? 1 : 0;
+    if (p.path == RANC_PATH_PLAIN)
+        set_plain_args(net, a);
     a.ext_base = base;
     a.tick_words = (long long)p.Cin * p.W;
     a.ext_sstride = (long long)num_ticks * a.tick_words;
@@ -946,11 +1090,20 @@ static hipError_t queue_blocks(ranc_net *net, const uint32_t *base, int num_tick
         int slot = -1;
         e = timed ? prof_begin(net, 0, s, &slot) : hipSuccess;
         if (e == hipSuccess)
-            e = launch_integrate_mfma_ticks(net->dn, a, p.two, s);
+            e = p.path == RANC_PATH_MFMA ? launch_integrate_mfma_ticks(net->dn, a, p.two, s) : launch_plain_ticks(net->dn, a, s);
         if (e == hipSuccess && timed)
             e = prof_end(net, slot, s);
     }
     return e;
+}
+
+// Samples per workgroup of k_plain_ticks, one tick per launch: as many as keep
+// the launch within what the GPU holds at once (2048 threads on 256 CUs).
+static int plain_samples_per_wg(const Plan &p)
+{
+    const long long held = 256LL * 2048 / p.N / p.C;   // samples in one round of workgroups
+    const long long spw = held < 1 ? 1 : (p.S + held - 1) / held;
+    return (int)std::min<long long>(spw, 32);
 }
 
 // Queue num_ticks ticks on stream s: per tick the integration (and on the
@@ -961,10 +1114,23 @@ static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_tick
     const Plan &p = net->p;
     const size_t tick_words = (size_t)p.Cin * p.W;
     timed = timed && net->prof.on;
-    // Feed-forward networks on the MFMA path run in segments of several ticks
-    // per launch (counts go straight into the totals); counting packets per
-    // link reads every tick's spikes as they stand after that tick.
-    const BlockPlan bp = net->links_on ? BlockPlan() : choose_blocks(p, std::min(num_ticks, p.seg_ticks));
+    // Feed-forward networks run in segments of several ticks per launch;
+    // counting packets per link reads every tick's spikes as they stand after
+    // that tick. These forms and the plain path's without a router add their
+    // counts to the totals themselves.
+    const bool fused = p.size[R_RING8] && net->rcfg.lanes == route_fused_lanes();
+    const bool via_words = p.size[R_RING8] && !fused;   // the router works on the bit ring
+    RouteCfg rcfg = net->rcfg;
+    rcfg.lanes = 1;
+    const bool whole = fused && !net->links_on && num_ticks >= PLAIN_WHOLE_MIN_TICKS &&
+                       plain_whole_supported(p.C, p.A, p.N, p.G, p.D, p.Cin, p.sorted_words);
+    if (via_words) {
+        hipError_t e = launch_move_ring(net->dn, net->ws + p.off[R_RING8], 0, s);
+        if (e != hipSuccess)
+            return hip_fail(e, "moving the scheduled spikes");
+    }
+    const BlockPlan bp = whole || net->links_on || (p.path == RANC_PATH_PLAIN && !fused) ? BlockPlan()
+                                                                                : choose_blocks(p, std::min(num_ticks, p.seg_ticks));
     for (int k = 0; bp.block && k < num_ticks; k += p.seg_ticks) {
         const int T = std::min(p.seg_ticks, num_ticks - k);
         BlockPlan b = bp;
@@ -973,7 +1139,24 @@ static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_tick
         if (e != hipSuccess)
             return hip_fail(e, "launching integration (several ticks)");
     }
-    for (int k = 0; !bp.block && k < num_ticks; ++k) {
+    if (whole) {
+        BlockArgs wa;
+        memset(&wa, 0, sizeof wa);
+        set_plain_args(net, wa);
+        wa.ticks = num_ticks;
+        wa.ext_base = base;
+        wa.tick_words = (long long)tick_words;
+        wa.ext_sstride = (long long)num_ticks * wa.tick_words;
+        int slot = -1;
+        hipError_t e = timed ? prof_begin(net, 0, s, &slot) : hipSuccess;
+        if (e == hipSuccess)
+            e = launch_plain_whole(net->dn, wa, s);
+        if (e == hipSuccess && timed)
+            e = prof_end(net, slot, s);
+        if (e != hipSuccess)
+            return hip_fail(e, "launching integration (whole network)");
+    }
+    for (int k = 0; !whole && !bp.block && k < num_ticks; ++k) {
         TickArgs ta;
         ta.k = k;
         ta.ext_t = base ? base + (size_t)k * tick_words : nullptr;
@@ -986,10 +1169,25 @@ static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_tick
             if (e != hipSuccess)
                 return hip_fail(e, "collecting kernel timings");
         }
+        BlockArgs pa;
+        if (fused) {
+            memset(&pa, 0, sizeof pa);
+            pa.count = p.C;
+            pa.block = pa.ticks = 1;
+            pa.k0 = k;
+            set_plain_args(net, pa);
+            pa.ext_base = base;
+            pa.tick_words = (long long)tick_words;
+            pa.ext_sstride = ta.ext_sstride;
+            pa.spw = plain_samples_per_wg(p);
+            if ((long long)p.C * p.N * p.S < PLAIN_SORTED_MIN_WORK)
+                pa.sorted_words = 0;
+        }
         int slot = -1;
         hipError_t e = timed ? prof_begin(net, 0, s, &slot) : hipSuccess;
         if (e == hipSuccess)
-            e = p.path == RANC_PATH_MFMA     ? launch_integrate_mfma(net->dn, ta, p.two, p.spw, mfma_compact(net), s)
+            e = fused                        ? launch_plain_ticks(net->dn, pa, s)
+                : p.path == RANC_PATH_MFMA   ? launch_integrate_mfma(net->dn, ta, p.two, p.spw, mfma_compact(net), s)
                 : p.path == RANC_PATH_SPARSE ? launch_integrate_sparse(net->dn, ta, p.spw, s)
                                              : launch_integrate_plain(net->dn, ta, s);
         if (e == hipSuccess && timed)
@@ -998,11 +1196,11 @@ static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_tick
             return hip_fail(e, "launching integration");
         // The MFMA path delivers spikes inside the next tick's integration
         // (spike history gathered by destination); the plain path routes
-        // into the scheduler ring here.
-        if (p.path == RANC_PATH_PLAIN) {
+        // into the scheduler ring here, unless integration did.
+        if (p.path == RANC_PATH_PLAIN && !fused) {
             e = timed ? prof_begin(net, 1, s, &slot) : hipSuccess;
             if (e == hipSuccess)
-                e = launch_route(net->dn, k, net->rcfg, s);
+                e = launch_route(net->dn, k, rcfg, s);
             if (e == hipSuccess && timed)
                 e = prof_end(net, slot, s);
             if (e != hipSuccess)
@@ -1014,9 +1212,11 @@ static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_tick
                 return hip_fail(e, "launching the mesh link count");
         }
     }
-    hipError_t e = bp.block ? hipSuccess : launch_fold_counts(net->dn, num_ticks, s);
+    hipError_t e = fused || bp.block ? hipSuccess : launch_fold_counts(net->dn, num_ticks, s);
     if (e == hipSuccess)
         e = launch_advance_tick(net->dn, num_ticks, s);
+    if (e == hipSuccess && via_words)
+        e = launch_move_ring(net->dn, net->ws + p.off[R_RING8], 1, s);
     if (e != hipSuccess)
         return hip_fail(e, "advancing the tick");
     return RANC_OK;
@@ -1461,6 +1661,16 @@ static ranc_status queue_batch_ticks(ranc_net *lead, const Batch &b, hipStream_t
         any_links = any_links || !pl.empty();
     const bool branches = !b.persistent && b.phases.size() == 1 && !any_links && !timed &&
                           b.phases[0].g_num + (b.phases[0].pl_num > 0 ? 1 : 0) > 1;
+    // the batched plain kernels work on the bit ring
+    auto move_rings = [&](int to_bytes) -> hipError_t {
+        hipError_t e = hipSuccess;
+        for (size_t i = 0; e == hipSuccess && i < b.nets.size(); ++i)
+            if (b.nets[i]->p.size[R_RING8])
+                e = launch_move_ring(b.nets[i]->dn, b.nets[i]->ws + b.nets[i]->p.off[R_RING8], to_bytes, s);
+        return e;
+    };
+    if (hipError_t e = move_rings(0); e != hipSuccess)
+        return hip_fail(e, "moving the scheduled spikes");
     if (branches) {
         hipError_t e = queue_batch_branches(lead, b, s);
         if (e != hipSuccess)
@@ -1512,6 +1722,8 @@ static ranc_status queue_batch_ticks(ranc_net *lead, const Batch &b, hipStream_t
         e = launch_advance_batch(tmf, (int)b.mf.size(), b.num_ticks, queue, s);
     if (e == hipSuccess && !b.pl.empty())
         e = launch_advance_batch(tpl, (int)b.pl.size(), b.num_ticks, queue, s);
+    if (e == hipSuccess)
+        e = move_rings(1);
     if (e != hipSuccess)
         return hip_fail(e, "advancing batch ticks");
     return RANC_OK;
@@ -1642,8 +1854,8 @@ ranc_status ranc_load_network(const ranc_net_desc *desc, int32_t num_samples, in
         return fail(RANC_EINVAL, "workspace is NULL");
     if ((uintptr_t)workspace % 256)
         return fail(RANC_EINVAL, "workspace must be 256-byte aligned");
-    if (workspace_bytes < p.total && p.levels) {
-        // a workspace sized for the tick-by-tick layout
+    if (workspace_bytes < p.total && (p.levels || p.size[R_RING8])) {
+        // a workspace sized for the layout without these
         Plan q;
         st = make_plan(desc, num_samples, max_ticks_per_call, path, q, false);
         if (st != RANC_OK)
@@ -1730,7 +1942,7 @@ ranc_status ranc_load_network(const ranc_net_desc *desc, int32_t num_samples, in
             e = hipMemcpyAsync(reg(R_ORDER) + (size_t)p.C * 4, p.level.data(), (size_t)p.C * 4, hipMemcpyHostToDevice, s);
     }
     if (e == hipSuccess)
-        e = launch_reset_state(n, net->lk, s);
+        e = reset_state(net, s);
     if (e == hipSuccess)
         e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
@@ -1752,7 +1964,7 @@ ranc_status ranc_load_network(const ranc_net_desc *desc, int32_t num_samples, in
         net->rcfg.stage = atoi(e) != 0;
     if ((size_t)n.C * n.NW * 4 * net->rcfg.samples_per_block > 128 * 1024)
         net->rcfg.stage = 0;
-    net->rcfg.lanes = route_auto_lanes(n, net->rcfg);
+    net->rcfg.lanes = auto_lanes(net, net->rcfg);
     net->last_stream = s;
     net->tick = 0;
     net->version = 1;
@@ -2193,7 +2405,7 @@ ranc_status ranc_reset_state(ranc_net *net, void *stream)
     if (!net)
         return fail(RANC_EINVAL, "net is NULL");
     hipStream_t s = (hipStream_t)stream;
-    hipError_t e = launch_reset_state(net->dn, net->lk, s);
+    hipError_t e = reset_state(net, s);
     if (e != hipSuccess)
         return hip_fail(e, "resetting state");
     net->tick = 0;
@@ -2275,10 +2487,10 @@ ranc_status ranc_autotune(ranc_net *net, const uint32_t *inputs, uint32_t flags,
             }
         }
         if (p.S <= 65535) {
-            // the lane-split router (one sample per block row; the fields
-            // above do not apply to it), once
+            // the form without a router (the fields above do not apply to
+            // it), once
             RouteCfg rc = def;
-            rc.lanes = route_split_lanes();
+            rc.lanes = route_fused_lanes();
             cands.push_back({p.spw, rc});
         }
         if (cands.empty())
@@ -2311,9 +2523,9 @@ ranc_status ranc_autotune(ranc_net *net, const uint32_t *inputs, uint32_t flags,
         p.spw = c.spw;
         net->rcfg = c.rc;
         // one untimed pass, then a timed pass, each from the initial state
-        e = launch_reset_state(net->dn, net->lk, s);
+        e = reset_state(net, s);
         if (e == hipSuccess && (st = queue_ticks(net, base, num_ticks, s, false)) == RANC_OK)
-            e = launch_reset_state(net->dn, net->lk, s);
+            e = reset_state(net, s);
         if (e == hipSuccess && st == RANC_OK)
             e = hipEventRecord(e0, s);
         if (e == hipSuccess && st == RANC_OK && (st = queue_ticks(net, base, num_ticks, s, false)) == RANC_OK)
@@ -2338,7 +2550,7 @@ ranc_status ranc_autotune(ranc_net *net, const uint32_t *inputs, uint32_t flags,
     if (st != RANC_OK)
         return st;
     if (e == hipSuccess)
-        e = launch_reset_state(net->dn, net->lk, s);
+        e = reset_state(net, s);
     if (e == hipSuccess)
         e = hipStreamSynchronize(s);
     if (e != hipSuccess)
@@ -2385,12 +2597,12 @@ ranc_status ranc_set_launch_shape(ranc_net *net, const ranc_tune *shape)
     if ((p.S + sb - 1) / sb > 65535)
         return fail(RANC_EINVAL, "too many sample groups for the router grid");
     const int lanes = shape->route_lanes_per_word;
-    if (lanes != 0 && lanes != 1 && lanes != route_split_lanes())
+    if (lanes != 0 && lanes != 1 && lanes != route_fused_lanes())
         return fail(RANC_EINVAL, "route_lanes_per_word %d must be 0 (automatic), 1 or %d", lanes,
-                    route_split_lanes());
-    rc.lanes = lanes ? lanes : route_auto_lanes(net->dn, rc);
+                    route_fused_lanes());
+    rc.lanes = lanes ? lanes : auto_lanes(net, rc);
     if (rc.lanes != 1 && p.S > 65535)
-        return fail(RANC_EINVAL, "the lane-split router takes at most 65535 samples");
+        return fail(RANC_EINVAL, "route_lanes_per_word 8 takes at most 65535 samples");
     drop_graphs(net);
     net->rcfg = rc;
     return RANC_OK;
