@@ -525,6 +525,107 @@ __device__ __forceinline__ void integrate_plain_wave(const DevNet &n, const Tick
     }
 }
 
+// One tick of one 64-neuron block of one (core, sample) on a single wavefront,
+// delivery included (the batched form of k_plain_ticks, natural order): words
+// and type masks are wave-uniform, the columns are read as they are used.
+template <int W_, int G_>
+__device__ __forceinline__ void plain_tick_wave(const BatchEntry &e, int k, int c, int s, int nb)
+{
+    constexpr int NB = W_ / 2;
+    const DevNet &n = e.n;
+    const int N = n.N;
+    const int lane = threadIdx.x & 63;
+    const int q = tick_slot(n, k);
+    const size_t CA = (size_t)n.C * n.A;
+    auto slot_of = [&](int q) -> uint8_t * { return e.ring8 + ((size_t)q * n.S + s) * CA; };
+    const uint8_t *rp = slot_of(q) + (size_t)c * n.A + lane;
+    const int ci = n.in_index[c];
+    const bool has_ext = e.ext_base != nullptr && ci >= 0;   // uniform
+    const uint32_t *ep = has_ext ? e.ext_base + (size_t)s * e.ext_sstride + (size_t)k * e.tick_words + (size_t)ci * W_ : nullptr;
+    uint32_t rb[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+        rb[b] = rp[64 * b];
+    const int j = nb * 64 + lane;
+    const size_t cj = (size_t)c * N + j;
+    const size_t vi = ((size_t)c * n.S + s) * N + j;
+    const int32_t v = n.V[vi], leak = n.leak[cj], thr = n.thr[cj], rst = n.rst[cj];
+    const uint32_t dst = e.dst[cj];
+    const size_t row = (size_t)c * (N >> 6) + nb;
+    unsigned long long *cp = n.cnt + (row * n.S + s) * CNT_N + (lane < CNT_N ? lane : 0);
+    const unsigned long long c_old = *cp;
+    uint32_t xw[W_];
+    unsigned de = 0;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const uint64_t r = __ballot(rb[b] != 0u);
+        de += (unsigned)__popcll(r);
+        xw[2 * b] = (uint32_t)r | (has_ext ? ep[2 * b] : 0u);
+        xw[2 * b + 1] = (uint32_t)(r >> 32) | (has_ext ? ep[2 * b + 1] : 0u);
+    }
+    const uint32_t *tmask = n.typemask + (size_t)c * G_ * W_;
+    const uint32_t *col = n.colbits + (size_t)c * W_ * N + j;
+    unsigned cnt[G_];
+#pragma unroll
+    for (int g = 0; g < G_; ++g)
+        cnt[g] = 0;
+#pragma unroll
+    for (int w = 0; w < W_; ++w) {
+        const uint32_t cw = col[(size_t)w * N] & xw[w];
+#pragma unroll
+        for (int g = 0; g < G_; ++g)
+            cnt[g] += __popc(cw & tmask[g * W_ + w]);
+    }
+    const int32_t *wt = n.wts + (size_t)c * G_ * N + j;
+    int in = 0;
+    unsigned ev = 0;
+#pragma unroll
+    for (int g = 0; g < G_; ++g) {
+        in += __mul24((int)cnt[g], wt[(size_t)g * N]);
+        ev += cnt[g];
+    }
+    int32_t vnew;
+    int32_t fl = n.vmin;
+    bool lin = false;
+    if (n.model_ext) {   // uniform
+        fl = n.floor[cj];
+        lin = (n.linmask[cj >> 5] >> (j & 31)) & 1u;
+    }
+    const bool fire = lif_update(v, in, leak, thr, rst, n.vmin, n.vmax, fl, lin, vnew);
+    n.V[vi] = vnew;
+    if (fire && dst != PLAIN_NO_DEST) {
+        const int qd = q + (int)(dst & 15u);
+        slot_of(qd >= n.Q ? qd - n.Q : qd)[dst >> 4] = 1;
+    }
+    // this wavefront's share of the core's bytes of the slot before
+    {
+        const int share = n.A / (N >> 6);   // bytes, a multiple of 8
+        uint32_t *p = reinterpret_cast<uint32_t *>(slot_of(q ? q - 1 : n.Q - 1) + (size_t)c * n.A + nb * share);
+        if (lane < share / 4)
+            p[lane] = 0u;
+        if (share > 256 && lane < share / 4 - 64)   // (512 axons, 64 neurons)
+            p[64 + lane] = 0u;
+    }
+    const uint64_t b = __ballot(fire);
+    ev = wave_sum_dpp(ev);
+    const size_t m0 = (size_t)c * n.NW + 2 * nb;
+    const unsigned em = (unsigned)__popcll(b);
+    const unsigned ro = (unsigned)__popcll(b & (n.coremask[m0] | (uint64_t)n.coremask[m0 + 1] << 32));
+    const unsigned ou = (unsigned)__popcll(b & (n.outmask[m0] | (uint64_t)n.outmask[m0 + 1] << 32));
+    if (lane < 2) {
+        const uint32_t word = (uint32_t)(b >> (32 * lane));
+        if (e.want_spk)
+            n.spk[((size_t)s * n.C + c) * n.NW + 2 * nb + lane] = word;
+        const int ow = n.outword[m0 + lane];
+        if (ow >= 0)
+            n.raster[((size_t)tick_row(n, k) * n.S + s) * n.Wout + ow] = word & n.outmask[m0 + lane];
+    }
+    const unsigned add = lane == CNT_EMITTED ? em : lane == CNT_ROUTED ? ro : lane == CNT_DELIVERED ? (nb == 0 ? de : 0u)
+                         : lane == CNT_OUT ? ou : ev;
+    if (lane < CNT_N)
+        *cp = c_old + add;
+}
+
 int plain_shape_code(int W, int G)
 {
     const int wi = W == 2 ? 0 : W == 4 ? 1 : W == 8 ? 2 : 3;
@@ -557,6 +658,37 @@ __global__ __launch_bounds__(64) void k_integrate_plain_batch(const BatchEntry *
 #undef RANC_PLAIN_CASE
     default: break;
     }
+}
+
+// The same units, one per wavefront, for networks with the byte ring.
+__global__ __launch_bounds__(256) void k_plain_ticks_batch(const BatchEntry *__restrict__ tab, int num, int total, int k)
+{
+    const int u = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    if (u >= total)
+        return;   // whole wavefronts
+    const BatchEntry &e = tab[batch_entry_of(tab, num, u, false)];
+    const int local = u - e.unit_begin;
+    const int nbs = e.n.N >> 6;
+    const int nb = local % nbs, c = (local / nbs) % e.n.C, s = local / nbs / e.n.C;
+    switch (e.code) {
+#define RANC_PLAIN_CASE(WI, W, GI, G) \
+    case WI * 4 + GI: plain_tick_wave<W, G>(e, k, c, s, nb); break;
+        RANC_PLAIN_CASE(0, 2, 0, 1) RANC_PLAIN_CASE(0, 2, 1, 2) RANC_PLAIN_CASE(0, 2, 2, 4) RANC_PLAIN_CASE(0, 2, 3, 8)
+        RANC_PLAIN_CASE(1, 4, 0, 1) RANC_PLAIN_CASE(1, 4, 1, 2) RANC_PLAIN_CASE(1, 4, 2, 4) RANC_PLAIN_CASE(1, 4, 3, 8)
+        RANC_PLAIN_CASE(2, 8, 0, 1) RANC_PLAIN_CASE(2, 8, 1, 2) RANC_PLAIN_CASE(2, 8, 2, 4) RANC_PLAIN_CASE(2, 8, 3, 8)
+        RANC_PLAIN_CASE(3, 16, 0, 1) RANC_PLAIN_CASE(3, 16, 1, 2) RANC_PLAIN_CASE(3, 16, 2, 4)
+        RANC_PLAIN_CASE(3, 16, 3, 8)
+#undef RANC_PLAIN_CASE
+    default: break;
+    }
+}
+
+hipError_t launch_plain_ticks_batch(const BatchEntry *tab, int num, int total, int k, hipStream_t st)
+{
+    if (num < 1 || total < 1)
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_plain_ticks_batch, dim3((total + 3) / 4), dim3(256), 0, st, tab, num, total, k);
+    return hipGetLastError();
 }
 
 hipError_t launch_integrate_plain_batch(const BatchEntry *tab, int num, int total, int k, hipStream_t st)

@@ -229,6 +229,10 @@ struct BatchEntry {
     int route_begin, route_units, route_code, route_split;   // plain path: router units and shape
     int phase;                  // cache-sized phase of the batch (host bookkeeping)
     int compact;                // MFMA path: B tiles built from the compact crossbar (host bookkeeping)
+    // plain path, networks with the byte ring (see BlockArgs)
+    uint8_t *ring8;
+    const uint32_t *dst;
+    int want_spk;
 };
 
 // Networks of one MFMA shape class in one launch, passed by value as kernel
@@ -324,6 +328,7 @@ int mfma_shape_code(int A, int N, int two_planes);
 int plain_shape_code(int W, int G);
 int route_shape_code(const RouteCfg &cfg, int max_delay);
 hipError_t launch_integrate_plain_batch(const BatchEntry *tab, int num, int total, int k, hipStream_t st);
+hipError_t launch_plain_ticks_batch(const BatchEntry *tab, int num, int total, int k, hipStream_t st);
 hipError_t launch_route_batch(const BatchEntry *tab, int num, int total, int k, size_t lds_bytes, hipStream_t st);
 hipError_t launch_advance_batch(const BatchEntry *tab, int num, int num_ticks, unsigned *queue, hipStream_t st);
 hipError_t launch_integrate_mfma_batch(const BatchEntry *tab, int num, int total, int k, unsigned *queue,

@@ -866,9 +866,14 @@ struct Batch {
     std::vector<Group> groups;
     // Phases: networks whose combined per-tick state fits the GPU's last-level
     // cache; all ticks of a phase run before the next phase starts. Groups
-    // [g_first, g_first + g_num) and plain entries [pl_first, pl_first +
-    // pl_num), numbered from 0 within the phase. One phase when persistent.
-    struct Phase { int g_first, g_num, pl_first, pl_num, pl_units, rt_units; };
+    // [g_first, g_first + g_num), plain entries with the byte ring [pf_first,
+    // pf_first + pf_num) and without [pl_first, pl_first + pl_num), each
+    // numbered from 0 within the phase. One phase when persistent.
+    struct Phase { int g_first, g_num, pf_first, pf_num, pf_units, pl_first, pl_num, pl_units, rt_units; };
+    // networks (indexes in nets) that run the call's ticks in launches of
+    // their own, several ticks each; they are in no other list
+    std::vector<int> solo;
+    std::vector<char> is_solo;
     std::vector<Phase> phases;
     std::vector<std::vector<int>> phase_links;   // per phase: networks (index in nets) counting mesh links
     std::vector<char> links;                     // links_on of each network when the batch was set up
@@ -1097,8 +1102,67 @@ static hipError_t queue_blocks(ranc_net *net, const uint32_t *base, int num_tick
     return e;
 }
 
+// How a call of num_ticks ticks runs: tick by tick; a feed-forward network's
+// blocks of ticks; a small network's whole call in one launch. The last two add
+// their counts to the totals themselves. Counting packets per link reads every
+// tick's spikes as they stand after that tick. fused: the plain path's form
+// without a router is wanted.
+enum TickForm { FORM_TICKS, FORM_BLOCKS, FORM_WHOLE };
+static TickForm choose_form(const ranc_net *net, int num_ticks, bool fused, BlockPlan &bp)
+{
+    const Plan &p = net->p;
+    bp = BlockPlan();
+    if (net->links_on || (p.path == RANC_PATH_PLAIN && !(fused && p.size[R_RING8])))
+        return FORM_TICKS;
+    if (p.path == RANC_PATH_PLAIN && num_ticks >= PLAIN_WHOLE_MIN_TICKS &&
+        plain_whole_supported(p.C, p.A, p.N, p.G, p.D, p.Cin, p.sorted_words))
+        return FORM_WHOLE;
+    bp = choose_blocks(p, std::min(num_ticks, p.seg_ticks));
+    return bp.block ? FORM_BLOCKS : FORM_TICKS;
+}
+
+// Queue a call's ticks in the form chosen, if it is not tick by tick (without
+// the tick advance).
+static hipError_t queue_several(ranc_net *net, const uint32_t *base, int num_ticks, hipStream_t s, bool timed)
+{
+    const Plan &p = net->p;
+    BlockPlan bp;
+    hipError_t e = hipSuccess;
+    if (choose_form(net, num_ticks, true, bp) == FORM_WHOLE) {
+        BlockArgs a;
+        memset(&a, 0, sizeof a);
+        set_plain_args(net, a);
+        a.ticks = num_ticks;
+        a.ext_base = base;
+        a.tick_words = (long long)p.Cin * p.W;
+        a.ext_sstride = (long long)num_ticks * a.tick_words;
+        int slot = -1;
+        e = timed ? prof_begin(net, 0, s, &slot) : hipSuccess;
+        if (e == hipSuccess)
+            e = launch_plain_whole(net->dn, a, s);
+        if (e == hipSuccess && timed)
+            e = prof_end(net, slot, s);
+        return e;
+    }
+    for (int k = 0; e == hipSuccess && k < num_ticks; k += p.seg_ticks) {
+        const int T = std::min(p.seg_ticks, num_ticks - k);
+        BlockPlan b = bp;
+        b.block = std::min(b.block, T);
+        e = queue_blocks(net, base, num_ticks, k, T, b, s, timed);
+    }
+    return e;
+}
+
+// A batch's network that runs several ticks per launch, its tick advance included.
+static hipError_t queue_solo(ranc_net *net, const uint32_t *base, int num_ticks, hipStream_t s)
+{
+    hipError_t e = queue_several(net, base, num_ticks, s, false);
+    return e == hipSuccess ? launch_advance_tick(net->dn, num_ticks, s) : e;
+}
+
 // Samples per workgroup of k_plain_ticks, one tick per launch: as many as keep
-// the launch within what the GPU holds at once (2048 threads on 256 CUs).
+// the launch within what the GPU holds at once (2048 threads on 256 CUs). One
+// to three measured the same at 128 cores x 23 samples, six 17% slower.
 static int plain_samples_per_wg(const Plan &p)
 {
     const long long held = 256LL * 2048 / p.N / p.C;   // samples in one round of workgroups
@@ -1114,49 +1178,23 @@ static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_tick
     const Plan &p = net->p;
     const size_t tick_words = (size_t)p.Cin * p.W;
     timed = timed && net->prof.on;
-    // Feed-forward networks run in segments of several ticks per launch;
-    // counting packets per link reads every tick's spikes as they stand after
-    // that tick. These forms and the plain path's without a router add their
-    // counts to the totals themselves.
+    BlockPlan bp;
     const bool fused = p.size[R_RING8] && net->rcfg.lanes == route_fused_lanes();
+    if (choose_form(net, num_ticks, fused, bp) != FORM_TICKS) {
+        hipError_t e = queue_several(net, base, num_ticks, s, timed);
+        if (e == hipSuccess)
+            e = launch_advance_tick(net->dn, num_ticks, s);
+        return e == hipSuccess ? RANC_OK : hip_fail(e, "launching integration (several ticks)");
+    }
     const bool via_words = p.size[R_RING8] && !fused;   // the router works on the bit ring
     RouteCfg rcfg = net->rcfg;
     rcfg.lanes = 1;
-    const bool whole = fused && !net->links_on && num_ticks >= PLAIN_WHOLE_MIN_TICKS &&
-                       plain_whole_supported(p.C, p.A, p.N, p.G, p.D, p.Cin, p.sorted_words);
     if (via_words) {
         hipError_t e = launch_move_ring(net->dn, net->ws + p.off[R_RING8], 0, s);
         if (e != hipSuccess)
             return hip_fail(e, "moving the scheduled spikes");
     }
-    const BlockPlan bp = whole || net->links_on || (p.path == RANC_PATH_PLAIN && !fused) ? BlockPlan()
-                                                                                : choose_blocks(p, std::min(num_ticks, p.seg_ticks));
-    for (int k = 0; bp.block && k < num_ticks; k += p.seg_ticks) {
-        const int T = std::min(p.seg_ticks, num_ticks - k);
-        BlockPlan b = bp;
-        b.block = std::min(b.block, T);
-        hipError_t e = queue_blocks(net, base, num_ticks, k, T, b, s, timed);
-        if (e != hipSuccess)
-            return hip_fail(e, "launching integration (several ticks)");
-    }
-    if (whole) {
-        BlockArgs wa;
-        memset(&wa, 0, sizeof wa);
-        set_plain_args(net, wa);
-        wa.ticks = num_ticks;
-        wa.ext_base = base;
-        wa.tick_words = (long long)tick_words;
-        wa.ext_sstride = (long long)num_ticks * wa.tick_words;
-        int slot = -1;
-        hipError_t e = timed ? prof_begin(net, 0, s, &slot) : hipSuccess;
-        if (e == hipSuccess)
-            e = launch_plain_whole(net->dn, wa, s);
-        if (e == hipSuccess && timed)
-            e = prof_end(net, slot, s);
-        if (e != hipSuccess)
-            return hip_fail(e, "launching integration (whole network)");
-    }
-    for (int k = 0; !whole && !bp.block && k < num_ticks; ++k) {
+    for (int k = 0; k < num_ticks; ++k) {
         TickArgs ta;
         ta.k = k;
         ta.ext_t = base ? base + (size_t)k * tick_words : nullptr;
@@ -1212,7 +1250,7 @@ static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_tick
                 return hip_fail(e, "launching the mesh link count");
         }
     }
-    hipError_t e = fused || bp.block ? hipSuccess : launch_fold_counts(net->dn, num_ticks, s);
+    hipError_t e = fused ? hipSuccess : launch_fold_counts(net->dn, num_ticks, s);
     if (e == hipSuccess)
         e = launch_advance_tick(net->dn, num_ticks, s);
     if (e == hipSuccess && via_words)
@@ -1447,6 +1485,8 @@ static ranc_status build_batch(ranc_net *const *nets, int num, const uint32_t *c
             phase_of[f.second] = (int)ph;
         }
     }
+    b.solo.clear();
+    b.is_solo.clear();
     b.nets.assign(nets, nets + num);
     b.uids.clear();
     for (int i = 0; i < num; ++i)
@@ -1470,6 +1510,15 @@ static ranc_status build_batch(ranc_net *const *nets, int num, const uint32_t *c
         e.phase = phase_of[i];
         if (p.path == RANC_PATH_SPARSE)
             return fail(RANC_EUNSUPPORTED, "nets[%d]: the sparse path runs one network per call", i);
+        b.is_solo.push_back(0);
+        if (!persistent && !budget) {
+            BlockPlan bp;
+            if (choose_form(net, num_ticks, true, bp) != FORM_TICKS) {
+                b.is_solo[i] = 1;
+                b.solo.push_back(i);
+                continue;
+            }
+        }
         if (p.path == RANC_PATH_MFMA) {
             e.code = mfma_shape_code(p.A, mfma_width(p.A, p.N, p.two), p.two);
             e.units = p.C * p.slices * ((p.S + p.spw - 1) / p.spw);
@@ -1477,6 +1526,15 @@ static ranc_status build_batch(ranc_net *const *nets, int num, const uint32_t *c
         } else {
             e.code = plain_shape_code(p.W, p.G);
             e.units = p.C * p.S * (p.N / 64);
+            if (p.size[R_RING8]) {
+                BlockArgs a;
+                set_plain_args(net, a);
+                e.ring8 = a.ring8;
+                e.dst = a.dst;
+                e.want_spk = a.want_spk;
+                b.pl.push_back(e);
+                continue;
+            }
             // batched routing reads the spike bitmaps from L2 (no LDS staging,
             // so the one launch keeps its occupancy for every network)
             RouteCfg rc = net->rcfg;
@@ -1550,13 +1608,14 @@ static ranc_status build_batch(ranc_net *const *nets, int num, const uint32_t *c
             mu += e.units;
         }
     }
-    // plain entries by phase, numbered from 0 within the phase
-    std::stable_sort(b.pl.begin(), b.pl.end(),
-                     [](const BatchEntry &x, const BatchEntry &y) { return x.phase < y.phase; });
+    // plain entries by phase, those with the byte ring first
+    std::stable_sort(b.pl.begin(), b.pl.end(), [](const BatchEntry &x, const BatchEntry &y) {
+        return x.phase != y.phase ? x.phase < y.phase : (x.ring8 != nullptr) > (y.ring8 != nullptr);
+    });
     int nphases = 0;
     for (int i = 0; i < num; ++i)
         nphases = std::max(nphases, phase_of[i] + 1);
-    b.phases.assign(nphases, Batch::Phase{0, 0, 0, 0, 0, 0});
+    b.phases.assign(nphases, Batch::Phase{});
     b.phase_links.assign(nphases, std::vector<int>());
     b.links.assign(num, 0);
     for (int i = 0; i < num; ++i) {
@@ -1570,9 +1629,18 @@ static ranc_status build_batch(ranc_net *const *nets, int num, const uint32_t *c
         ph.g_num += 1;
     }
     for (size_t i = b.pl.size(); i-- > 0;)
-        b.phases[b.pl[i].phase].pl_first = (int)i;
+        (b.pl[i].ring8 ? b.phases[b.pl[i].phase].pf_first : b.phases[b.pl[i].phase].pl_first) = (int)i;
     for (auto &e : b.pl) {
         Batch::Phase &ph = b.phases[e.phase];
+        if (e.ring8) {
+            if ((long long)ph.pf_units + e.units > INT32_MAX)
+                return fail(RANC_EUNSUPPORTED, "batch has too many work units");
+            e.unit_begin = ph.pf_units;
+            ph.pf_units += e.units;
+            ph.pf_num += 1;
+            pu += e.units;
+            continue;
+        }
         if ((long long)ph.pl_units + e.units > INT32_MAX || (long long)ph.rt_units + e.route_units > INT32_MAX)
             return fail(RANC_EUNSUPPORTED, "batch has too many work units");
         e.unit_begin = ph.pl_units;
@@ -1604,16 +1672,23 @@ static unsigned *batch_queue(ranc_net *lead)
 
 // Branch form of a batch's ticks: the networks of different shape classes do
 // not depend on each other, so each class's launches for all ticks form one
-// chain, and the chains (and the chain of the plain-path networks) run on the
+// chain, and the chains (and those of the plain-path networks and of each
+// network that runs several ticks per launch) run on the
 // lead handle's branch streams side by side, forked from and joined back to
 // `s` with events (under stream capture they become parallel branches of the
 // graph). Used when nothing orders the classes within a tick: one phase, no
 // persistent launch, no link counting, no per-launch timing.
+static int batch_chains(const Batch &b)
+{
+    const Batch::Phase &ph = b.phases[0];
+    return ph.g_num + (int)b.solo.size() + (ph.pf_num > 0 ? 1 : 0) + (ph.pl_num > 0 ? 1 : 0);
+}
+
 static hipError_t queue_batch_branches(ranc_net *lead, const Batch &b, hipStream_t s)
 {
     const BatchEntry *tpl = batch_table(lead, 1);
     const Batch::Phase &ph = b.phases[0];
-    const int chains = ph.g_num + (ph.pl_num > 0 ? 1 : 0);
+    const int chains = batch_chains(b);
     const int nb = std::min(chains, (int)ranc_net::BATCH_BRANCHES);
     hipError_t e = hipSuccess;
     for (int i = 0; e == hipSuccess && i < nb; ++i) {
@@ -1634,6 +1709,12 @@ static hipError_t queue_batch_branches(ranc_net *lead, const Batch &b, hipStream
             const Batch::Group &g = b.groups[ph.g_first + c];
             for (int k = 0; e == hipSuccess && k < b.num_ticks; ++k)
                 e = launch_integrate_mfma_group(g.args, g.units, k, g.code, g.ext, g.compact, st);
+        } else if (c < ph.g_num + (int)b.solo.size()) {
+            const int i = b.solo[c - ph.g_num];
+            e = queue_solo(b.nets[i], b.bases[i], b.num_ticks, st);
+        } else if (ph.pf_num > 0 && c == ph.g_num + (int)b.solo.size()) {
+            for (int k = 0; e == hipSuccess && k < b.num_ticks; ++k)
+                e = launch_plain_ticks_batch(tpl + ph.pf_first, ph.pf_num, ph.pf_units, k, st);
         } else {
             const BatchEntry *tp = tpl + ph.pl_first;
             for (int k = 0; e == hipSuccess && k < b.num_ticks; ++k) {
@@ -1660,21 +1741,16 @@ static ranc_status queue_batch_ticks(ranc_net *lead, const Batch &b, hipStream_t
     for (const auto &pl : b.phase_links)
         any_links = any_links || !pl.empty();
     const bool branches = !b.persistent && b.phases.size() == 1 && !any_links && !timed &&
-                          b.phases[0].g_num + (b.phases[0].pl_num > 0 ? 1 : 0) > 1;
-    // the batched plain kernels work on the bit ring
-    auto move_rings = [&](int to_bytes) -> hipError_t {
-        hipError_t e = hipSuccess;
-        for (size_t i = 0; e == hipSuccess && i < b.nets.size(); ++i)
-            if (b.nets[i]->p.size[R_RING8])
-                e = launch_move_ring(b.nets[i]->dn, b.nets[i]->ws + b.nets[i]->p.off[R_RING8], to_bytes, s);
-        return e;
-    };
-    if (hipError_t e = move_rings(0); e != hipSuccess)
-        return hip_fail(e, "moving the scheduled spikes");
+                          batch_chains(b) > 1;
     if (branches) {
         hipError_t e = queue_batch_branches(lead, b, s);
         if (e != hipSuccess)
             return hip_fail(e, "launching batch integration (branches)");
+    }
+    for (int i : b.solo) {
+        hipError_t e = branches ? hipSuccess : queue_solo(b.nets[i], b.bases[i], b.num_ticks, s);
+        if (e != hipSuccess)
+            return hip_fail(e, "launching batch integration (several ticks)");
     }
     for (const Batch::Phase &ph : b.phases)
     for (int k = 0; !branches && k < b.num_ticks; ++k) {
@@ -1692,6 +1768,15 @@ static ranc_status queue_batch_ticks(ranc_net *lead, const Batch &b, hipStream_t
                 e = prof_end(lead, slot, s);
             if (e != hipSuccess)
                 return hip_fail(e, "launching batch integration (MFMA)");
+        }
+        if (ph.pf_num > 0) {
+            e = timed ? prof_begin(lead, 0, s, &slot) : hipSuccess;
+            if (e == hipSuccess)
+                e = launch_plain_ticks_batch(tpl + ph.pf_first, ph.pf_num, ph.pf_units, k, s);
+            if (e == hipSuccess && timed)
+                e = prof_end(lead, slot, s);
+            if (e != hipSuccess)
+                return hip_fail(e, "launching batch integration (plain)");
         }
         if (ph.pl_num > 0) {
             const BatchEntry *tp = tpl + ph.pl_first;
@@ -1717,13 +1802,12 @@ static ranc_status queue_batch_ticks(ranc_net *lead, const Batch &b, hipStream_t
     }
     hipError_t e = hipSuccess;
     for (size_t i = 0; e == hipSuccess && i < b.nets.size(); ++i)
-        e = launch_fold_counts(b.nets[i]->dn, b.num_ticks, s);
+        if (!b.is_solo[i] && !b.nets[i]->p.size[R_RING8])   // (the others add to the totals themselves)
+            e = launch_fold_counts(b.nets[i]->dn, b.num_ticks, s);
     if (e == hipSuccess && !b.mf.empty())
         e = launch_advance_batch(tmf, (int)b.mf.size(), b.num_ticks, queue, s);
     if (e == hipSuccess && !b.pl.empty())
         e = launch_advance_batch(tpl, (int)b.pl.size(), b.num_ticks, queue, s);
-    if (e == hipSuccess)
-        e = move_rings(1);
     if (e != hipSuccess)
         return hip_fail(e, "advancing batch ticks");
     return RANC_OK;
@@ -1775,6 +1859,8 @@ static ranc_status run_batch(ranc_net *const *nets, int num, const uint32_t *con
         b.phases = std::move(nb.phases);
         b.phase_links = std::move(nb.phase_links);
         b.links = std::move(nb.links);
+        b.solo = std::move(nb.solo);
+        b.is_solo = std::move(nb.is_solo);
         b.persistent = nb.persistent;
         b.mf_units = nb.mf_units;
         b.pl_units = nb.pl_units;

@@ -164,3 +164,33 @@ def test_workspace_without_the_byte_ring():
             for k, v in R.ranc_read_counters(handle, s).items():
                 assert v == ref[s]["counters"][k], (size, s, k)
         R.ranc_free(handle)
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_batch_of_every_form(graph):
+    """One batch of networks that run one launch per tick on the byte ring
+    (every core shape of the wave form), a whole call in one launch, blocks of
+    ticks on both paths, and the MFMA tick loop; called twice."""
+    import torch
+    from paper_2404_16208_amd.ranc import RancNet, run_batch
+    T = 14
+    nets = [(recurrent(70 + i, 5, A, N, G, 5, max_delay=1 + i), "plain", 9) for i, (A, N, G) in
+            enumerate([(64, 512, 1), (512, 64, 8), (128, 128, 2), (256, 256, 4), (512, 512, 8)])]
+    nets += [(recurrent(80, 40, 128, 128, 4, 8), "plain", 7), (recurrent(81, 24, 256, 64, 2, 6, potential_bits=12), "plain", 5),
+             (forward_net(82, 30, 128, 128, 4, 8, 6), "plain", 3), (forward_net(83, 6, 256, 256, 4, 9, 3), "mfma", 70),
+             (recurrent(84, 6, 256, 128, 4, 3), "mfma", 65)]
+    gs, xs, refs = [], [], []
+    for net, path, S in nets:
+        x = W.bernoulli_inputs(3, net, S, 2 * T, 0.2, config_id=872)
+        refs.append(oracle_results(net, x, 2 * T, sorted({0, S - 1})))
+        xs.append(torch.from_numpy(x.view(np.int32)).cuda())
+        gs.append(RancNet(net, S, T, path=path, workspace_fill=0xA5))
+    bufs = [torch.empty((x.shape[0], T) + tuple(x.shape[2:]), dtype=torch.int32, device="cuda") for x in xs]
+    for call in range(2):
+        for b, x in zip(bufs, xs):
+            b.copy_(x[:, call * T:(call + 1) * T])
+        run_batch(gs, bufs, T, graph=graph)
+        torch.cuda.synchronize()
+    for g, ref in zip(gs, refs):
+        for s, r in ref.items():
+            assert_sample_equal(g, r, s, 2 * T, what=f"{g.net.name}/{g.path}")
