@@ -64,7 +64,10 @@ enum {
 
 /* Integration paths (fixed at load time; they differ in device data layout). */
 enum {
-    RANC_PATH_AUTO = 0,   /* pick per shape */
+    RANC_PATH_AUTO = 0,   /* pick per shape: the MFMA path from 64 samples on, and from 32 on where the
+                             network has 2^20 neurons times samples and the workspace holds it (such
+                             a handle also takes the plain path's launch shapes, without effect, and
+                             no state-resident runs); else the plain path */
     RANC_PATH_PLAIN = 1,  /* per (core, sample) workgroups, crossbar words and popcounts */
     RANC_PATH_MFMA = 2,   /* per-core workgroups over sample tiles, exact int8 MFMA;
                              every supported core shape (512 neurons run as 256-neuron
@@ -231,8 +234,10 @@ ranc_status ranc_load_network(const ranc_net_desc *desc, int32_t num_samples,
  * at most once) advance together: per tick, one launch per MFMA shape class
  * (axons, neurons per workgroup, weight planes, potential clamp) runs every
  * MFMA-path network of that class (or, with RANC_BATCH_PERSISTENT, one
- * persistent launch runs all of them from a work queue), and one launch each
- * integrates and routes every plain-path network. The batch tables are kept in the workspace of nets[0] (at most
+ * persistent launch runs all of them from a work queue), and one launch
+ * integrates the small plain-path networks. Networks that run several ticks per
+ * launch and plain-path networks of 2^17 neurons times samples or more have
+ * launches of their own, beside the others'. The batch tables are kept in the workspace of nets[0] (at most
  * 128 networks per path); they are rebuilt, with a synchronization of
  * `stream`, whenever the list of networks, the input addresses or num_ticks
  * change. Results are identical to running each network alone.
@@ -357,8 +362,9 @@ typedef struct ranc_tune {
                                         destination word (the three router fields above apply);
                                         8 = the form for launches too small to fill the GPU: spikes
                                         are delivered by the kernel that integrates (the router
-                                        fields do not apply; networks of more than 2^22 neurons
-                                        times samples still take a router launch); 0 in
+                                        fields do not apply; networks of more than 2^26 neurons
+                                        times samples, or 2^22 from 64 samples on, still take
+                                        a router launch); 0 in
                                         ranc_set_launch_shape = chosen automatically */
 } ranc_tune;
 

@@ -614,7 +614,7 @@ __device__ __forceinline__ void plain_tick_wave(const BatchEntry &e, int k, int 
     const unsigned ou = (unsigned)__popcll(b & (n.outmask[m0] | (uint64_t)n.outmask[m0 + 1] << 32));
     if (lane < 2) {
         const uint32_t word = (uint32_t)(b >> (32 * lane));
-        if (e.want_spk)
+        if (e.form & BATCH_WANT_SPK)
             n.spk[((size_t)s * n.C + c) * n.NW + 2 * nb + lane] = word;
         const int ow = n.outword[m0 + lane];
         if (ow >= 0)

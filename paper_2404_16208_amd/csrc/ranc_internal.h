@@ -226,14 +226,20 @@ struct BatchEntry {
     int spw;                    // samples per workgroup (MFMA path)
     int code;
     int unit_begin, units;      // integration units
-    int route_begin, route_units, route_code, route_split;   // plain path: router units and shape
+    union {
+        struct {
+            int route_begin, route_units, route_code, route_split;   // plain path: router units and shape
+        };
+        struct {
+            uint8_t *ring8;         // plain path with the byte ring (see BlockArgs)
+            const uint32_t *dst;
+        };
+    };
     int phase;                  // cache-sized phase of the batch (host bookkeeping)
-    int compact;                // MFMA path: B tiles built from the compact crossbar (host bookkeeping)
-    // plain path, networks with the byte ring (see BlockArgs)
-    uint8_t *ring8;
-    const uint32_t *dst;
-    int want_spk;
+    int form;                   // MFMA path: 1 = B tiles built from the compact crossbar (host bookkeeping);
+                                // plain path: BATCH_BYTES, BATCH_WANT_SPK
 };
+enum { BATCH_BYTES = 1, BATCH_WANT_SPK = 2 };
 
 // Networks of one MFMA shape class in one launch, passed by value as kernel
 // arguments (at most 4 KiB): pointers read from kernel arguments are known

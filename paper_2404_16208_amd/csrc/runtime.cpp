@@ -74,6 +74,7 @@ struct Plan {
     // `order` (levels + 1 entries), and the ticks a segment of a call may run
     // at most (the history ring holds D more). No levels: tick by tick.
     int levels = 0, seg_ticks = 1;
+    bool auto_mid = false;       // the MFMA path chosen for fewer than 64 samples
     bool multi_source = false;   // some axon has several sources
     int sorted_words = 0;        // plain path: words per axon type of the sorted columns, 0: none
     std::vector<int32_t> order, level, level_first;
@@ -206,8 +207,17 @@ bool neuron_model_ext(const ranc_net_desc *d)
 // (directly or through others): a core's level is the longest path to it from
 // a core without sources. More than MAX_LEVELS levels, or a cycle: none.
 constexpr int MAX_LEVELS = 64;
-constexpr long long PLAIN_FUSED_MAX_NEURONS = 1 << 22;   // neurons times samples
-constexpr long long PLAIN_RING8_MAX_BYTES = 512 << 20;
+// Lines of the dispatch, in neurons times samples.
+constexpr long long AUTO_MFMA_MIN_NEURONS = 1 << 20;
+constexpr long long PLAIN_SOLO_MIN_NEURONS = 1 << 17;
+// The byte ring, and so the plain path's launches without a router, up to here
+// and to 2 GiB of ring (a byte per axon, sample and slot; its addresses within a
+// slot have 28 bits); with 64 samples or more, where the automatic path is
+// MFMA, up to 2^22. With a router and without, us per tick: 512 cores of
+// 256 x 256 with 63 samples 127 and 59, 4096 with 10 samples 201 and 155, 1024
+// of 512 x 512 with 30 samples 402 and 200.
+constexpr long long PLAIN_FUSED_MAX_NEURONS = 1 << 26, PLAIN_FUSED_MAX_NEURONS_S64 = 1 << 22;
+constexpr long long PLAIN_RING8_MAX_BYTES = 2LL << 30;
 // The whole-network form (kern_plain_whole.hip) loads and stores everything
 // once per call: 18 us and 1.9 us per tick for 12 cores of 256 x 256, against
 // 5 us and 3.4 us per tick.
@@ -272,10 +282,13 @@ bool feed_forward_levels(const ranc_net_desc *d, Plan &p)
     return true;
 }
 
-// blocks: lay out a feed-forward MFMA network for several ticks per launch
-// (a longer history ring); without, as for any other network.
-ranc_status make_plan(const ranc_net_desc *d, int32_t S, int32_t RT, int32_t path, Plan &p, bool blocks = true)
+// level: what the layout may use memory for. PLAN_FULL: RANC_PATH_AUTO may take
+// the MFMA path below 64 samples; PLAN_FORMS: rings for several ticks per launch
+// and for launches without a router; PLAN_SMALL: neither.
+enum PlanLevel { PLAN_SMALL, PLAN_FORMS, PLAN_FULL };
+ranc_status make_plan(const ranc_net_desc *d, int32_t S, int32_t RT, int32_t path, Plan &p, PlanLevel level = PLAN_FULL)
 {
+    const bool blocks = level >= PLAN_FORMS;
     ranc_status st = validate(d, S, RT, path);
     if (st != RANC_OK)
         return st;
@@ -294,8 +307,18 @@ ranc_status make_plan(const ranc_net_desc *d, int32_t S, int32_t RT, int32_t pat
     p.grid_w = d->grid_w;
     p.grid_h = d->grid_h;
     p.two = d->weight_bits > 8;
-    if (path == RANC_PATH_AUTO)
-        path = (S >= 64 && mfma_shape_supported(p.A, p.N, p.two)) ? RANC_PATH_MFMA : RANC_PATH_PLAIN;
+    if (path == RANC_PATH_AUTO) {
+        // From 64 samples on (one full tile) the MFMA path, whose time goes by
+        // tiles; from 32 on where the network has a million neurons times
+        // samples. us per tick, plain and MFMA: 128 cores of 256 x 256 with 23
+        // and 40 samples 11.5, 13.8 and 15.8, 13.8; 64 cores with 32 and 63 9.6,
+        // 11.9 and 14.1, 12.4; 512 with 40 and 63 42, 27 and 59, 27; 64 of 512 x
+        // 512 with 50 34, 15; four layers of 128 cores with 48 36, 7.6 (several
+        // ticks per launch). The other way 512 of 128 x 128 with 40: 22, 25.
+        const bool mid = level >= PLAN_FULL && S >= 32 && S < 64 && (long long)p.C * p.N * S >= AUTO_MFMA_MIN_NEURONS;
+        path = (S >= 64 || mid) && mfma_shape_supported(p.A, p.N, p.two) ? RANC_PATH_MFMA : RANC_PATH_PLAIN;
+        p.auto_mid = mid && path == RANC_PATH_MFMA;
+    }
     if (path == RANC_PATH_MFMA && !mfma_shape_supported(p.A, p.N, p.two))
         return fail(RANC_EUNSUPPORTED, "MFMA path does not support A=%d N=%d with %d-bit weights", p.A, p.N,
                     d->weight_bits);
@@ -313,11 +336,10 @@ ranc_status make_plan(const ranc_net_desc *d, int32_t S, int32_t RT, int32_t pat
             p.Q = p.D + p.seg_ticks;
         }
     }
-    // plain path with few (core, sample) pairs: the byte ring, longer for a
-    // feed-forward network, at most 512 MB
+    // plain path: the byte ring, longer for a feed-forward network
     const long long slot8 = (long long)p.C * p.A * S;
-    const bool ring8 = blocks && path == RANC_PATH_PLAIN && (long long)p.C * p.N * S <= PLAIN_FUSED_MAX_NEURONS &&
-                       slot8 * (p.D + 2) <= PLAIN_RING8_MAX_BYTES;
+    const bool ring8 = blocks && path == RANC_PATH_PLAIN && (long long)p.C * p.N * S <= (S < 64 ? PLAIN_FUSED_MAX_NEURONS : PLAIN_FUSED_MAX_NEURONS_S64) &&
+                       slot8 * (p.D + 2) <= PLAIN_RING8_MAX_BYTES && (long long)p.C * p.A < 1LL << 28;
     if (ring8) {
         p.Q = p.D + 2;
         const int seg = std::min(RT, MFMA_BLOCK_TICKS_MAX);
@@ -871,7 +893,7 @@ struct Batch {
     // numbered from 0 within the phase. One phase when persistent.
     struct Phase { int g_first, g_num, pf_first, pf_num, pf_units, pl_first, pl_num, pl_units, rt_units; };
     // networks (indexes in nets) that run the call's ticks in launches of
-    // their own, several ticks each; they are in no other list
+    // their own (runs_solo); they are in no other list
     std::vector<int> solo;
     std::vector<char> is_solo;
     std::vector<Phase> phases;
@@ -930,8 +952,7 @@ static int mfma_compact(const ranc_net *net)
     return p.bsrc >= 0 ? p.bsrc : mfma_compact_b(net->dn, p.two, p.spw) ? 1 : 0;
 }
 
-// Plain path: the form without a router wherever the network has it (up to 2^22
-// neurons times samples, where it takes a third to two thirds of the time).
+// Plain path: the form without a router wherever the network has the byte ring.
 static int auto_lanes(const ranc_net *net, const RouteCfg &rc)
 {
     return net->p.size[R_RING8] ? route_fused_lanes() : route_auto_lanes(net->dn, rc);
@@ -1153,13 +1174,6 @@ static hipError_t queue_several(ranc_net *net, const uint32_t *base, int num_tic
     return e;
 }
 
-// A batch's network that runs several ticks per launch, its tick advance included.
-static hipError_t queue_solo(ranc_net *net, const uint32_t *base, int num_ticks, hipStream_t s)
-{
-    hipError_t e = queue_several(net, base, num_ticks, s, false);
-    return e == hipSuccess ? launch_advance_tick(net->dn, num_ticks, s) : e;
-}
-
 // Samples per workgroup of k_plain_ticks, one tick per launch: as many as keep
 // the launch within what the GPU holds at once (2048 threads on 256 CUs). One
 // to three measured the same at 128 cores x 23 samples, six 17% slower.
@@ -1168,6 +1182,25 @@ static int plain_samples_per_wg(const Plan &p)
     const long long held = 256LL * 2048 / p.N / p.C;   // samples in one round of workgroups
     const long long spw = held < 1 ? 1 : (p.S + held - 1) / held;
     return (int)std::min<long long>(spw, 32);
+}
+
+// Tick k of the call on the plain path without a router (k_plain_ticks).
+static hipError_t queue_plain_tick(ranc_net *net, const uint32_t *base, int num_ticks, int k, hipStream_t s)
+{
+    const Plan &p = net->p;
+    BlockArgs a;
+    memset(&a, 0, sizeof a);
+    a.count = p.C;
+    a.block = a.ticks = 1;
+    a.k0 = k;
+    set_plain_args(net, a);
+    a.ext_base = base;
+    a.tick_words = (long long)p.Cin * p.W;
+    a.ext_sstride = (long long)num_ticks * a.tick_words;
+    a.spw = plain_samples_per_wg(p);
+    if ((long long)p.C * p.N * p.S < PLAIN_SORTED_MIN_WORK)
+        a.sorted_words = 0;
+    return launch_plain_ticks(net->dn, a, s);
 }
 
 // Queue num_ticks ticks on stream s: per tick the integration (and on the
@@ -1207,24 +1240,10 @@ static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_tick
             if (e != hipSuccess)
                 return hip_fail(e, "collecting kernel timings");
         }
-        BlockArgs pa;
-        if (fused) {
-            memset(&pa, 0, sizeof pa);
-            pa.count = p.C;
-            pa.block = pa.ticks = 1;
-            pa.k0 = k;
-            set_plain_args(net, pa);
-            pa.ext_base = base;
-            pa.tick_words = (long long)tick_words;
-            pa.ext_sstride = ta.ext_sstride;
-            pa.spw = plain_samples_per_wg(p);
-            if ((long long)p.C * p.N * p.S < PLAIN_SORTED_MIN_WORK)
-                pa.sorted_words = 0;
-        }
         int slot = -1;
         hipError_t e = timed ? prof_begin(net, 0, s, &slot) : hipSuccess;
         if (e == hipSuccess)
-            e = fused                        ? launch_plain_ticks(net->dn, pa, s)
+            e = fused                        ? queue_plain_tick(net, base, num_ticks, k, s)
                 : p.path == RANC_PATH_MFMA   ? launch_integrate_mfma(net->dn, ta, p.two, p.spw, mfma_compact(net), s)
                 : p.path == RANC_PATH_SPARSE ? launch_integrate_sparse(net->dn, ta, p.spw, s)
                                              : launch_integrate_plain(net->dn, ta, s);
@@ -1258,6 +1277,25 @@ static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_tick
     if (e != hipSuccess)
         return hip_fail(e, "advancing the tick");
     return RANC_OK;
+}
+
+// Whether a batch runs network `net` in launches of its own (queue_ticks): those
+// that run several ticks per launch, and plain networks without a router large
+// enough that a few of them fill the GPU. k_plain_ticks keeps a core's columns
+// in registers for several samples where the batch's kernel reads them for
+// each, and the chains run beside each other: the eight networks of a sweep
+// with 8 samples (16 thousand to a million neurons times samples) 1405 us for
+// 16 ticks in one launch per tick, 1120 with those from 2^20 on alone, 640 from
+// 2^18, 633 from 2^16, 697 each alone; five networks with 15 samples 3550,
+// 1769, 1171, 1128, 1130.
+static bool runs_solo(const ranc_net *net, int num_ticks, bool several)
+{
+    const Plan &p = net->p;
+    BlockPlan bp;
+    if (p.path == RANC_PATH_PLAIN && p.size[R_RING8] &&
+        (long long)p.C * p.N * p.S >= PLAIN_SOLO_MIN_NEURONS)
+        return true;
+    return several && choose_form(net, num_ticks, true, bp) != FORM_TICKS;
 }
 
 // Run num_ticks ticks as one captured graph: the tick loop is captured once
@@ -1350,8 +1388,8 @@ static unsigned long long resident_wait_us()
 static const char *resident_blocker(const ranc_net *net, int num_ticks, int *grid)
 {
     const Plan &p = net->p;
-    if (p.path != RANC_PATH_MFMA)
-        return "the state-resident loop runs MFMA-path handles only";
+    if (p.path != RANC_PATH_MFMA || p.auto_mid)
+        return "the state-resident loop runs MFMA-path handles (64 samples or the path asked for) only";
     if (p.N != 256 || p.slices != 1)
         return "the state-resident loop needs cores of 256 neurons";
     if (p.A > 256)
@@ -1496,6 +1534,10 @@ static ranc_status build_batch(ranc_net *const *nets, int num, const uint32_t *c
     b.mf.clear();
     b.pl.clear();
     b.rt_lds = 0;
+    int num_mf = 0, num_pl = 0;   // as RANC_PATH_AUTO's rule of 64 samples counts them
+    for (int i = 0; i < num; ++i)
+        ++(nets[i]->p.path == RANC_PATH_MFMA && !nets[i]->p.auto_mid ? num_mf : num_pl);
+    int spare = BATCH_MAX - num_mf;
     for (int i = 0; i < num; ++i) {
         ranc_net *net = nets[i];
         const Plan &p = net->p;
@@ -1506,18 +1548,17 @@ static ranc_status build_batch(ranc_net *const *nets, int num, const uint32_t *c
         e.tick_words = (long long)p.Cin * p.W;
         e.ext_sstride = (long long)num_ticks * e.tick_words;
         e.spw = p.spw;
-        e.compact = p.path == RANC_PATH_MFMA ? mfma_compact(net) : 0;
+        e.form = p.path == RANC_PATH_MFMA ? mfma_compact(net) : 0;
         e.phase = phase_of[i];
         if (p.path == RANC_PATH_SPARSE)
             return fail(RANC_EUNSUPPORTED, "nets[%d]: the sparse path runs one network per call", i);
         b.is_solo.push_back(0);
-        if (!persistent && !budget) {
-            BlockPlan bp;
-            if (choose_form(net, num_ticks, true, bp) != FORM_TICKS) {
-                b.is_solo[i] = 1;
-                b.solo.push_back(i);
-                continue;
-            }
+        // (networks below 64 samples that RANC_PATH_AUTO put on the MFMA path
+        // take what places the others leave)
+        if (runs_solo(net, num_ticks, !persistent && !budget) || (p.auto_mid && --spare < 0)) {
+            b.is_solo[i] = 1;
+            b.solo.push_back(i);
+            continue;
         }
         if (p.path == RANC_PATH_MFMA) {
             e.code = mfma_shape_code(p.A, mfma_width(p.A, p.N, p.two), p.two);
@@ -1531,7 +1572,7 @@ static ranc_status build_batch(ranc_net *const *nets, int num, const uint32_t *c
                 set_plain_args(net, a);
                 e.ring8 = a.ring8;
                 e.dst = a.dst;
-                e.want_spk = a.want_spk;
+                e.form = BATCH_BYTES | (a.want_spk ? BATCH_WANT_SPK : 0);
                 b.pl.push_back(e);
                 continue;
             }
@@ -1548,13 +1589,13 @@ static ranc_status build_batch(ranc_net *const *nets, int num, const uint32_t *c
             b.pl.push_back(e);
         }
     }
-    if ((int)b.mf.size() > BATCH_MAX || (int)b.pl.size() > BATCH_MAX)
+    if (num_mf > BATCH_MAX || num_pl > BATCH_MAX)
         return fail(RANC_EUNSUPPORTED, "a batch holds at most %d networks per path", BATCH_MAX);
     auto work = [](const BatchEntry &e) {
         return (double)e.spw * (e.n.N / e.n.slices) * (e.n.A + 64) * ((e.code & 1) ? 2 : 1);
     };
     auto ext = [](const BatchEntry &e) { return e.n.model_ext; };
-    auto compact = [](const BatchEntry &e) { return e.compact; };
+    auto compact = [](const BatchEntry &e) { return e.form; };
     long long mu = 0, pu = 0, ru = 0;
     if (persistent) {
         // one unit numbering, largest units first
@@ -1610,7 +1651,7 @@ static ranc_status build_batch(ranc_net *const *nets, int num, const uint32_t *c
     }
     // plain entries by phase, those with the byte ring first
     std::stable_sort(b.pl.begin(), b.pl.end(), [](const BatchEntry &x, const BatchEntry &y) {
-        return x.phase != y.phase ? x.phase < y.phase : (x.ring8 != nullptr) > (y.ring8 != nullptr);
+        return x.phase != y.phase ? x.phase < y.phase : (x.form & BATCH_BYTES) > (y.form & BATCH_BYTES);
     });
     int nphases = 0;
     for (int i = 0; i < num; ++i)
@@ -1620,7 +1661,7 @@ static ranc_status build_batch(ranc_net *const *nets, int num, const uint32_t *c
     b.links.assign(num, 0);
     for (int i = 0; i < num; ++i) {
         b.links[i] = nets[i]->links_on ? 1 : 0;
-        if (nets[i]->links_on)
+        if (nets[i]->links_on && !b.is_solo[i])
             b.phase_links[phase_of[i]].push_back(i);
     }
     for (size_t g = b.groups.size(); g-- > 0;) {
@@ -1629,10 +1670,10 @@ static ranc_status build_batch(ranc_net *const *nets, int num, const uint32_t *c
         ph.g_num += 1;
     }
     for (size_t i = b.pl.size(); i-- > 0;)
-        (b.pl[i].ring8 ? b.phases[b.pl[i].phase].pf_first : b.phases[b.pl[i].phase].pl_first) = (int)i;
+        ((b.pl[i].form & BATCH_BYTES) ? b.phases[b.pl[i].phase].pf_first : b.phases[b.pl[i].phase].pl_first) = (int)i;
     for (auto &e : b.pl) {
         Batch::Phase &ph = b.phases[e.phase];
-        if (e.ring8) {
+        if (e.form & BATCH_BYTES) {
             if ((long long)ph.pf_units + e.units > INT32_MAX)
                 return fail(RANC_EUNSUPPORTED, "batch has too many work units");
             e.unit_begin = ph.pf_units;
@@ -1711,7 +1752,8 @@ static hipError_t queue_batch_branches(ranc_net *lead, const Batch &b, hipStream
                 e = launch_integrate_mfma_group(g.args, g.units, k, g.code, g.ext, g.compact, st);
         } else if (c < ph.g_num + (int)b.solo.size()) {
             const int i = b.solo[c - ph.g_num];
-            e = queue_solo(b.nets[i], b.bases[i], b.num_ticks, st);
+            if (queue_ticks(b.nets[i], b.bases[i], b.num_ticks, st, false) != RANC_OK)
+                return hipErrorLaunchFailure;
         } else if (ph.pf_num > 0 && c == ph.g_num + (int)b.solo.size()) {
             for (int k = 0; e == hipSuccess && k < b.num_ticks; ++k)
                 e = launch_plain_ticks_batch(tpl + ph.pf_first, ph.pf_num, ph.pf_units, k, st);
@@ -1748,9 +1790,9 @@ static ranc_status queue_batch_ticks(ranc_net *lead, const Batch &b, hipStream_t
             return hip_fail(e, "launching batch integration (branches)");
     }
     for (int i : b.solo) {
-        hipError_t e = branches ? hipSuccess : queue_solo(b.nets[i], b.bases[i], b.num_ticks, s);
-        if (e != hipSuccess)
-            return hip_fail(e, "launching batch integration (several ticks)");
+        const ranc_status st = branches ? RANC_OK : queue_ticks(b.nets[i], b.bases[i], b.num_ticks, s, false);
+        if (st != RANC_OK)
+            return st;
     }
     for (const Batch::Phase &ph : b.phases)
     for (int k = 0; !branches && k < b.num_ticks; ++k) {
@@ -1940,10 +1982,10 @@ ranc_status ranc_load_network(const ranc_net_desc *desc, int32_t num_samples, in
         return fail(RANC_EINVAL, "workspace is NULL");
     if ((uintptr_t)workspace % 256)
         return fail(RANC_EINVAL, "workspace must be 256-byte aligned");
-    if (workspace_bytes < p.total && (p.levels || p.size[R_RING8])) {
-        // a workspace sized for the layout without these
-        Plan q;
-        st = make_plan(desc, num_samples, max_ticks_per_call, path, q, false);
+    for (int level = PLAN_FORMS; workspace_bytes < p.total && level >= PLAN_SMALL; --level) {
+        // a workspace sized for a layout without these
+        Plan q{};
+        st = make_plan(desc, num_samples, max_ticks_per_call, path, q, (PlanLevel)level);
         if (st != RANC_OK)
             return st;
         p = std::move(q);
@@ -2066,7 +2108,7 @@ ranc_status ranc_load_network_static(const ranc_net_desc *desc, int32_t num_samp
         return fail(RANC_EINVAL, "out is NULL");
     *out = nullptr;
     Plan p{};
-    ranc_status st = make_plan(desc, num_samples, max_ticks_per_call, path, p, false);
+    ranc_status st = make_plan(desc, num_samples, max_ticks_per_call, path, p, PLAN_SMALL);
     if (st != RANC_OK)
         return st;
     if (p.total > RANC_STATIC_WORKSPACE_BYTES)
@@ -2660,10 +2702,13 @@ ranc_status ranc_set_launch_shape(ranc_net *net, const ranc_tune *shape)
     if (!net || !shape)
         return fail(RANC_EINVAL, "net or shape is NULL");
     const Plan &p = net->p;
-    if (p.path != RANC_PATH_PLAIN) {
-        const int v = shape->samples_per_wg;
-        const int cap = p.path == RANC_PATH_SPARSE ? sparse_max_samples_per_wg() : mfma_max_samples_per_wg();
-        if (v <= 0 || v % 64 || v > cap)
+    const int v = shape->samples_per_wg;
+    const int cap = p.path == RANC_PATH_SPARSE ? sparse_max_samples_per_wg() : mfma_max_samples_per_wg();
+    const bool v_ok = v > 0 && v % 64 == 0 && v <= cap;
+    // (a handle below 64 samples that RANC_PATH_AUTO put on the MFMA path also
+    // takes the shapes of the plain path, which do nothing there)
+    if (p.path != RANC_PATH_PLAIN && (!p.auto_mid || v_ok)) {
+        if (!v_ok)
             return fail(RANC_EINVAL, "samples_per_wg %d must be a multiple of 64 in [64, %d]", v, cap);
         drop_graphs(net);
         net->p.spw = v;
@@ -2690,7 +2735,8 @@ ranc_status ranc_set_launch_shape(ranc_net *net, const ranc_tune *shape)
     if (rc.lanes != 1 && p.S > 65535)
         return fail(RANC_EINVAL, "route_lanes_per_word 8 takes at most 65535 samples");
     drop_graphs(net);
-    net->rcfg = rc;
+    if (p.path == RANC_PATH_PLAIN)
+        net->rcfg = rc;
     return RANC_OK;
 }
 

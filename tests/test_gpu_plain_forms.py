@@ -194,3 +194,69 @@ def test_batch_of_every_form(graph):
     for g, ref in zip(gs, refs):
         for s, r in ref.items():
             assert_sample_equal(g, r, s, 2 * T, what=f"{g.net.name}/{g.path}")
+
+
+@pytest.mark.parametrize("persistent", [False, True])
+@pytest.mark.parametrize("links", [False, True])
+def test_batch_of_networks_with_launches_of_their_own(links, persistent):
+    """Plain networks from 2^17 neurons times samples on (one just below, one
+    with the router asked for) beside small ones, over three calls."""
+    import torch
+    from paper_2404_16208_amd.ranc import RancNet, run_batch
+    T = 5
+    nets = [(recurrent(90, 64, 128, 128, 4, 8), 16), (recurrent(91, 32, 256, 128, 2, 8, potential_bits=12), 31),
+            (recurrent(92, 100, 64, 64, 8, 10, max_delay=9), 21), (recurrent(93, 24, 512, 256, 4, 6), 23),
+            (recurrent(94, 4, 64, 64, 1, 2), 3)]
+    gs, xs, refs = [], [], []
+    for i, (net, S) in enumerate(nets):
+        x = W.bernoulli_inputs(3, net, S, 3 * T, 0.2, config_id=872)
+        refs.append(oracle_results(net, x, 3 * T, [0, S - 1]))
+        xs.append(torch.from_numpy(x.view(np.int32)).cuda())
+        g = RancNet(net, S, T, path="plain", workspace_fill=0xA5)
+        g.count_links(links and i % 2 == 0)
+        if i == 3:
+            g.launch_shape(dict(g.launch_shape(), route_lanes_per_word=1))
+        gs.append(g)
+    for call in range(3):
+        run_batch(gs, [x[:, call * T:(call + 1) * T].contiguous() for x in xs], T, graph=call > 0, persistent=persistent)
+    for (net, S), g, ref in zip(nets, gs, refs):
+        for s, r in ref.items():
+            assert_sample_equal(g, r, s, 3 * T, what=f"{net.name} links={links}")
+
+
+# (cores, samples): below, at and above the million neurons times samples and
+# the 32 samples from which RANC_PATH_AUTO takes the MFMA path
+@pytest.mark.parametrize("C,S,path", [(128, 31, "plain"), (128, 32, "mfma"), (127, 32, "plain"), (66, 63, "mfma")])
+def test_automatic_path_below_64_samples(C, S, path):
+    """Results against the oracle and the plain path's, what the handle
+    accepts, and the plain path in a workspace sized for it."""
+    import torch
+    from paper_2404_16208_amd import ranc as R
+    net = recurrent(95, C, 256, 256, 4, C if C == 127 else C // 2)
+    T = 6
+    x = W.bernoulli_inputs(3, net, S, T, 0.2, config_id=872)
+    ref = oracle_results(net, x, T, [0, S - 1])
+    xd = torch.from_numpy(x.view(np.int32)).cuda()
+    for which in ("auto", "plain"):
+        g = R.RancNet(net, S, T, path=which, workspace_fill=0xA5)
+        assert g.path == (path if which == "auto" else "plain")
+        router = dict(samples_per_wg=0, route_samples_per_block=1, route_split=2, route_stage=0, route_lanes_per_word=1)
+        g.launch_shape(router)
+        with pytest.raises(R.RancError):
+            g.launch_shape(dict(router, route_split=0))
+        with pytest.raises(R.RancError):
+            g.run(xd, T, resident=True)
+        g.run(xd[:, :2].contiguous(), 2)
+        R.run_batch([g, R.RancNet(net, 2, 4, path="plain")], [xd[:, 2:].contiguous(), xd[:2, 2:].contiguous()], T - 2)
+        for s, r in ref.items():
+            assert_sample_equal(g, r, s, T, what=which)
+        g.close()
+    d = R.Desc(net)
+    size = R.ranc_workspace_bytes(d, S, T, R.RANC_PATH_PLAIN)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+    h = R.ranc_load_network(d, S, T, R.RANC_PATH_AUTO, ws.data_ptr(), size, st)
+    R.ranc_run_ticks([h], [xd.data_ptr()], R.RANC_INPUTS_ON_DEVICE, T, st)
+    for s, r in ref.items():
+        assert np.array_equal(R.ranc_read_potentials(h, s, C, 256), r["v"])
+    R.ranc_free(h)
