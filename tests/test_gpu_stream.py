@@ -70,6 +70,46 @@ def test_bulk_raster_equals_per_sample_readout(path, layout, S):
     g.close()
 
 
+# (ticks, samples, density of output neurons): the small and the large workgroups
+# of the tiled paths with 1, 2, 3 and 5 tiles of samples, and output neurons that
+# end within a block, of 64 to 2500
+@pytest.mark.parametrize("path", PATHS)
+@pytest.mark.parametrize("T,S,p_out", [(3, 2, 0.5), (3, 130, 0.03), (180, 40, 0.5), (180, 65, 0.5), (180, 129, 0.45),
+                                       (90, 300, 0.5)])
+def test_bulk_raster_blocks(path, T, S, p_out):
+    """Both layouts against the per-sample readout (decoded on the host from the
+    retained raster) for samples at the edges of tiles."""
+    import torch
+    from paper_2404_16208_amd.ranc import RancNet, decode_raster
+    net = W.random_net(62, 40, 64, 128, 4, grid_w=8, max_delay=3, density=0.3, p_core=0.45, p_out=p_out,
+                       thr_range=(32, 160), config_id=831)
+    rng = np.random.default_rng(T * S)
+    x = rng.integers(0, 1 << 32, (S, T, len(net.input_cores), 2), dtype=np.uint32) & rng.integers(
+        0, 1 << 32, (S, T, len(net.input_cores), 2), dtype=np.uint32)
+    g = RancNet(net, S, T, path=path)
+    g.run(torch.from_numpy(x.view(np.int32)).cuda(), T)
+    on = g.output_neurons()
+    bufs = {}
+    for layout in ("sample", "neuron"):
+        d = torch.full((g.raster_bytes(T, layout),), 0xA5, dtype=torch.uint8, device="cuda")
+        g.copy_raster(0, T, d, layout)
+        a = d.cpu().numpy()
+        bufs[layout] = a.view(np.uint32).reshape(T, S, -1) if layout == "sample" else a.view(np.uint64).reshape(T, len(on), -1)
+    total = 0
+    for s in sorted({0, 1, 31, 32, 63, 64, 127, 128, 255, 256, S - 1}):
+        if s < S:
+            want = g.spikes(s, 0, T)
+            total += len(want)
+            for layout, w in bufs.items():
+                assert np.array_equal(decode_raster(w, on, 0, s, layout), want), (layout, s)
+    assert total
+    if len(on) % 32:
+        assert not (bufs["sample"][:, :, -1] >> np.uint32(len(on) % 32)).any()
+    if S % 64:
+        assert not (bufs["neuron"][:, :, -1] >> np.uint64(S % 64)).any()
+    g.close()
+
+
 def test_copy_raster_rejects_ticks_outside_the_window():
     import torch
     from paper_2404_16208_amd import ranc as R
