@@ -78,4 +78,52 @@ __device__ inline uint32_t transpose32(uint32_t x, int lane)
     return transpose_stage<1>(x, lane);
 }
 
+// Four rows' compare, select and spike bit: v[i] = u[i] >= th ? r[i] : v[i],
+// f = 2 f + fire for i = 3 down to 0. Written out because the compiler turns
+// the spike bit into a select and a shift (two instructions); the compare's
+// lane mask is the carry of one add. Four compares come first, so each mask is
+// read at least three instructions after it was written (two are required).
+__device__ __forceinline__ void fire_rows(uint32_t &f, int32_t &v0, int32_t &v1, int32_t &v2, int32_t &v3, int32_t u0,
+                                          int32_t u1, int32_t u2, int32_t u3, int32_t r0, int32_t r1, int32_t r2,
+                                          int32_t r3, int32_t th)
+{
+    uint64_t m1, m2, m3;
+    asm volatile("v_cmp_ge_i32_e64 %7, %11, %16\n\t"
+        "v_cmp_ge_i32_e64 %6, %10, %16\n\t"
+        "v_cmp_ge_i32_e64 %5, %9, %16\n\t"
+        "v_cmp_ge_i32_e32 vcc, %8, %16\n\t"
+        "v_cndmask_b32_e64 %4, %4, %15, %7\n\t"
+        "v_cndmask_b32_e64 %3, %3, %14, %6\n\t"
+        "v_cndmask_b32_e64 %2, %2, %13, %5\n\t"
+        "v_cndmask_b32_e32 %1, %1, %12, vcc\n\t"
+        "v_addc_co_u32_e64 %0, %7, %0, %0, %7\n\t"
+        "v_addc_co_u32_e64 %0, %6, %0, %0, %6\n\t"
+        "v_addc_co_u32_e64 %0, %5, %0, %0, %5\n\t"
+        "v_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
+        : "+v"(f), "+v"(v0), "+v"(v1), "+v"(v2), "+v"(v3), "=&s"(m1), "=&s"(m2), "=&s"(m3)
+        : "v"(u0), "v"(u1), "v"(u2), "v"(u3), "v"(r0), "v"(r1), "v"(r2), "v"(r3), "v"(th)
+        : "vcc");
+}
+// (the same with u = v and one reset value)
+__device__ __forceinline__ void fire_rows(uint32_t &f, int32_t &v0, int32_t &v1, int32_t &v2, int32_t &v3, int32_t rs,
+                                          int32_t th)
+{
+    uint64_t m1, m2, m3;
+    asm volatile("v_cmp_ge_i32_e64 %7, %4, %9\n\t"
+        "v_cmp_ge_i32_e64 %6, %3, %9\n\t"
+        "v_cmp_ge_i32_e64 %5, %2, %9\n\t"
+        "v_cmp_ge_i32_e32 vcc, %1, %9\n\t"
+        "v_cndmask_b32_e64 %4, %4, %8, %7\n\t"
+        "v_cndmask_b32_e64 %3, %3, %8, %6\n\t"
+        "v_cndmask_b32_e64 %2, %2, %8, %5\n\t"
+        "v_cndmask_b32_e32 %1, %1, %8, vcc\n\t"
+        "v_addc_co_u32_e64 %0, %7, %0, %0, %7\n\t"
+        "v_addc_co_u32_e64 %0, %6, %0, %0, %6\n\t"
+        "v_addc_co_u32_e64 %0, %5, %0, %0, %5\n\t"
+        "v_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
+        : "+v"(f), "+v"(v0), "+v"(v1), "+v"(v2), "+v"(v3), "=&s"(m1), "=&s"(m2), "=&s"(m3)
+        : "v"(rs), "v"(th)
+        : "vcc");
+}
+
 }  // namespace ranc

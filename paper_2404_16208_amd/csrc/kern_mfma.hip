@@ -164,6 +164,8 @@ hipError_t launch_integrate_mfma_group(const MfmaGroupArgs &g, int total, int k,
     static_assert(sizeof(MfmaGroupArgs) + sizeof(int) <= 4096, "kernel arguments exceed 4 KiB");
     if (g.num < 1 || g.num > MFMA_GROUP_MAX || total < 1)
         return hipErrorInvalidValue;
+    if (code & MFMA_TILE)
+        return launch_integrate_tile_group(g, total, k, code & ~MFMA_TILE, compact, st);
     return compact ? launch_integrate_mfma_group_cb(g, total, k, code, ext, st)
                    : launch_group_code<false>(g, total, k, code, ext, st);
 }
@@ -177,8 +179,16 @@ hipError_t launch_integrate_mfma_group(const MfmaGroupArgs &g, int total, int k,
 // sweep, 512-neuron cores with 512 axons run 8-24% faster, while 64- and
 // 128-neuron cores and networks of fewer workgroups than CUs run 2-20%
 // slower with the compact source.
+// One-tile workgroups (kern_mfma_tile.hip) use the B tiles as they are built, and
+// take the compact source wherever there is a workgroup per CU, the two smallest
+// shapes apart. us per tick with planes and compact, 64 samples: 1024 cores of
+// 64 x 64 11.3, 11.3, 128 x 128 (9 bits) 25.2, 21.5, 256 x 256 (8 bits) 40.4, 36.3,
+// 512 x 512 (9 bits) 176, 112; 64 cores of 128 x 128 7.2, 7.6; 16 of 256 x 256
+// (9 bits) 9.3, 9.8.
 bool mfma_compact_b(const DevNet &n, int two_planes, int samples_per_wg)
 {
+    if (samples_per_wg == MFMA_TS)
+        return n.C * n.slices >= 256 && n.A * n.N * (two_planes ? 2 : 1) >= 128 * 128;
     return n.S <= samples_per_wg && n.N >= 256 && n.A * (two_planes ? 2 : 1) >= 256 && n.C * n.slices >= 256;
 }
 
@@ -212,6 +222,8 @@ hipError_t launch_integrate_mfma(const DevNet &n, const TickArgs &a, int two_pla
         samples_per_wg > MFMA_SPW_MAX || n.vlayout != VLAYOUT_BRICK || n.S64 % MFMA_TS || n.S > n.S64 ||
         (compact ? !n.colbits : !n.planes))
         return hipErrorInvalidValue;
+    if (samples_per_wg == MFMA_TS)
+        return launch_integrate_tile(n, a, two_planes, compact, st);
     if (compact)
         return launch_integrate_mfma_cb(n, a, two_planes, samples_per_wg, st);
     return launch_mfma_shape<false>(n, a, two_planes, samples_per_wg, st);

@@ -331,6 +331,10 @@ bool mfma_shape_supported(int A, int N, int two_planes);
 int mfma_width(int A, int N, int two_planes);   // neurons per MFMA workgroup (128 or 256)
 int mfma_slices(int A, int N, int two_planes);  // MFMA workgroups per core and sample chunk
 int mfma_shape_code(int A, int N, int two_planes);
+// shape codes of the one-tile form (kern_mfma_tile.hip)
+enum { MFMA_TILE_N64 = 32, MFMA_TILE = 64 };
+hipError_t launch_integrate_tile(const DevNet &n, const TickArgs &a, int two, int compact, hipStream_t st);
+hipError_t launch_integrate_tile_group(const MfmaGroupArgs &g, int total, int k, int code, int compact, hipStream_t st);
 int plain_shape_code(int W, int G);
 int route_shape_code(const RouteCfg &cfg, int max_delay);
 hipError_t launch_integrate_plain_batch(const BatchEntry *tab, int num, int total, int k, hipStream_t st);

@@ -60,7 +60,7 @@ enum Region {
 };
 
 struct Plan {
-    int C, A, N, G, W, NW, D, Q, S, S64, RT, Wout, Nout, Cin, path, two, spw;
+    int C, A, N, G, W, NW, D, Q, S, S64, RT, Wout, Nout, Cin, path, two, spw, spw_pipelined;
     int bsrc;            // MFMA path B source: -1 by mfma_compact_b, 0 the planes, 1 the compact crossbar
     int grid_w, grid_h;  // mesh size
     int slices;          // MFMA and sparse: neuron slices per core (one workgroup each)
@@ -282,6 +282,27 @@ bool feed_forward_levels(const ranc_net_desc *d, Plan &p)
     return true;
 }
 
+// MFMA path: whether workgroups take one tile of 64 samples each
+// (kern_mfma_tile.hip), or run a pipeline over several (kern_mfma_unit.h), which
+// read their core's B tiles once. One tile each: where the pipelines would leave
+// CUs idle; where the B tiles are few beside the potentials, or the pipelined
+// form's LDS leaves one workgroup on a CU; and where there are two tiles, unless
+// both planes of 256 neurons are read for each. us per tick, pipelined and
+// one tile each: 40 cores of 256 x 256 (8 bits) x 300 samples 28.2, 10.1; 2048 x 200
+// of 64 x 64 67.2, 59.6, of 128 x 128 (9 bits) 196, 131, of 256 x 256 (8 bits) 223,
+// 221; 4096 x 128 of 256 x 128 152, 143, of 512 x 256 (9 bits) 467, 397. The other
+// way, 2048 x 200 of 128 x 256 (9 bits) 231, 289, of 256 x 128 (8 bits) 124, 138, of
+// 512 x 256 (9 bits) 357, 376; 512 x 128 of 256 x 256 (9 bits) 40, 44.
+bool one_tile_per_workgroup(const Plan &p, int tiles)
+{
+    const bool wide = mfma_width(p.A, p.N, p.two) == 256;
+    if (tiles == 1 || (long long)p.C * p.slices * tiles <= 400)
+        return true;
+    if (wide && p.two)
+        return false;
+    return tiles == 2 || p.N == 64 || p.A <= 128 || (wide && p.A <= 256);
+}
+
 // level: what the layout may use memory for. PLAN_FULL: RANC_PATH_AUTO may take
 // the MFMA path below 64 samples; PLAN_FORMS: rings for several ticks per launch
 // and for launches without a router; PLAN_SMALL: neither.
@@ -374,7 +395,9 @@ ranc_status make_plan(const ranc_net_desc *d, int32_t S, int32_t RT, int32_t pat
         chunks = std::max(1, std::min(chunks, std::max(1, tiles / 4)));
         const int tiles_per = (tiles + chunks - 1) / chunks;
         const int cap = path == RANC_PATH_SPARSE ? sparse_max_samples_per_wg() : mfma_max_samples_per_wg();
-        p.spw = std::min(64 * tiles_per, std::min(cap, 512));
+        p.spw = p.spw_pipelined = std::min(64 * tiles_per, std::min(cap, 512));
+        if (path == RANC_PATH_MFMA && one_tile_per_workgroup(p, tiles))
+            p.spw = 64;
         if (const char *e = getenv("RANC_MFMA_SPW")) {
             const int v = atoi(e);
             if (v > 0 && v % 64 == 0 && v <= cap)
@@ -1547,7 +1570,7 @@ static ranc_status build_batch(ranc_net *const *nets, int num, const uint32_t *c
         e.ext_base = bases[i];
         e.tick_words = (long long)p.Cin * p.W;
         e.ext_sstride = (long long)num_ticks * e.tick_words;
-        e.spw = p.spw;
+        e.spw = p.spw == 64 && persistent ? p.spw_pipelined : p.spw;   // (the persistent kernel has the pipelined form)
         e.form = p.path == RANC_PATH_MFMA ? mfma_compact(net) : 0;
         e.phase = phase_of[i];
         if (p.path == RANC_PATH_SPARSE)
@@ -1562,7 +1585,9 @@ static ranc_status build_batch(ranc_net *const *nets, int num, const uint32_t *c
         }
         if (p.path == RANC_PATH_MFMA) {
             e.code = mfma_shape_code(p.A, mfma_width(p.A, p.N, p.two), p.two);
-            e.units = p.C * p.slices * ((p.S + p.spw - 1) / p.spw);
+            if (p.spw == 64 && !persistent)
+                e.code |= MFMA_TILE | (p.N == 64 ? MFMA_TILE_N64 : 0);
+            e.units = p.C * p.slices * ((p.S + e.spw - 1) / e.spw);
             b.mf.push_back(e);
         } else {
             e.code = plain_shape_code(p.W, p.G);
@@ -1594,7 +1619,8 @@ static ranc_status build_batch(ranc_net *const *nets, int num, const uint32_t *c
     auto work = [](const BatchEntry &e) {
         return (double)e.spw * (e.n.N / e.n.slices) * (e.n.A + 64) * ((e.code & 1) ? 2 : 1);
     };
-    auto ext = [](const BatchEntry &e) { return e.n.model_ext; };
+    // (one-tile launches take networks with and without the extended update)
+    auto ext = [](const BatchEntry &e) { return (e.code & MFMA_TILE) ? 0 : e.n.model_ext; };
     auto compact = [](const BatchEntry &e) { return e.form; };
     long long mu = 0, pu = 0, ru = 0;
     if (persistent) {
@@ -1750,6 +1776,8 @@ static hipError_t queue_batch_branches(ranc_net *lead, const Batch &b, hipStream
             const Batch::Group &g = b.groups[ph.g_first + c];
             for (int k = 0; e == hipSuccess && k < b.num_ticks; ++k)
                 e = launch_integrate_mfma_group(g.args, g.units, k, g.code, g.ext, g.compact, st);
+            for (int i = g.first; e == hipSuccess && i < g.first + g.num; ++i)
+                e = launch_fold_counts(b.mf[i].n, b.num_ticks, st);
         } else if (c < ph.g_num + (int)b.solo.size()) {
             const int i = b.solo[c - ph.g_num];
             if (queue_ticks(b.nets[i], b.bases[i], b.num_ticks, st, false) != RANC_OK)
@@ -1764,6 +1792,8 @@ static hipError_t queue_batch_branches(ranc_net *lead, const Batch &b, hipStream
                 if (e == hipSuccess)
                     e = launch_route_batch(tp, ph.pl_num, ph.rt_units, k, b.rt_lds, st);
             }
+            for (int i = ph.pl_first; e == hipSuccess && i < ph.pl_first + ph.pl_num; ++i)
+                e = launch_fold_counts(b.pl[i].n, b.num_ticks, st);
         }
     }
     for (int i = 0; e == hipSuccess && i < nb; ++i) {
@@ -1843,7 +1873,7 @@ static ranc_status queue_batch_ticks(ranc_net *lead, const Batch &b, hipStream_t
         }
     }
     hipError_t e = hipSuccess;
-    for (size_t i = 0; e == hipSuccess && i < b.nets.size(); ++i)
+    for (size_t i = 0; e == hipSuccess && !branches && i < b.nets.size(); ++i)
         if (!b.is_solo[i] && !b.nets[i]->p.size[R_RING8])   // (the others add to the totals themselves)
             e = launch_fold_counts(b.nets[i]->dn, b.num_ticks, s);
     if (e == hipSuccess && !b.mf.empty())
