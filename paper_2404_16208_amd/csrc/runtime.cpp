@@ -44,14 +44,15 @@ ranc_status hip_fail(hipError_t e, const char *what)
 
 enum Region {
     R_COLBITS, R_TYPEMASK, R_WTS, R_LEAK, R_THR, R_RST, R_VINIT, R_COREMASK, R_OUTMASK, R_OUTWORD,
-    R_ININDEX, R_RTDCNT, R_RTGOFF, R_RTENT, R_DEGB, R_OUTIDX, R_PLANES, R_RTXPTR, R_RTXENT, R_HZERO,
+    R_ININDEX, R_RTDCNT, R_RTGOFF, R_RTENT, R_DEGB, R_OUTIDX, R_RTXPTR, R_RTXENT, R_HZERO,
     R_FLOOR, R_LINMASK, R_ECSRPTR, R_ECSRENT, R_LINKREC, R_OUTCOL, R_OUTPOS, R_LINKPTR, R_LINKENT, R_PLAINDST, R_SCOLS, R_SPOS,
     R_PARAMS_END,  // everything before this is uploaded once at load
     R_V = R_PARAMS_END, R_RING, R_SPK, R_HIST, R_RASTER, R_CNT, R_CRING, R_TICK, R_BATCH, R_EXT, R_LINKD,
     R_RSYNC,
     // MFMA path: the compact B source, uploaded at load as well; kept past
-    // the state regions so that their placement does not depend on it
-    R_BSRC,
+    // the state regions so that their placement does not depend on it; and the
+    // int8 planes, built from it on the GPU
+    R_BSRC, R_PLANES,
     // feed-forward networks (MFMA and plain paths): cores by level, then each
     // core's level; uploaded at load
     R_ORDER,
@@ -845,30 +846,6 @@ void pack_params(const ranc_net_desc *d, const Plan &p, std::vector<uint8_t> &bu
         for (size_t i = 0; i < (size_t)C * N; ++i)
             oi[i] = d->dest_kind[i] == RANC_DEST_OUT ? next++ : -1;
     }
-    if (p.size[R_PLANES]) {
-        // B tiles: [C][N/32][A/32][planes][64 lanes][16 bytes]; lane l, byte b of
-        // k-step k covers axon 32k + 16(l/32) + b and neuron 32nb + l%32.
-        // Two planes: hi = w >> 7 (floor(w / 128)) first, then lo = w & 127.
-        int8_t *pl = (int8_t *)at(R_PLANES);
-        const int NB = N / 32, KS = A / 32, PL = p.two ? 2 : 1;
-        for (int c = 0; c < C; ++c)
-            for (int nb = 0; nb < NB; ++nb)
-                for (int k = 0; k < KS; ++k)
-                    for (int l = 0; l < 64; ++l)
-                        for (int b = 0; b < 16; ++b) {
-                            const int a = 32 * k + 16 * (l / 32) + b, j = 32 * nb + l % 32;
-                            const int w = conn(c, a, j) ? d->weight[((size_t)c * N + j) * G +
-                                                                    d->axon_type[(size_t)c * A + a]]
-                                                        : 0;
-                            const size_t base = ((((size_t)c * NB + nb) * KS + k) * PL) * 1024 + (size_t)l * 16 + b;
-                            if (PL == 2) {
-                                pl[base] = (int8_t)(w >> 7);
-                                pl[base + 1024] = (int8_t)(w & 127);
-                            } else {
-                                pl[base] = (int8_t)w;
-                            }
-                        }
-    }
 }
 
 }  // namespace
@@ -1529,7 +1506,7 @@ static ranc_status build_batch(ranc_net *const *nets, int num, const uint32_t *c
         std::vector<std::pair<size_t, int>> foot;
         for (int i = 0; i < num; ++i) {
             const Plan &p = nets[i]->p;
-            foot.push_back({p.params_bytes + p.size[R_BSRC] + p.size[R_V] + p.size[R_HIST] + p.size[R_RING] +
+            foot.push_back({p.params_bytes + p.size[R_PLANES] + p.size[R_BSRC] + p.size[R_V] + p.size[R_HIST] + p.size[R_RING] +
                                 p.size[R_SPK] + p.size[R_CNT],
                             i});
         }
@@ -2093,6 +2070,8 @@ ranc_status ranc_load_network(const ranc_net_desc *desc, int32_t num_samples, in
     if (e == hipSuccess && p.size[R_BSRC]) {
         pack_bsrc(desc, p, bsrc);
         e = hipMemcpyAsync(reg(R_BSRC), bsrc.data(), bsrc.size(), hipMemcpyHostToDevice, s);
+        if (e == hipSuccess && p.size[R_PLANES])
+            e = launch_build_planes(n, p.two, (uint4 *)reg(R_PLANES), s);
     }
     if (e == hipSuccess && p.levels) {
         e = hipMemcpyAsync(reg(R_ORDER), p.order.data(), (size_t)p.C * 4, hipMemcpyHostToDevice, s);
