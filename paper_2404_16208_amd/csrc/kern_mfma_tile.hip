@@ -13,9 +13,10 @@
 // order of their use, the potentials last, so that the wait for history words
 // does not wait for them.
 // us per tick at 64 samples, pipelined form and this: 1024 cores of 256 x 64 27.7,
-// 13.7 (at 5.2 TB/s the potentials take 6.5); of 128 x 128 (9 bits) 44.7, 21.5
-// (13.0); of 256 x 256 (8 bits) 47.6, 36.1 (26.0); of 512 x 512 (9 bits) 188, 113
-// (52.0); 16 cores of 256 x 256 10.5, 9.3.
+// 13.0 (at 5.2 TB/s the potentials take 6.5); of 128 x 128 (9 bits) 44.7, 20.5
+// (13.0); of 256 x 256 (8 bits) 47.6, 35.0 (26.0); of 512 x 512 (9 bits) 188, 97
+// (52.0); 16 cores of 256 x 256 10.5, 9.0. Potentials by ordinary loads and stores
+// instead of streaming ones: 133 to 166 us for 4096 cores of 256 x 256.
 #include "kern_common.h"
 #include "kern_bits.h"
 #include "kern_mfma_unit.h"
@@ -49,6 +50,7 @@ __device__ __forceinline__ void integrate_tile(const DevNet &n, const TickArgs &
 {
     typedef TileShape<A_, NB_, TWO> T;
     constexpr int KS = A_ / 32, W_ = A_ / 32, PL = TWO ? 2 : 1, STW = T::STW, TPW = T::TPW, WPW = T::WPW;
+    constexpr int DP = WPW < 2 ? WPW : 2;   // axon words whose connection counts are loaded ahead
     typedef typename RawWord<T::GPW == 2>::type RawT;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -118,6 +120,51 @@ __device__ __forceinline__ void integrate_tile(const DevNet &n, const TickArgs &
         if (e_beg[k] < e_end[k])
             raw[k] = word_of(ent[k], grp[k]);
     }
+    // What the products need first, ahead of the barriers: the B tiles of two
+    // k-steps, or all column words, the plane values and the types of two k-steps
+    // (with four, no faster); and the connection counts. 1024 cores of 512 x 512
+    // (9 bits) 110.6 us per tick without, 97.4 with; the sweep of eight networks
+    // 1037 and 993 us.
+    constexpr int KP = STW == 2 ? (CB ? 1 : 2) : KS < 2 ? KS : 2;
+    const uint32_t *colw = n.colbits + (size_t)c * W_ * n.N + jc;
+    const uint4 *ts = reinterpret_cast<const uint4 *>(mfma_bsrc_types(n, PL) + (size_t)c * A_) + h;
+    const v4i *planes = reinterpret_cast<const v4i *>(n.planes) + ((size_t)c * n.NW + nbc) * KS * PL * 64 + lane;
+    v4i bpre[KP][PL];
+    uint32_t bits[KS], wl[PL], wh[PL];
+    uint4 types[KP];
+    if constexpr (CB) {
+        const uint32_t *wsel = mfma_bsrc_wsel(n) + (size_t)c * PL * 2 * n.N + jc;
+#pragma unroll
+        for (int p = 0; p < PL; ++p) {
+            wl[p] = wsel[(size_t)(2 * p) * n.N];
+            wh[p] = wsel[(size_t)(2 * p + 1) * n.N];
+        }
+#pragma unroll
+        for (int k = 0; k < KS; ++k)
+            bits[k] = colw[(size_t)k * n.N];
+#pragma unroll
+        for (int k = 0; k < KP; ++k)
+            types[k] = ts[2 * k];
+    } else {
+#pragma unroll
+        for (int k = 0; k < KP; ++k)
+#pragma unroll
+            for (int p = 0; p < PL; ++p)
+                bpre[k][p] = planes[(k * PL + p) * 64];
+    }
+    const size_t dg = (size_t)c * n.slices + slice;
+    uint32_t degl[DP][8], degh[DP][8];
+#pragma unroll
+    for (int k = 0; k < DP; ++k) {
+        const int wi = min(wave + T::WAVES * k, W_ - 1);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            degl[k][q] = n.degb[(dg * 2 + 0) * (A_ / 4) + wi * 8 + q];
+            degh[k][q] = n.degb[(dg * 2 + 1) * (A_ / 4) + wi * 8 + q];
+        }
+    }
+    const uint32_t cm32 = n.coremask[(size_t)c * n.NW + nbc];
+    const uint32_t om32 = n.outmask[(size_t)c * n.NW + nbc];
     compiler_fence();
     v4i *vb = reinterpret_cast<v4i *>(n.V) + (((size_t)c * n.NW + nbc) * (n.S64 / 32) + 2 * tile + stg * STW) * 256 + lane;
     v4i vr[STW][4];
@@ -147,7 +194,6 @@ __device__ __forceinline__ void integrate_tile(const DevNet &n, const TickArgs &
     // expansion, one lane per sample: delivered | external spikes of this
     // wave's axon words to int8, delivered and event counts
     {
-        const size_t dg = (size_t)c * n.slices + slice;
         unsigned pdl = 0u, pev = 0u, pevh = 0u;
 #pragma unroll
         for (int k = 0; k < WPW; ++k) {
@@ -156,21 +202,22 @@ __device__ __forceinline__ void integrate_tile(const DevNet &n, const TickArgs &
                 const uint32_t xd = lds.x[lane][wi];
                 const uint32_t x = xd | xe[k];
                 pdl += (unsigned)__popc(xd);
-                const uint32_t *degl = n.degb + (dg * 2 + 0) * (A_ / 4) + wi * 8;
-                const uint32_t *degh = n.degb + (dg * 2 + 1) * (A_ / 4) + wi * 8;
-                uint32_t d[8], any_hi = 0;
+                uint32_t dl[8], dh[8], d[8], any_hi = 0;
 #pragma unroll
-                for (int q = 0; q < 8; ++q)
-                    any_hi |= degh[q];
+                for (int q = 0; q < 8; ++q) {
+                    dl[q] = k < DP ? degl[k < DP ? k : 0][q] : n.degb[(dg * 2 + 0) * (A_ / 4) + wi * 8 + q];
+                    dh[q] = k < DP ? degh[k < DP ? k : 0][q] : n.degb[(dg * 2 + 1) * (A_ / 4) + wi * 8 + q];
+                    any_hi |= dh[q];
+                }
 #pragma unroll
                 for (int q = 0; q < 8; ++q) {
                     d[q] = (((x >> (4 * q)) & 0xFu) * 0x00204081u) & 0x01010101u;
-                    pev = __builtin_amdgcn_udot4(d[q], degl[q], pev, false);
+                    pev = __builtin_amdgcn_udot4(d[q], dl[q], pev, false);
                 }
                 if (any_hi) {   // uniform: a core of 256 connected neurons on an axon
 #pragma unroll
                     for (int q = 0; q < 8; ++q)
-                        pevh = __builtin_amdgcn_udot4(d[q], degh[q], pevh, false);
+                        pevh = __builtin_amdgcn_udot4(d[q], dh[q], pevh, false);
                 }
                 v4i *dst = reinterpret_cast<v4i *>(&lds.a[lane * T::ROWB + 32 * wi]);
                 dst[0] = v4i{(int)d[0], (int)d[1], (int)d[2], (int)d[3]};
@@ -201,39 +248,19 @@ __device__ __forceinline__ void integrate_tile(const DevNet &n, const TickArgs &
             lo[t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b[PL - 1], lo[t], 0, 0, 0);
         }
     };
-    if constexpr (CB) {
-        // (see integrate_mfma_unit)
-        const uint32_t *colw = n.colbits + (size_t)c * W_ * n.N + jc;
-        const uint32_t *wsel = mfma_bsrc_wsel(n) + (size_t)c * PL * 2 * n.N + jc;
-        const uint4 *ts = reinterpret_cast<const uint4 *>(mfma_bsrc_types(n, PL) + (size_t)c * A_) + h;
-        uint32_t wl[PL], wh[PL];
 #pragma unroll
-        for (int p = 0; p < PL; ++p) {
-            wl[p] = wsel[(size_t)(2 * p) * n.N];
-            wh[p] = wsel[(size_t)(2 * p + 1) * n.N];
-        }
-#pragma unroll
-        for (int k = 0; k < KS; ++k) {
-            const uint32_t bits = colw[(size_t)k * n.N] >> (16 * h);
-            const uint4 t4 = ts[2 * k];
-            v4i b[PL];
-            compact_b_tile(bits, t4, wl, wh, b);
-            multiply(k, b);
-        }
-    } else {
-        const v4i *planes = reinterpret_cast<const v4i *>(n.planes) + ((size_t)c * n.NW + nbc) * KS * PL * 64 + lane;
-#pragma unroll
-        for (int k = 0; k < KS; ++k) {
-            v4i b[PL];
+    for (int k = 0; k < KS; ++k) {
+        v4i b[PL];
+        if constexpr (CB) {
+            compact_b_tile(bits[k] >> (16 * h), k < KP ? types[k < KP ? k : 0] : ts[2 * k], wl, wh, b);
+        } else {
 #pragma unroll
             for (int p = 0; p < PL; ++p)
-                b[p] = planes[(k * PL + p) * 64];
-            multiply(k, b);
+                b[p] = k < KP ? bpre[k < KP ? k : 0][p] : planes[(k * PL + p) * 64];
         }
+        multiply(k, b);
     }
 
-    const uint32_t cm32 = n.coremask[(size_t)c * n.NW + nbc];
-    const uint32_t om32 = n.outmask[(size_t)c * n.NW + nbc];
     const int32_t vmin = n.vmin, vmax = n.vmax;
     uint32_t hword[STW];
 #pragma unroll
