@@ -167,12 +167,14 @@ __device__ __forceinline__ void integrate_tile(const DevNet &n, const TickArgs &
     const uint32_t om32 = n.outmask[(size_t)c * n.NW + nbc];
     compiler_fence();
     v4i *vb = reinterpret_cast<v4i *>(n.V) + (((size_t)c * n.NW + nbc) * (n.S64 / 32) + 2 * tile + stg * STW) * 256 + lane;
+    // (a group past the last sample has nothing to read or keep: it loads the tile's first)
+    auto group_of = [&](int t) { return s0 + 32 * (stg * STW + t) < s_end ? t : -stg * STW; };
     v4i vr[STW][4];
 #pragma unroll
     for (int t = 0; t < STW; ++t)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            vr[t][q] = __builtin_nontemporal_load(vb + (t * 4 + q) * 64);
+            vr[t][q] = __builtin_nontemporal_load(vb + (group_of(t) * 4 + q) * 64);
     compiler_fence();
     // Lane (h, j) holds, for axon 64 axb + 32 h + j, the bits of a 32-sample
     // group; after the transpose lane (h, i) holds the axon word 2 axb + h of
@@ -261,7 +263,7 @@ __device__ __forceinline__ void integrate_tile(const DevNet &n, const TickArgs &
         multiply(k, b);
     }
 
-    const int32_t vmin = n.vmin, vmax = n.vmax;
+    const NeuronParams np{th, rs, fl, n.vmin, n.vmax, lin};
     uint32_t hword[STW];
 #pragma unroll
     for (int t = 0; t < STW; ++t) {
@@ -269,25 +271,16 @@ __device__ __forceinline__ void integrate_tile(const DevNet &n, const TickArgs &
         uint32_t f = 0;
 #pragma unroll
         for (int q = 3; q >= 0; --q) {
-            int32_t u[4];
+            int32_t in[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                u[e] = __builtin_elementwise_add_sat(vr[t][q][e], TWO ? lo[t][4 * q + e] + hi[t][4 * q + e] * 128 : lo[t][4 * q + e]);
-            if (n.model_ext) {   // uniform
-                int32_t w[4], r[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    u[e] = min(max(u[e], vmin), vmax);
-                    w[e] = max(u[e], fl);
-                    r[e] = lif_reset(u[e], th, rs, vmax, lin);
-                }
-                fire_rows(f, w[0], w[1], w[2], w[3], u[0], u[1], u[2], u[3], r[0], r[1], r[2], r[3], th);
-                vr[t][q] = v4i{w[0], w[1], w[2], w[3]};
-            } else {
-                fire_rows(f, u[0], u[1], u[2], u[3], rs, th);
-                vr[t][q] = v4i{u[0], u[1], u[2], u[3]};
-            }
-            __builtin_nontemporal_store(vr[t][q], vb + (t * 4 + q) * 64);
+                in[e] = TWO ? lo[t][4 * q + e] + hi[t][4 * q + e] * 128 : lo[t][4 * q + e];
+            if (n.model_ext)   // uniform
+                update_rows<true>(vr[t][q], in, np, f);
+            else
+                update_rows<false>(vr[t][q], in, np, f);
+            if (first < s_end)
+                __builtin_nontemporal_store(vr[t][q], vb + (t * 4 + q) * 64);
         }
         // samples past the end never fire (their potentials are never read)
         if (first + 32 > s_end) {   // wave-uniform
