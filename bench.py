@@ -37,9 +37,11 @@ TRAFFIC_FILE_MESH = os.path.join(ROOT, "profiles", "traffic_integrate_mesh16384_
 # summary under profiles/ is used only while these hash to the value it
 # records.
 _CSRC = "paper_2404_16208_amd/csrc/"
-KERNEL_SOURCES_MFMA = [_CSRC + f for f in ("kern_mfma.hip", "kern_mfma_unit.h", "kern_mfma_cb.hip", "kern_common.h",
-                                              "kern_bits.h", "ranc_internal.h")]
-KERNEL_SOURCES_MESH = KERNEL_SOURCES_MFMA + [_CSRC + "kern_sparse.hip"]
+KERNEL_SOURCES_MFMA = [_CSRC + f for f in ("kern_mfma_ticks.hip", "kern_mfma_unit.h", "kern_common.h", "kern_bits.h",
+                                              "ranc_internal.h")]
+KERNEL_SOURCES_MESH = [_CSRC + f for f in ("kern_mfma_tile.hip", "kern_mfma_unit.h", "kern_common.h", "kern_bits.h",
+                                              "ranc_internal.h", "kern_sparse.hip")]
+BLOCK_TICKS = 32   # ticks that a launch of the several-tick kernel runs at most
 
 
 def kernel_source_hash(files=KERNEL_SOURCES_MFMA) -> str:
@@ -90,8 +92,19 @@ def resident_algorithmic_bytes(net, S: int, T: int) -> dict:
     return dict(total=total, potentials=S * C * 8 * N, per_tick=per_tick_state, params=tick["params"])
 
 
+def blocks_algorithmic_bytes(net, S: int, T: int) -> dict:
+    """Bytes that one call of T ticks must move at minimum where a
+    feed-forward network runs blocks of at most BLOCK_TICKS ticks per launch:
+    per block the potentials and the parameters once; per tick the axon and
+    output spike bits, external input bits and raster words."""
+    r = resident_algorithmic_bytes(net, S, T)
+    blocks = -(-T // BLOCK_TICKS)
+    total = blocks * (r["potentials"] + r["params"]) + T * r["per_tick"]
+    return dict(r, total=total, blocks=blocks)
+
+
 def mfma_ops_per_launch(net, S: int) -> int:
-    """int8 multiply-adds the MFMA path executes per launch, counted as 2 ops
+    """int8 multiply-adds the MFMA path executes per tick, counted as 2 ops
     each: every 64-sample tile of every core multiplies [64 x A] by [A x N]
     once per weight plane (samples padded to a multiple of 64)."""
     planes = 2 if net.weight_bits > 8 else 1
@@ -99,8 +112,8 @@ def mfma_ops_per_launch(net, S: int) -> int:
     return 2 * planes * S64 * net.num_cores * net.num_axons * net.num_neurons
 
 
-def read_traffic(src_hash: str, path: str = TRAFFIC_FILE, key: str = "hbm_bytes_per_launch"):
-    """HBM traffic per integration launch from a committed rocprofv3 PMC
+def read_traffic(src_hash: str, path: str = TRAFFIC_FILE, key: str = "hbm_bytes_per_call"):
+    """HBM traffic of a path's kernels (per call or tick, as `key` says) from a committed rocprofv3 PMC
     summary, or None if it is absent or was taken on other kernel sources."""
     if not os.path.exists(path):
         return None
@@ -510,7 +523,7 @@ def main():
                          "streamed for 10010 ticks from host memory, end to end")
     ap.add_argument("--path", default="auto", choices=["auto", "plain", "mfma", "sparse"],
                     help="integration path of the table1 and stream runs (default auto: the plain path for "
-                         "one instance, with the lane-split router the fastest on every Table I shape)")
+                         "one instance, the fastest on every Table I shape)")
     ap.add_argument("--apps", default="",
                     help="table1 only: comma-separated application names to run (default: all)")
     ap.add_argument("--calib-copy-mib", type=int, default=0,
@@ -571,19 +584,16 @@ def main():
     secs = ms / 1e3
     events_per_s = delta["events"] / secs
     core_ticks = S * C * T * args.steps
-    ib = integrate_algorithmic_bytes(net, S, "mfma")
-    if graph:
-        # graph launches hold T integration launches and one tick-advance
-        # launch each: the per-tick share bounds the kernel's duration from above
-        avg_int_ms = prof["graph_ms"] / max(1, prof["graph_launches"] * T)
-        launches = prof["graph_launches"] * T
-    else:
-        avg_int_ms = prof["integrate_ms"] / max(1, prof["integrate_launches"])
-        launches = prof["integrate_launches"]
+    ib = blocks_algorithmic_bytes(net, S, T)
+    # the per-tick share of a call's kernels; a graph launch also holds the
+    # tick-advance launch, so it bounds them from above
+    call_ms = prof["graph_ms"] / max(1, prof["graph_launches"]) if graph else prof["integrate_ms"] / args.steps
+    avg_int_ms = call_ms / T
     avg_route_ms = prof["route_ms"] / max(1, prof["route_launches"])
-    achieved = ib["total"] / (avg_int_ms / 1e3) / 1e9
+    achieved = ib["total"] / (call_ms / 1e3) / 1e9
     eprof = kernel_profile(g, xd, T, max(2, min(args.steps, 10)), torch)
-    eager_int_ms = eprof["integrate_ms"] / max(1, eprof["integrate_launches"])
+    ecalls = max(2, min(args.steps, 10))
+    eager_int_ms = eprof["integrate_ms"] / (ecalls * T)
     src_hash = kernel_source_hash()
     traffic = read_traffic(src_hash)
     out = {
@@ -609,26 +619,27 @@ def main():
         "spikes_emitted_per_step": delta["emitted"] / args.steps,
         "tick_loop": "hip graph replay" if graph else "per-tick launches",
         "kernels": {"integrate_mfma_avg_ms": avg_int_ms, "route_avg_ms": avg_route_ms,
-                    "launches_timed": launches,
+                    "calls_timed": args.steps,
+                    "launches_per_call": eprof["integrate_launches"] / ecalls,
                     "timing": ("graph launch time / ticks, HIP events on the launch stream over the timed steps"
-                               if graph else "HIP events around each launch over the timed steps"),
+                               if graph else "HIP events around each launch over the timed steps, per tick"),
                     "integrate_mfma_eager_avg_ms": eager_int_ms,
                     "eager_launches_profiled": eprof["integrate_launches"]},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
-                     "traffic": (traffic / (avg_int_ms / 1e3) / 1e9) if traffic else None,
-                     "kernel": "k_integrate_mfma<256,256,two planes>",
-                     "algorithmic_bytes_per_launch": ib["total"],
-                     "bytes_per_unit": ib["per_unit"], "units_per_launch": ib["units"],
-                     "params_bytes_per_launch": ib["params"],
-                     "b_source_bytes_per_launch": ib["b_source"],
+                     "traffic": (traffic / (call_ms / 1e3) / 1e9) if traffic else None,
+                     "kernel": "k_integrate_mfma_ticks<256,256,two planes>",
+                     "algorithmic_bytes_per_call": ib["total"], "potentials_bytes_per_block": ib["potentials"],
+                     "blocks_per_call": ib["blocks"], "params_bytes_per_block": ib["params"],
+                     "note": "bound by instruction issue (products and the per-sample update), see mfma; the "
+                             "potentials move once per block of ticks",
                      "kernel_source_sha256_16": src_hash},
-        "mfma": {"bound": "mfma", "executed_int8_ops_per_launch": mfma_ops_per_launch(net, S),
+        "mfma": {"bound": "mfma", "executed_int8_ops_per_tick": mfma_ops_per_launch(net, S),
                  "achieved": mfma_ops_per_launch(net, S) / (avg_int_ms / 1e3) / 1e12,
                  "peak": INT8_MFMA_PEAK_TOPS, "unit": "TOPS",
                  "util": mfma_ops_per_launch(net, S) / (avg_int_ms / 1e3) / 1e12 / INT8_MFMA_PEAK_TOPS,
-                 "useful_ops_per_launch": 2 * delta["events"] / max(1, args.steps * T),
-                 "note": "executed int8 ops (both weight planes, padded tiles) per average launch duration; "
+                 "useful_ops_per_tick": 2 * delta["events"] / max(1, args.steps * T),
+                 "note": "executed int8 ops (both weight planes, padded tiles) per tick's share of the call; "
                          "useful ops = 2 x synaptic events"},
     }
     g.close()
