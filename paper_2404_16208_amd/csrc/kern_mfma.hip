@@ -170,15 +170,14 @@ hipError_t launch_integrate_mfma_group(const MfmaGroupArgs &g, int total, int k,
                    : launch_group_code<false>(g, total, k, code, ext, st);
 }
 
-// B source of a launch by default. The compact crossbar when one workgroup covers all
-// samples of a core (it alone reads the core's B tiles in the tick) and the
-// planes it replaces are large (A x planes >= 256 bytes per neuron, cores of
-// >= 256 neurons) and the launch has a workgroup per CU or more; otherwise
-// the int8 planes. With one 64-sample tile per workgroup the expansion's
-// VALU work is latency nothing hides: measured per network of the 64-variant
-// sweep, 512-neuron cores with 512 axons run 8-24% faster, while 64- and
-// 128-neuron cores and networks of fewer workgroups than CUs run 2-20%
-// slower with the compact source.
+// B source of a launch by default. Pipelined form: the compact crossbar when one
+// workgroup covers all samples of a core (it alone reads the core's B tiles in
+// the tick) and the planes it replaces are large (A x planes >= 256 bytes per
+// neuron, cores of >= 256 neurons) and the launch has a workgroup per CU or
+// more; otherwise the int8 planes (the expansion comes before the first product;
+// measured per network with 64 samples, 512-neuron cores with 512 axons ran 8-24%
+// faster, 64- and 128-neuron cores and networks of fewer workgroups than CUs
+// 2-20% slower).
 // One-tile workgroups (kern_mfma_tile.hip) use the B tiles as they are built, and
 // take the compact source wherever there is a workgroup per CU, the two smallest
 // shapes apart. us per tick with planes and compact, 64 samples: 1024 cores of

@@ -1,10 +1,10 @@
-// kern_mfma_cb.hip -- the MFMA path's kernels (kern_mfma_unit.h) with the
-// B tiles built in registers from the compact crossbar (column words,
+// kern_mfma_cb.hip -- the MFMA path's pipelined kernels (kern_mfma_unit.h) with
+// the B tiles built in registers from the compact crossbar (column words,
 // per-type plane bytes, axon types) instead of read as int8 weight planes:
 // used when one workgroup covers all samples of a core, so that the core's
-// B source is read once per tick (a sweep of 64-sample networks: the planes
-// were a third of the tick's bytes). Kept in a translation unit of its own,
-// apart from the plane form (kern_mfma.hip).
+// B source is read once per tick; and the kernel that builds the planes at load.
+// Kept in a translation unit of its own, apart from the plane form
+// (kern_mfma.hip).
 #include <algorithm>
 
 #include "kern_mfma_unit.h"

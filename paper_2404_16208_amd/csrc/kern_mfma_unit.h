@@ -660,8 +660,7 @@ __device__ __forceinline__ void integrate_mfma_unit(const DevNet &n, const TickA
 // 8-wavefront workgroups per CU): the compiler meets it for the 128-neuron
 // slices with at most 128 axons (a few spilled VGPRs), whose LDS also fits
 // twice per CU, and keeps the larger shapes as they are (one workgroup per
-// CU). On the 64-variant sweep at 64 samples (one tile per workgroup, so no
-// pipelining across tiles) the overlap of two workgroups gains 1.6%.
+// CU). Workgroups of one tile have a form of their own (kern_mfma_tile.hip).
 template <int A_, int N_, bool TWO, bool EXT, bool CB>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_integrate_mfma(DevNet n, TickArgs ta,
                                                                                                int spw)
