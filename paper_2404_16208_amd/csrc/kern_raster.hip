@@ -100,7 +100,8 @@ __global__ __launch_bounds__(256) void k_raster_plain_by_neuron(DevNet n, const 
 // mod 8) a contiguous range, so that the lines are fetched into one L2.
 // 32 ticks of 32768 output neurons: 1024 samples (134 MB read and written) 617
 // us with 32-byte runs and one broadcast load per neuron, 94 now (2.9 TB/s); 100
-// samples 46, 8.4. Few units: 16 ticks, 64 samples, 7 us, 4.7.
+// samples 46, 8.4. Few units: 16 ticks, 64 samples, 7 us, 4.7. Streaming stores
+// (ordinary ones 73 us when repeated on one raster, 69; 8.3, 7.3).
 template <int WAVES_, int TILES_>
 __global__ __launch_bounds__(64 * WAVES_) void k_raster_hist_by_sample(DevNet n, long long t0, int total, uint32_t *dst)
 {
@@ -143,7 +144,7 @@ __global__ __launch_bounds__(64 * WAVES_) void k_raster_hist_by_sample(DevNet n,
     for (int k = threadIdx.x / OWS; k < 64 * TILES_; k += 64 * WAVES_ / OWS) {
         const int s = 64 * tile0 + k;
         if (s < n.S && g < words)
-            dst[((size_t)t * n.S + s) * NOW + OWS * ob + g] = sw[k][g];
+            __builtin_nontemporal_store(sw[k][g], dst + (((size_t)t * n.S + s) * NOW + OWS * ob + g));
     }
 }
 
