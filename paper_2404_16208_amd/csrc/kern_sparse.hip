@@ -48,6 +48,8 @@
 // loads and scatters overlap (6% faster on the 16384-core mesh than loading
 // them in step 0 with three workgroups per CU). Barriers order LDS only
 // (lds_barrier), so no wave waits for the potential loads of the others.
+#include <type_traits>
+
 #include "kern_bits.h"
 #include "kern_common.h"
 #include "ranc_internal.h"
@@ -162,7 +164,11 @@ __device__ __forceinline__ void scatter_word(uint32_t bits, int word, int s, con
 // most lanes would idle and one lane would walk every row entry of its
 // sample, so instead the wavefront takes the samples in turn and its 64 lanes
 // take 64 entries of a spiking axon's row at a time.
-template <int A_, int NS_, bool EXT, bool SMALL>
+// MASK: at most 32 samples, so half of the tile's potentials or more would move
+// unread: only the valid samples' do (4096 cores of 256 x 256, 20 samples, 132.8 us per
+// tick, masked 123.8; with 40 and 64, where whole lines are in use, the masks cost:
+// 137.2, 142.1 and 143.4, 147.0).
+template <int A_, int NS_, bool EXT, bool SMALL, bool MASK>
 __global__ __launch_bounds__(64 * EV_WAVES) __attribute__((amdgpu_waves_per_eu(8)))
 void k_integrate_event(DevNet n, TickArgs ta)
 {
@@ -310,11 +316,10 @@ void k_integrate_event(DevNet n, TickArgs ta)
     // ---- 2. update, one neuron of the wave at a time for all 64 samples
     int32_t vreg[NPW];
     const int32_t *vin = n.V + ((size_t)c * n.N + j0) * n.S64 + s;
-    // (small batches: only the valid samples' potentials move; the padding
-    // lanes of the tile are never read)
+    // (the padding lanes of the tile are never read)
 #pragma unroll
     for (int k = 0; k < NPW; ++k)
-        vreg[k] = (!SMALL || svalid) ? __builtin_nontemporal_load(vin + (size_t)k * n.S64) : 0;
+        vreg[k] = (!MASK || svalid) ? __builtin_nontemporal_load(vin + (size_t)k * n.S64) : 0;
     uint32_t fm = 0;       // bit k: this lane's sample fired on neuron j0 + k
     uint64_t myword = 0;   // lane k < NPW: the history word of neuron j0 + k
     int32_t *vout = n.V + ((size_t)c * n.N + j0) * n.S64 + s;
@@ -337,7 +342,7 @@ void k_integrate_event(DevNet n, TickArgs ta)
             vn = fire ? rs : u;
         }
         fire = fire && svalid;
-        if (!SMALL || svalid)
+        if (!MASK || svalid)
             __builtin_nontemporal_store(vn, vout + (size_t)k * n.S64);
         const uint64_t word = __ballot(fire);
         myword = lane == k ? word : myword;
@@ -368,15 +373,18 @@ static void launch_event_k(const DevNet &n, const TickArgs &a, hipStream_t st)
     hipLaunchKernelGGL((k_deliver_event<A_>), dim3((unsigned)((dv_waves + DV_WAVES - 1) / DV_WAVES)),
                        dim3(64 * DV_WAVES), 0, st, n, a);
     const dim3 grid(n.C * n.slices * (n.S64 / EV_TS)), block(64 * EV_WAVES);
-    const bool small = n.S <= EV_SMALL_S;
-    if (n.model_ext && small)
-        hipLaunchKernelGGL((k_integrate_event<A_, NS_, true, true>), grid, block, 0, st, n, a);
-    else if (n.model_ext)
-        hipLaunchKernelGGL((k_integrate_event<A_, NS_, true, false>), grid, block, 0, st, n, a);
-    else if (small)
-        hipLaunchKernelGGL((k_integrate_event<A_, NS_, false, true>), grid, block, 0, st, n, a);
+    auto launch = [&](auto small, auto mask) {
+        if (n.model_ext)
+            hipLaunchKernelGGL((k_integrate_event<A_, NS_, true, decltype(small)::value, decltype(mask)::value>), grid, block, 0, st, n, a);
+        else
+            hipLaunchKernelGGL((k_integrate_event<A_, NS_, false, decltype(small)::value, decltype(mask)::value>), grid, block, 0, st, n, a);
+    };
+    if (n.S <= EV_SMALL_S)
+        launch(std::true_type(), std::true_type());
+    else if (n.S <= EV_TS / 2)
+        launch(std::false_type(), std::true_type());
     else
-        hipLaunchKernelGGL((k_integrate_event<A_, NS_, false, false>), grid, block, 0, st, n, a);
+        launch(std::false_type(), std::false_type());
 }
 
 template <int A_>

@@ -48,3 +48,24 @@ def test_one_tile_shapes(A, bsrc, S, monkeypatch):
         for s, r in ref.items():
             assert_sample_equal(g, r, s, 2 * T, what=g.net.name)
         g.close()
+
+
+@pytest.mark.parametrize("S", [8, 9, 31, 32, 33])
+def test_event_driven_partial_tiles(S):
+    """The event-driven path's potentials of valid samples only (up to 32 samples)
+    and of whole tiles, both potential updates."""
+    import torch
+    from paper_2404_16208_amd.ranc import RancNet
+    T = 6
+    for i, kw in enumerate((dict(), dict(potential_bits=13))):
+        net = W.random_net(540 + i, 6, 128, 256 if i else 64, 4, grid_w=3, density=0.3, p_core=0.8, p_out=0.15,
+                           max_delay=3, input_cores=[0, 3], config_id=881, **kw)
+        x = W.bernoulli_inputs(3, net, S, T, 0.25, config_id=881)
+        ref = oracle_results(net, x, T, range(S))
+        g = RancNet(net, S, T, path="sparse", workspace_fill=0xA5)
+        xd = torch.from_numpy(x.view(np.int32)).cuda()
+        g.run(xd[:, :2].contiguous(), 2)
+        g.run(xd[:, 2:].contiguous(), T - 2)
+        for s in range(S):
+            assert_sample_equal(g, ref[s], s, T, what=f"event S{S}")
+        g.close()
