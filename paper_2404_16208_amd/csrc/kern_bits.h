@@ -126,4 +126,12 @@ __device__ __forceinline__ void fire_rows(uint32_t &f, int32_t &v0, int32_t &v1,
         : "vcc");
 }
 
+// fire_rows' spike bits before a lane swap takes them as they are: the swap needs
+// two wait states after a vector instruction wrote its register, and the compiler
+// keeps them only after instructions of its own.
+__device__ __forceinline__ void rows_settled(uint32_t &f)
+{
+    asm volatile("s_nop 1" : "+v"(f));
+}
+
 }  // namespace ranc

@@ -437,6 +437,7 @@ __global__ __launch_bounds__((64 * TicksShape<A_, N_>::WAVES), (A_ == 512 && N_ 
         // lane (h, j), two blocks: fire bits of samples 4h' of neuron j of
         // block h, h' = 0 in the low half, 1 in the high; one block: its word
         // in both lane halves
+        rows_settled(hb[NPB - 1]);
         const auto sw = __builtin_amdgcn_permlane32_swap(hb[0], hb[NPB - 1], false, false);
         const uint32_t word = ((uint32_t)sw[0] | ((uint32_t)sw[1] << 16)) & vmask;
         word_lds[i][threadIdx.x] = word;
