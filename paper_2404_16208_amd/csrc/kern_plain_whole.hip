@@ -27,6 +27,8 @@ namespace ranc {
 
 static constexpr int WH_THREADS = 1024, WH_WAVES = WH_THREADS / 64;
 static constexpr int WH_TASKS = 8;          // 64-axon tasks per wavefront, at most
+static_assert(64ull * 512 * PLAIN_WHOLE_TICKS_MAX < 1ull << 32 &&
+                  64ull * WH_TASKS * WH_WAVES * PLAIN_WHOLE_TICKS_MAX < 1ull << 32, "a launch's counts overflow");
 
 // LDS (dynamic), in bytes: D + 1 scheduler slots, each the bytes of all axons,
 // 64 bytes that stay zero (read for padding positions) and 64 that are never
@@ -291,7 +293,7 @@ static hipError_t launch_whole_k(const DevNet &n, const BlockArgs &a, hipStream_
 hipError_t launch_plain_whole(const DevNet &n, const BlockArgs &a, hipStream_t st)
 {
     if (n.vlayout != VLAYOUT_CSN || n.cnt_rows != n.N / 64 || n.S > 65535 || n.Q < n.D + 2 || !a.ring8 || !a.dst ||
-        !a.cols || !a.pos || !plain_whole_supported(n.C, n.A, n.N, n.G, n.D, n.Cin, a.sorted_words) || a.ticks < 1 || a.k0 < 0 ||
+        !a.cols || !a.pos || !plain_whole_supported(n.C, n.A, n.N, n.G, n.D, n.Cin, a.sorted_words) || a.ticks < 1 || a.ticks > PLAIN_WHOLE_TICKS_MAX || a.k0 < 0 ||
         a.k0 + a.ticks > n.RT)
         return hipErrorInvalidValue;
     switch (n.G * 32 + a.sorted_words) {

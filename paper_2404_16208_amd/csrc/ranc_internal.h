@@ -164,6 +164,9 @@ struct BlockArgs {
 };
 constexpr int MFMA_BLOCK_TICKS_MAX = 32;
 constexpr int PLAIN_WHOLE_NEURONS = 4096;
+// k_plain_whole counts a launch's events in 32 bits per 64-neuron block (at most
+// 64 * 512 a tick) and its delivered spikes per sample (at most 8192 a tick).
+constexpr int PLAIN_WHOLE_TICKS_MAX = 1 << 16;
 constexpr uint32_t PLAIN_NO_DEST = 0xFFFFFFFFu;
 
 // Grid synchronization words of the state-resident loop: arrival counter and
@@ -290,7 +293,7 @@ hipError_t launch_integrate_plain(const DevNet &n, const TickArgs &a, hipStream_
 // integration and delivery of one tick, or of a block of a feed-forward network
 hipError_t launch_plain_ticks(const DevNet &n, const BlockArgs &a, hipStream_t st);
 int plain_sorted_words(int G, int longest);   // `longest`: axons of one type in a core, at most
-// all ticks of a call for a network that fits one CU (a.ticks from a.k0)
+// up to PLAIN_WHOLE_TICKS_MAX ticks of a call for a network that fits one CU (a.ticks from a.k0)
 hipError_t launch_plain_whole(const DevNet &n, const BlockArgs &a, hipStream_t st);
 bool plain_whole_supported(int C, int A, int N, int G, int D, int Cin, int sorted_words);
 // scheduled deliveries from the bit ring to the byte ring, or back

@@ -1153,16 +1153,18 @@ static hipError_t queue_several(ranc_net *net, const uint32_t *base, int num_tic
         BlockArgs a;
         memset(&a, 0, sizeof a);
         set_plain_args(net, a);
-        a.ticks = num_ticks;
         a.ext_base = base;
         a.tick_words = (long long)p.Cin * p.W;
         a.ext_sstride = (long long)num_ticks * a.tick_words;
-        int slot = -1;
-        e = timed ? prof_begin(net, 0, s, &slot) : hipSuccess;
-        if (e == hipSuccess)
-            e = launch_plain_whole(net->dn, a, s);
-        if (e == hipSuccess && timed)
-            e = prof_end(net, slot, s);
+        for (; e == hipSuccess && a.k0 < num_ticks; a.k0 += a.ticks) {
+            a.ticks = std::min(num_ticks - a.k0, PLAIN_WHOLE_TICKS_MAX);
+            int slot = -1;
+            e = timed ? prof_begin(net, 0, s, &slot) : hipSuccess;
+            if (e == hipSuccess)
+                e = launch_plain_whole(net->dn, a, s);
+            if (e == hipSuccess && timed)
+                e = prof_end(net, slot, s);
+        }
         return e;
     }
     for (int k = 0; e == hipSuccess && k < num_ticks; k += p.seg_ticks) {
