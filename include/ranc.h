@@ -373,7 +373,9 @@ typedef struct ranc_tune {
  * samples per workgroup; plain: router samples per block x split x LDS
  * staging) on num_ticks ticks of `inputs` (as for ranc_run_ticks; flags may
  * hold RANC_INPUTS_ON_DEVICE), each from the initial state after one untimed
- * pass, and keep the fastest. Results never depend on the shape. Leaves every
+ * pass, and keep the fastest. MFMA candidates run tick by tick, which is what
+ * the shape applies to (a feed-forward network's launches of several ticks have
+ * none). Results never depend on the shape. Leaves every
  * instance in its initial state (as ranc_reset_state) and drops captured
  * tick loops. Synchronizes `stream`; *out receives the chosen shape.
  */

@@ -1207,15 +1207,17 @@ static hipError_t queue_plain_tick(ranc_net *net, const uint32_t *base, int num_
 
 // Queue num_ticks ticks on stream s: per tick the integration (and on the
 // plain path the router), then the device tick advance. With `timed`, HIP
-// event pairs are recorded around each launch while profiling is on.
-static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_ticks, hipStream_t s, bool timed)
+// event pairs are recorded around each launch while profiling is on. one_tick:
+// tick by tick even where several ticks would take one launch.
+static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_ticks, hipStream_t s, bool timed,
+                               bool one_tick = false)
 {
     const Plan &p = net->p;
     const size_t tick_words = (size_t)p.Cin * p.W;
     timed = timed && net->prof.on;
     BlockPlan bp;
     const bool fused = p.size[R_RING8] && net->rcfg.lanes == route_fused_lanes();
-    if (choose_form(net, num_ticks, fused, bp) != FORM_TICKS) {
+    if (!one_tick && choose_form(net, num_ticks, fused, bp) != FORM_TICKS) {
         hipError_t e = queue_several(net, base, num_ticks, s, timed);
         if (e == hipSuccess)
             e = launch_advance_tick(net->dn, num_ticks, s);
@@ -2687,6 +2689,9 @@ ranc_status ranc_autotune(ranc_net *net, const uint32_t *inputs, uint32_t flags,
     double best = -1.0;
     Cand best_c = cands[0];
     ranc_status st = RANC_OK;
+    // (samples per workgroup are those of the tick-by-tick launches; several
+    // ticks in one launch run the same for every candidate)
+    const bool one_tick = p.path != RANC_PATH_PLAIN;
     for (const Cand &c : cands) {
         if (e != hipSuccess || st != RANC_OK)
             break;
@@ -2694,11 +2699,11 @@ ranc_status ranc_autotune(ranc_net *net, const uint32_t *inputs, uint32_t flags,
         net->rcfg = c.rc;
         // one untimed pass, then a timed pass, each from the initial state
         e = reset_state(net, s);
-        if (e == hipSuccess && (st = queue_ticks(net, base, num_ticks, s, false)) == RANC_OK)
+        if (e == hipSuccess && (st = queue_ticks(net, base, num_ticks, s, false, one_tick)) == RANC_OK)
             e = reset_state(net, s);
         if (e == hipSuccess && st == RANC_OK)
             e = hipEventRecord(e0, s);
-        if (e == hipSuccess && st == RANC_OK && (st = queue_ticks(net, base, num_ticks, s, false)) == RANC_OK)
+        if (e == hipSuccess && st == RANC_OK && (st = queue_ticks(net, base, num_ticks, s, false, one_tick)) == RANC_OK)
             e = hipEventRecord(e1, s);
         if (e == hipSuccess && st == RANC_OK)
             e = hipEventSynchronize(e1);

@@ -24,3 +24,20 @@ net = W.random_net(1, 1, 64, 64, 1, input_cores=[], config_id=873)
 result = kernels(run(load(net, 1, {T}, "plain"), {T}))
 """)
     assert k == ["k_plain_whole"] * launches + ["k_advance_tick"]
+
+
+def test_autotune_times_the_launches_that_the_shape_applies_to(dry):
+    """A feed-forward network runs several ticks per launch whatever its samples
+    per workgroup: the candidates (64 and 128 here) are timed tick by tick."""
+    T = 16
+    run, tuned, tune = dry(f"""
+net = forward_net(17, 4, 256, 256, 4, 9, 2)
+h = load(net, 128, {T}, "mfma")
+result = [kernels(run(h, {T}))]
+tune = R.ranc_autotune(h, 0, 0, {T}, 0)
+result += [kernels(), tune]
+""")
+    assert run.count("k_integrate_mfma_ticks") < T
+    assert tuned.count("k_integrate_tile") == tuned.count("k_integrate_mfma") == 2 * T
+    assert "k_integrate_mfma_ticks" not in tuned
+    assert tune["candidates"] == 2
