@@ -360,12 +360,13 @@ typedef struct ranc_tune {
     int32_t candidates;              /* ranc_autotune: number of shapes timed */
     int32_t route_lanes_per_word;    /* plain path: 1 = a router launch per tick, one lane per
                                         destination word (the three router fields above apply);
-                                        8 = the form for launches too small to fill the GPU: spikes
-                                        are delivered by the kernel that integrates (the router
-                                        fields do not apply; networks of more than 2^26 neurons
-                                        times samples, or 2^22 from 64 samples on, still take
-                                        a router launch); 0 in
-                                        ranc_set_launch_shape = chosen automatically */
+                                        8 (they do not) = no router: spikes are delivered by the
+                                        kernel that integrates, or, for networks of more than 2^26
+                                        neurons times samples (2^22 from 64 samples on) and in a
+                                        workspace without room for that, a router with eight lanes
+                                        per word, one sample per block row. 0 in
+                                        ranc_set_launch_shape = chosen automatically. Batches
+                                        route with one lane per word where they need a router. */
 } ranc_tune;
 
 /*

@@ -106,18 +106,95 @@ __global__ __launch_bounds__(ROUTE_THREADS) void k_route(DevNet n, int k)
     route_unit<SB, DMAX, STAGE>(n, k, blockIdx.x, blockIdx.y, gridDim.x, sp);
 }
 
-// Launch-shape value (route_lanes_per_word) of the form without a router
-// (k_plain_ticks in kern_plain.hip): chosen when the one-lane launch would have
-// fewer blocks than the GPU has compute units, where a router launch costs its
-// latency (about 4 us) whatever it delivers.
-static constexpr int ROUTE_FUSED = 8;
+// The same tick for one sample (blockIdx.y) with K lanes per destination
+// word: lane r of a word's group walks entries r, r + K, ... of each delay's
+// list, and the group ORs its partial words together with lane shuffles, so
+// the serial walk is K times shorter and K times more lanes are in flight
+// (used when the samples alone cannot fill the GPU). Lane 0 of the group is
+// still the only writer of the word's scheduler slots. The loop bound is
+// uniform across the block, so every lane reaches every shuffle. The spike
+// bitmap is read in place: with one sample per block, copying all of it
+// into every block's LDS cost more than the gather reads it saved (one
+// MNIST-512c-shaped instance: 12.8 us per plain tick staged, 9.4 direct).
+template <int DMAX, int K>
+__global__ __launch_bounds__(ROUTE_THREADS) void k_route_split(DevNet n, int k)
+{
+    static_assert(K >= 2 && K <= 64 && (K & (K - 1)) == 0, "K divides a wavefront");
+    const int q_now = tick_slot(n, k);
+    const int s = blockIdx.y;
+    const size_t words = (size_t)n.C * n.NW;
+    const uint32_t *bits = n.spk + (size_t)s * words;
+    const int CW = n.C * n.W;
+    const size_t slot_stride = (size_t)n.S * CW;
+    uint32_t *ring_s = n.ring + (size_t)s * CW;
+    const int r = threadIdx.x & (K - 1);
+    constexpr int WPB = ROUTE_THREADS / K;   // destination words per block and pass
+    for (int dw0 = blockIdx.x * WPB; dw0 < CW; dw0 += gridDim.x * WPB) {
+        const int dw = dw0 + threadIdx.x / K;
+        const bool own = dw < CW;
+        uint32_t acc[DMAX];
+#pragma unroll
+        for (int d = 0; d < DMAX; ++d)
+            acc[d] = 0u;
+        if (own) {
+            if (r == 0)
+                ring_s[(size_t)q_now * slot_stride + dw] = 0u;
+            const uint16_t *dcnt = n.rt_dcnt + (size_t)dw * DMAX;
+            const uint32_t *e = n.rt_ent + n.rt_goff[dw >> 6] + (dw & 63);
+            uint32_t k0 = 0;
+#pragma unroll
+            for (int d = 0; d < DMAX; ++d) {
+                const uint32_t kn = k0 + dcnt[d];
+#pragma unroll 2
+                for (uint32_t j = k0 + r; j < kn; j += K) {
+                    const uint32_t ent = e[(size_t)j * 64];
+                    const uint32_t g = ent >> RT_SRC_SHIFT;
+                    acc[d] |= ((bits[g >> 5] >> (g & 31u)) & 1u) << (ent & 31u);
+                }
+                k0 = kn;
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < DMAX; ++d) {
+#pragma unroll
+            for (int off = 1; off < K; off <<= 1)
+                acc[d] |= (uint32_t)__shfl_xor((int)acc[d], off, 64);
+        }
+        if (own && r == 0) {
+#pragma unroll
+            for (int d = 0; d < DMAX; ++d) {
+                if (d >= n.D)
+                    break;
+                int q = q_now + d + 1;
+                if (q >= n.Q)
+                    q -= n.Q;
+                if (acc[d])
+                    ring_s[(size_t)q * slot_stride + dw] |= acc[d];
+            }
+        }
+    }
+}
 
-int route_fused_lanes() { return ROUTE_FUSED; }
+// Lanes per destination word of the split router; as a launch-shape value
+// (route_lanes_per_word) of a handle with the byte ring, the form without a router
+// (k_plain_ticks in kern_plain.hip).
+static constexpr int ROUTE_SPLIT_K = 8;
+
+int route_split_lanes() { return ROUTE_SPLIT_K; }
 
 int route_auto_lanes(const DevNet &n, const RouteCfg &cfg)
 {
     const long groups = (n.S + cfg.samples_per_block - 1) / cfg.samples_per_block;
-    return (long)cfg.blocks_per_group * groups < 256 ? ROUTE_FUSED : 1;
+    return (long)cfg.blocks_per_group * groups < 256 ? ROUTE_SPLIT_K : 1;
+}
+
+template <int DMAX>
+static hipError_t launch_route_split(const DevNet &n, int k, hipStream_t st)
+{
+    constexpr int WPB = ROUTE_THREADS / ROUTE_SPLIT_K;
+    const dim3 grid((n.C * n.W + WPB - 1) / WPB, n.S);
+    hipLaunchKernelGGL((k_route_split<DMAX, ROUTE_SPLIT_K>), grid, dim3(ROUTE_THREADS), 0, st, n, k);
+    return hipGetLastError();
 }
 
 int route_dmax(int D) { return D <= 4 ? 4 : D <= 8 ? 8 : 16; }
@@ -264,6 +341,15 @@ static hipError_t launch_route_s(const DevNet &n, int k, const RouteCfg &cfg, hi
 
 hipError_t launch_route(const DevNet &n, int k, const RouteCfg &cfg, hipStream_t st)
 {
+    if (cfg.lanes == ROUTE_SPLIT_K) {
+        if (n.S > 65535)
+            return hipErrorInvalidValue;   // one sample per grid row
+        switch (route_dmax(n.D)) {
+        case 4: return launch_route_split<4>(n, k, st);
+        case 8: return launch_route_split<8>(n, k, st);
+        default: return launch_route_split<16>(n, k, st);
+        }
+    }
     if (cfg.lanes != 1 || cfg.blocks_per_group < 1)
         return hipErrorInvalidValue;
     if (cfg.stage && (size_t)n.C * n.NW * 4 * cfg.samples_per_block > ROUTE_LDS_BYTES)

@@ -284,8 +284,9 @@ struct RouteCfg {
     int samples_per_block;  // 1, 2, 4 or 8 spike bitmaps per block
     int blocks_per_group;   // blocks sharing one group of samples (split of the destination words)
     int stage;              // stage the bitmaps in LDS
-    int lanes;              // 1 (k_route, the fields above apply) or route_fused_lanes()
-                            // (k_plain_ticks delivers the spikes itself)
+    int lanes;              // 1 (k_route, the fields above apply) or route_split_lanes(): handles
+                            // with the byte ring have no router (k_plain_ticks delivers the
+                            // spikes itself), others several lanes per destination word
 };
 
 // Launchers (return the first HIP error, hipSuccess otherwise).
@@ -360,8 +361,8 @@ hipError_t launch_integrate_mfma_cb(const DevNet &n, const TickArgs &a, int two_
 hipError_t launch_integrate_mfma_group_cb(const MfmaGroupArgs &g, int total, int k, int code, int ext,
                                           hipStream_t st);
 RouteCfg route_default_cfg(const DevNet &n);
-int route_fused_lanes();
-// The form chosen for a configuration: without a router when the one-lane
+int route_split_lanes();
+// Lanes of a handle without the byte ring: several per word when the one-lane
 // launch would have fewer blocks than the GPU has compute units.
 int route_auto_lanes(const DevNet &n, const RouteCfg &cfg);
 int route_dmax(int max_delay);

@@ -955,7 +955,7 @@ static int mfma_compact(const ranc_net *net)
 // Plain path: the form without a router wherever the network has the byte ring.
 static int auto_lanes(const ranc_net *net, const RouteCfg &rc)
 {
-    return net->p.size[R_RING8] ? route_fused_lanes() : route_auto_lanes(net->dn, rc);
+    return net->p.size[R_RING8] ? route_split_lanes() : route_auto_lanes(net->dn, rc);
 }
 
 // Every instance to its initial state.
@@ -1216,7 +1216,7 @@ static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_tick
     const size_t tick_words = (size_t)p.Cin * p.W;
     timed = timed && net->prof.on;
     BlockPlan bp;
-    const bool fused = p.size[R_RING8] && net->rcfg.lanes == route_fused_lanes();
+    const bool fused = p.size[R_RING8] && net->rcfg.lanes == route_split_lanes();
     if (!one_tick && choose_form(net, num_ticks, fused, bp) != FORM_TICKS) {
         hipError_t e = queue_several(net, base, num_ticks, s, timed);
         if (e == hipSuccess)
@@ -1224,8 +1224,6 @@ static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_tick
         return e == hipSuccess ? RANC_OK : hip_fail(e, "launching integration (several ticks)");
     }
     const bool via_words = p.size[R_RING8] && !fused;   // the router works on the bit ring
-    RouteCfg rcfg = net->rcfg;
-    rcfg.lanes = 1;
     if (via_words) {
         hipError_t e = launch_move_ring(net->dn, net->ws + p.off[R_RING8], 0, s);
         if (e != hipSuccess)
@@ -1261,7 +1259,7 @@ static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_tick
         if (p.path == RANC_PATH_PLAIN && !fused) {
             e = timed ? prof_begin(net, 1, s, &slot) : hipSuccess;
             if (e == hipSuccess)
-                e = launch_route(net->dn, k, rcfg, s);
+                e = launch_route(net->dn, k, net->rcfg, s);
             if (e == hipSuccess && timed)
                 e = prof_end(net, slot, s);
             if (e != hipSuccess)
@@ -2658,15 +2656,11 @@ ranc_status ranc_autotune(ranc_net *net, const uint32_t *inputs, uint32_t flags,
                 }
             }
         }
-        if (p.S <= 65535) {
-            // the form without a router (the fields above do not apply to
-            // it), once
-            RouteCfg rc = def;
-            rc.lanes = route_fused_lanes();
-            cands.push_back({p.spw, rc});
-        }
-        if (cands.empty())
-            cands.push_back({p.spw, def});
+        // without a router, or several lanes per destination word (the fields
+        // above do not apply), once
+        RouteCfg rc = def;
+        rc.lanes = route_split_lanes();
+        cands.push_back({p.spw, rc});
     }
     const uint32_t *base = inputs;
     if (base && p.Cin > 0 && !(flags & RANC_INPUTS_ON_DEVICE)) {
@@ -2775,12 +2769,10 @@ ranc_status ranc_set_launch_shape(ranc_net *net, const ranc_tune *shape)
     if ((p.S + sb - 1) / sb > 65535)
         return fail(RANC_EINVAL, "too many sample groups for the router grid");
     const int lanes = shape->route_lanes_per_word;
-    if (lanes != 0 && lanes != 1 && lanes != route_fused_lanes())
+    if (lanes != 0 && lanes != 1 && lanes != route_split_lanes())
         return fail(RANC_EINVAL, "route_lanes_per_word %d must be 0 (automatic), 1 or %d", lanes,
-                    route_fused_lanes());
+                    route_split_lanes());
     rc.lanes = lanes ? lanes : auto_lanes(net, rc);
-    if (rc.lanes != 1 && p.S > 65535)
-        return fail(RANC_EINVAL, "route_lanes_per_word 8 takes at most 65535 samples");
     drop_graphs(net);
     if (p.path == RANC_PATH_PLAIN)
         net->rcfg = rc;

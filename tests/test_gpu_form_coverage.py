@@ -139,3 +139,33 @@ def test_uneven_types_in_sorted_order(G, A, most):
                               input_cores=[0, 3], config_id=874), most)
     whole = G * -(-most // 32) <= 12
     check(net, "plain", 171, [(5, False), (14, whole)], samples=[0, 1, 99, 170])
+
+
+@pytest.mark.parametrize("D", [3, 7, 12], ids=["dmax4", "dmax8", "dmax16"])
+@pytest.mark.parametrize("lanes", [1, 8])
+def test_routers_without_the_byte_ring(D, lanes):
+    """Both routers in a workspace that holds everything but the byte ring, with
+    every delay-register width, launches and a graph."""
+    import torch
+    from paper_2404_16208_amd import ranc as R
+    net = W.random_net(300 + D, 24, 128, 128, 4, max_delay=D, grid_w=6, density=0.25, p_core=0.85, p_out=0.1,
+                       input_cores=list(range(0, 24, 3)), config_id=874)
+    S, T = 5, D + 2
+    d = R.Desc(net)
+    small = R.ranc_workspace_bytes(d, S, T, R.RANC_PATH_PLAIN) - (D + 2) * S * 24 * 128
+    ws = torch.full((small + 256,), 0xA5, dtype=torch.uint8, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+    x = W.bernoulli_inputs(3, net, S, 2 * T, 0.25, config_id=874)
+    ref = oracle_results(net, x, 2 * T, range(S))
+    xd = torch.from_numpy(x.view(np.int32)).cuda()
+    h = R.ranc_load_network(d, S, T, R.RANC_PATH_PLAIN, ws.data_ptr(), small, st)
+    R.ranc_set_launch_shape(h, dict(R.ranc_get_launch_shape(h), route_lanes_per_word=lanes))
+    for call in range(2):
+        xi = xd[:, call * T:(call + 1) * T].contiguous()
+        R.ranc_run_ticks([h], [xi.data_ptr()], R.RANC_INPUTS_ON_DEVICE | (R.RANC_RUN_GRAPH if call else 0), T, st)
+        torch.cuda.synchronize()
+    for s in range(S):
+        assert np.array_equal(R.ranc_read_potentials(h, s, 24, 128), ref[s]["v"]), s
+        for k, v in R.ranc_read_counters(h, s).items():
+            assert v == ref[s]["counters"][k], (s, k)
+    R.ranc_free(h)

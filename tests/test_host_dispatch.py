@@ -41,3 +41,26 @@ result += [kernels(), tune]
     assert tuned.count("k_integrate_tile") == tuned.count("k_integrate_mfma") == 2 * T
     assert "k_integrate_mfma_ticks" not in tuned
     assert tune["candidates"] == 2
+
+
+def test_router_of_a_handle_without_the_byte_ring(dry):
+    """In a workspace that holds everything but the byte ring, the router that the
+    launch shape names is the one that runs: eight lanes per word for a few
+    blocks (the automatic choice), one lane per word when asked for."""
+    auto, one, tuned = dry("""
+net = W.random_net(63, 8, 256, 256, 4, grid_w=4)
+S, T = 3, 2
+h = load(net, S, T, "plain", need(net, S, T, "plain") - (4 + 2) * S * 8 * 256)
+shape = R.ranc_get_launch_shape(h)
+result = [[shape["route_lanes_per_word"], kernels(run(h, T))]]
+R.ranc_set_launch_shape(h, dict(shape, route_lanes_per_word=1))
+result.append([R.ranc_get_launch_shape(h)["route_lanes_per_word"], kernels(run(h, T))])
+tune = R.ranc_autotune(h, 0, 0, T, 0)
+result.append([tune["candidates"], kernels()])
+""")
+    ends = ["k_fold_counts", "k_advance_tick"]
+    assert auto == [8, ["k_integrate_plain", "k_route_split"] * 2 + ends]
+    assert one == [1, ["k_integrate_plain", "k_route"] * 2 + ends]
+    # (each candidate twice, and one of them is the eight-lane form)
+    assert tuned[1].count("k_route_split") == 2 * 2
+    assert tuned[1].count("k_route") == (tuned[0] - 1) * 2 * 2
