@@ -43,7 +43,7 @@
 //   plain path:
 //   ring     u32 [Q][S][C][W]  scheduler: slot t%Q holds the axon spikes of tick t
 //   ring8    u8 [Q][S][C][A]   the scheduler with a byte per axon (small networks; Q = D + 2 or
-//                              more): between calls it holds the scheduled spikes and ring none
+//                              more); the scheduled spikes are in one of the two rings
 //   spk      u32 [S][C][NW]    spikes of the current tick
 //   raster   u32 [RT][S][Wout] output-bus spikes of tick t in row t%RT
 //   sparse path:

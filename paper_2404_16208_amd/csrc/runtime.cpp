@@ -899,6 +899,7 @@ struct Batch {
     std::vector<Phase> phases;
     std::vector<std::vector<int>> phase_links;   // per phase: networks (index in nets) counting mesh links
     std::vector<char> links;                     // links_on of each network when the batch was set up
+    std::vector<char> words;                     // and whether it runs through the router (wants_words)
     bool persistent = false;
     int mf_units = 0, pl_units = 0, rt_units = 0, mf_workgroups = 0;
     size_t rt_lds = 0;
@@ -941,6 +942,8 @@ struct ranc_net {
     std::vector<long long> links_host; // mirror of the link difference arrays
     int static_dev = -1;               // device whose library-held workspace this handle holds, or -1
     bool state_lost = false;           // a state-resident launch gave up: state undefined until reset
+    bool ring_words = false;           // the scheduled spikes are in the bit ring, not the byte ring (enter_ring)
+    bool recorded = false;             // a caller's own graph holds runs of this handle
 };
 
 // MFMA path: whether this network's launches build their B tiles from the
@@ -1223,12 +1226,6 @@ static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_tick
             e = launch_advance_tick(net->dn, num_ticks, s);
         return e == hipSuccess ? RANC_OK : hip_fail(e, "launching integration (several ticks)");
     }
-    const bool via_words = p.size[R_RING8] && !fused;   // the router works on the bit ring
-    if (via_words) {
-        hipError_t e = launch_move_ring(net->dn, net->ws + p.off[R_RING8], 0, s);
-        if (e != hipSuccess)
-            return hip_fail(e, "moving the scheduled spikes");
-    }
     for (int k = 0; k < num_ticks; ++k) {
         TickArgs ta;
         ta.k = k;
@@ -1274,11 +1271,50 @@ static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_tick
     hipError_t e = fused ? hipSuccess : launch_fold_counts(net->dn, num_ticks, s);
     if (e == hipSuccess)
         e = launch_advance_tick(net->dn, num_ticks, s);
-    if (e == hipSuccess && via_words)
-        e = launch_move_ring(net->dn, net->ws + p.off[R_RING8], 1, s);
     if (e != hipSuccess)
         return hip_fail(e, "advancing the tick");
     return RANC_OK;
+}
+
+// Whether a handle with the byte ring runs through the router all the same
+// (route_lanes_per_word 1), which works on the bit ring.
+static bool wants_words(const ranc_net *net)
+{
+    return net->p.size[R_RING8] && net->rcfg.lanes != route_split_lanes();
+}
+
+// Before a call that finds its scheduled spikes in the bit ring (words) or the
+// byte ring: move them there if they are in the other. They stay where a call
+// leaves them, so calls of one form after another move nothing (a move at both
+// ends of every router call took 6 to 10 us of the 30 to 54 of a one-tick call).
+// A call recorded into a caller's own graph may be replayed after calls of the other
+// form, so from the first such call on they go back to the byte ring after every
+// router call, and every router call starts with a move (one that finds the other
+// ring empty changes nothing).
+static hipError_t move_ring(ranc_net *net, bool words, hipStream_t s, bool recording)
+{
+    const hipError_t e = launch_move_ring(net->dn, net->ws + net->p.off[R_RING8], words ? 0 : 1, s);
+    if (e == hipSuccess && !recording)
+        net->ring_words = words;
+    return e;
+}
+static bool is_recording(hipStream_t s)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    return s && hipStreamIsCapturing(s, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
+}
+static hipError_t enter_ring(ranc_net *net, bool words, hipStream_t s)
+{
+    if (!net->p.size[R_RING8])
+        return hipSuccess;
+    const bool recording = is_recording(s);
+    net->recorded = net->recorded || recording;
+    const bool move = words ? net->recorded || !net->ring_words : net->ring_words;
+    return move ? move_ring(net, words, s, recording) : hipSuccess;
+}
+static hipError_t leave_ring(ranc_net *net, bool words, hipStream_t s)
+{
+    return words && net->recorded ? move_ring(net, false, s, is_recording(s)) : hipSuccess;
 }
 
 // Whether a batch runs network `net` in launches of its own (queue_ticks): those
@@ -1664,8 +1700,10 @@ static ranc_status build_batch(ranc_net *const *nets, int num, const uint32_t *c
     b.phases.assign(nphases, Batch::Phase{});
     b.phase_links.assign(nphases, std::vector<int>());
     b.links.assign(num, 0);
+    b.words.assign(num, 0);
     for (int i = 0; i < num; ++i) {
         b.links[i] = nets[i]->links_on ? 1 : 0;
+        b.words[i] = b.is_solo[i] && wants_words(nets[i]) ? 1 : 0;   // (the batch's own kernels use the byte ring)
         if (nets[i]->links_on && !b.is_solo[i])
             b.phase_links[phase_of[i]].push_back(i);
     }
@@ -1907,7 +1945,8 @@ static ranc_status run_batch(ranc_net *const *nets, int num, const uint32_t *con
     bool same = b.num_ticks == num_ticks && b.persistent == persistent && (int)b.nets.size() == num &&
                 std::equal(b.nets.begin(), b.nets.end(), nets) && std::equal(b.bases.begin(), b.bases.end(), bases);
     for (int i = 0; same && i < num; ++i)
-        same = b.uids[i] == nets[i]->uid && b.links[i] == (nets[i]->links_on ? 1 : 0);
+        same = b.uids[i] == nets[i]->uid && b.links[i] == (nets[i]->links_on ? 1 : 0) &&
+               b.words[i] == (b.is_solo[i] && wants_words(nets[i]) ? 1 : 0);
     if (!same) {
         if (b.exec)
             hipGraphExecDestroy(b.exec);
@@ -1941,6 +1980,7 @@ static ranc_status run_batch(ranc_net *const *nets, int num, const uint32_t *con
         b.phases = std::move(nb.phases);
         b.phase_links = std::move(nb.phase_links);
         b.links = std::move(nb.links);
+        b.words = std::move(nb.words);
         b.solo = std::move(nb.solo);
         b.is_solo = std::move(nb.is_solo);
         b.persistent = nb.persistent;
@@ -1951,8 +1991,20 @@ static ranc_status run_batch(ranc_net *const *nets, int num, const uint32_t *con
         b.rt_lds = nb.rt_lds;
         b.num_ticks = num_ticks;
     }
-    if (!graph)
-        return queue_batch_ticks(lead, b, s, true);
+    auto each_ring = [&](hipError_t (*settle)(ranc_net *, bool, hipStream_t)) -> ranc_status {
+        for (int i = 0; i < num; ++i) {
+            const hipError_t e = settle(nets[i], b.words[i] != 0, s);
+            if (e != hipSuccess)
+                return hip_fail(e, "moving the scheduled spikes");
+        }
+        return RANC_OK;
+    };
+    if (!graph) {
+        ranc_status st = each_ring(enter_ring);
+        if (st == RANC_OK)
+            st = queue_batch_ticks(lead, b, s, true);
+        return st == RANC_OK ? each_ring(leave_ring) : st;
+    }
     if (!b.exec) {
         hipError_t e = hipSuccess;
         if (!lead->cap_stream)
@@ -1978,6 +2030,9 @@ static ranc_status run_batch(ranc_net *const *nets, int num, const uint32_t *con
         }
         b.graph = g;
     }
+    ranc_status st = each_ring(enter_ring);
+    if (st != RANC_OK)
+        return st;
     int slot = -1;
     hipError_t e = prof_begin(lead, 2, s, &slot);
     if (e == hipSuccess)
@@ -1986,7 +2041,7 @@ static ranc_status run_batch(ranc_net *const *nets, int num, const uint32_t *con
         e = prof_end(lead, slot, s);
     if (e != hipSuccess)
         return hip_fail(e, "launching the batch tick loop");
-    return RANC_OK;
+    return each_ring(leave_ring);
 }
 
 static void drop_graphs(ranc_net *net);
@@ -2232,9 +2287,15 @@ ranc_status ranc_run_ticks(ranc_net *const *nets, int32_t num_nets, const uint32
         if (st != RANC_OK)
             return st;
     } else {
+        const bool words = wants_words(nets[0]);
+        hipError_t e = enter_ring(nets[0], words, s);
+        if (e != hipSuccess)
+            return hip_fail(e, "moving the scheduled spikes");
         ranc_status st = (flags & RANC_RUN_RESIDENT) ? run_resident(nets[0], bases[0], num_ticks, s)
                          : (flags & RANC_RUN_GRAPH)  ? run_captured(nets[0], bases[0], num_ticks, s)
                                                      : queue_ticks(nets[0], bases[0], num_ticks, s, true);
+        if (st == RANC_OK && (e = leave_ring(nets[0], words, s)) != hipSuccess)
+            st = hip_fail(e, "moving the scheduled spikes");
         if (st == RANC_ETIMEOUT) {   // the ticks ran partially: the call counts as run
             nets[0]->tick += num_ticks;
             nets[0]->last_stream = s;

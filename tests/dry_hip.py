@@ -44,8 +44,8 @@ def load(net, S, T, path, size=None):
 def need(net, S, T, path):
     return R.ranc_workspace_bytes(R.Desc(net), S, T, R.PATHS[path])
 
-def run(handles, T, flags=0):
-    R.ranc_run_ticks(handles if isinstance(handles, list) else [handles], None, flags, T, 0)
+def run(handles, T, flags=0, stream=0):
+    R.ranc_run_ticks(handles if isinstance(handles, list) else [handles], None, flags, T, stream)
     return log()
 
 {body}

@@ -169,3 +169,46 @@ def test_routers_without_the_byte_ring(D, lanes):
         for k, v in R.ranc_read_counters(h, s).items():
             assert v == ref[s]["counters"][k], (s, k)
     R.ranc_free(h)
+
+
+def test_forms_among_replays_of_a_callers_graph():
+    """Runs recorded into the caller's own graphs, without a router and with one,
+    replayed among calls of the other form: every tick against the oracle."""
+    import torch
+    from paper_2404_16208_amd.ranc import RancNet
+    net = W.random_net(31, 40, 128, 128, 4, max_delay=9, grid_w=8, density=0.25, p_core=0.85, p_out=0.1,
+                       input_cores=list(range(0, 40, 3)), config_id=874)
+    S, k = 3, 5
+    plan = ["bytes", "record bytes", "words", "replay bytes", "words", "record words", "words", "replay words", "replay bytes",
+            "bytes", "replay words", "replay words", "words", "bytes"]
+    T = k * sum(not p.startswith("record") for p in plan)
+    x = W.bernoulli_inputs(3, net, S, T, 0.2, config_id=874)
+    ref = oracle_results(net, x, T, range(S))
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        g = RancNet(net, S, k, path="plain", workspace_fill=0xA5)
+        auto = g.launch_shape()
+        buf = torch.empty((S, k) + x.shape[2:], dtype=torch.int32, device="cuda")
+        graphs, t = {}, 0
+        for step in plan:
+            log(f"[graphs] tick {t} {step}")
+            what, form = step.split() if " " in step else ("run", step)
+            if what != "replay":
+                g.launch_shape(dict(auto, route_lanes_per_word=1 if form == "words" else 8))
+            if what == "record":
+                graphs[form] = torch.cuda.CUDAGraph()
+                with torch.cuda.graph(graphs[form], stream=side):
+                    g.run(buf, k)
+                continue
+            buf.copy_(torch.from_numpy(np.ascontiguousarray(x[:, t:t + k]).view(np.int32)))
+            if what == "replay":
+                graphs[form].replay()
+            else:
+                g.run(buf, k)
+            t += k
+        side.synchronize()
+        for s in range(S):
+            assert np.array_equal(g.potentials(s), ref[s]["v"]), s
+            for c, v in g.counters(s).items():
+                assert v == ref[s]["counters"][c], (s, c)
+        g.close()

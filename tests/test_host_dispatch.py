@@ -64,3 +64,42 @@ result.append([tune["candidates"], kernels()])
     # (each candidate twice, and one of them is the eight-lane form)
     assert tuned[1].count("k_route_split") == 2 * 2
     assert tuned[1].count("k_route") == (tuned[0] - 1) * 2 * 2
+
+
+def test_scheduled_spikes_move_when_the_form_changes(dry):
+    """Calls through the router on a handle with the byte ring: the scheduled
+    spikes move once, to the bit ring, and once back; in a batch too. Once a
+    caller's graph holds a run, they are back in the byte ring after every call."""
+    plain, batch, recorded = dry("""
+GRAPH = R.RANC_RUN_GRAPH
+net, other = W.random_net(1, 64, 128, 128, 4, grid_w=8), W.random_net(2, 3, 64, 64, 2, grid_w=3)
+moves = lambda *a: [r[2] for r in run(*a) if r[0] == "launch"].count("k_move_ring")
+def shape(h, lanes):
+    R.ranc_set_launch_shape(h, dict(R.ranc_get_launch_shape(h), route_lanes_per_word=lanes))
+h = load(net, 20, 4, "plain")
+plain = [moves(h, 4)]
+shape(h, 1)
+plain += [moves(h, 4), moves(h, 4, GRAPH), moves(h, 1), moves(h, 4, GRAPH)]
+shape(h, 8)
+plain += [moves(h, 4), moves(h, 4, GRAPH)]
+o = load(other, 2, 4, "plain")
+batch = [moves([h, o], 4), moves([h, o], 4, GRAPH)]
+shape(h, 1)
+shape(o, 1)
+batch += [moves([h, o], 4), moves([h, o], 4, GRAPH), moves(o, 4), moves([h, o], 4), moves(h, 4)]
+shape(h, 8)
+batch += [moves([h, o], 4, GRAPH), moves(h, 4)]
+dry.dry_capturing(1)
+recorded = [moves(h, 4, 0, 7)]
+dry.dry_capturing(0)
+shape(h, 1)
+recorded += [moves(h, 4, 0, 7), moves(h, 4, GRAPH, 7)]
+shape(h, 8)
+recorded += [moves(h, 4, 0, 7)]
+result = [plain, batch, recorded]
+""")
+    assert plain == [0, 1, 0, 0, 0, 1, 0]
+    # (h has launches of its own in the batch and keeps its router there; o,
+    # among the batch's kernels, is on the byte ring there and on the bit ring alone)
+    assert batch == [0, 0, 1, 0, 1, 1, 0, 1, 0]
+    assert recorded == [0, 2, 2, 0]
