@@ -1789,7 +1789,7 @@ static double chain_work(const Batch &b, int c)
     return w;
 }
 
-static hipError_t queue_batch_branches(ranc_net *lead, const Batch &b, hipStream_t s)
+static ranc_status queue_batch_branches(ranc_net *lead, const Batch &b, hipStream_t s)
 {
     const BatchEntry *tpl = batch_table(lead, 1);
     const Batch::Phase &ph = b.phases[0];
@@ -1806,8 +1806,10 @@ static hipError_t queue_batch_branches(ranc_net *lead, const Batch &b, hipStream
         e = hipEventCreateWithFlags(&lead->br_fork, hipEventDisableTiming);
     if (e == hipSuccess)
         e = hipEventRecord(lead->br_fork, s);
-    for (int i = 0; e == hipSuccess && i < nb; ++i)
-        e = hipStreamWaitEvent(lead->br_stream[i], lead->br_fork, 0);
+    int forked = 0;
+    for (; e == hipSuccess && forked < nb; forked += e == hipSuccess)
+        e = hipStreamWaitEvent(lead->br_stream[forked], lead->br_fork, 0);
+    ranc_status st_solo = RANC_OK;
     // chains by decreasing work, each on the branch with the least so far (in list
     // order, round robin: six networks x 100 samples 1870 us, now 1745)
     std::vector<std::pair<double, int>> order;
@@ -1815,7 +1817,7 @@ static hipError_t queue_batch_branches(ranc_net *lead, const Batch &b, hipStream
         order.push_back({chain_work(b, c), c});
     std::stable_sort(order.begin(), order.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
     double load[ranc_net::BATCH_BRANCHES] = {};
-    for (int i = 0; e == hipSuccess && i < chains; ++i) {
+    for (int i = 0; e == hipSuccess && st_solo == RANC_OK && i < chains; ++i) {
         const int c = order[i].second;
         const int branch = (int)(std::min_element(load, load + nb) - load);
         load[branch] += order[i].first;
@@ -1828,8 +1830,7 @@ static hipError_t queue_batch_branches(ranc_net *lead, const Batch &b, hipStream
                 e = launch_fold_counts(b.mf[i].n, b.num_ticks, st);
         } else if (c < ph.g_num + (int)b.solo.size()) {
             const int i = b.solo[c - ph.g_num];
-            if (queue_ticks(b.nets[i], b.bases[i], b.num_ticks, st, false) != RANC_OK)
-                return hipErrorLaunchFailure;
+            st_solo = queue_ticks(b.nets[i], b.bases[i], b.num_ticks, st, false);
         } else if (ph.pf_num > 0 && c == ph.g_num + (int)b.solo.size()) {
             for (int k = 0; e == hipSuccess && k < b.num_ticks; ++k)
                 e = launch_plain_ticks_batch(tpl + ph.pf_first, ph.pf_num, ph.pf_units, k, st);
@@ -1844,12 +1845,15 @@ static hipError_t queue_batch_branches(ranc_net *lead, const Batch &b, hipStream
                 e = launch_fold_counts(b.pl[i].n, b.num_ticks, st);
         }
     }
-    for (int i = 0; e == hipSuccess && i < nb; ++i) {
-        e = hipEventRecord(lead->br_join[i], lead->br_stream[i]);
+    // joined also after an error: what was queued is ordered before what follows on `s`
+    for (int i = 0; i < forked; ++i) {
+        hipError_t j = hipEventRecord(lead->br_join[i], lead->br_stream[i]);
+        if (j == hipSuccess)
+            j = hipStreamWaitEvent(s, lead->br_join[i], 0);
         if (e == hipSuccess)
-            e = hipStreamWaitEvent(s, lead->br_join[i], 0);
+            e = j;
     }
-    return e;
+    return st_solo != RANC_OK ? st_solo : e != hipSuccess ? hip_fail(e, "launching batch integration (branches)") : RANC_OK;
 }
 
 static ranc_status queue_batch_ticks(ranc_net *lead, const Batch &b, hipStream_t s, bool timed)
@@ -1863,9 +1867,9 @@ static ranc_status queue_batch_ticks(ranc_net *lead, const Batch &b, hipStream_t
     const bool branches = !b.persistent && b.phases.size() == 1 && !any_links && !timed &&
                           batch_chains(b) > 1;
     if (branches) {
-        hipError_t e = queue_batch_branches(lead, b, s);
-        if (e != hipSuccess)
-            return hip_fail(e, "launching batch integration (branches)");
+        const ranc_status st = queue_batch_branches(lead, b, s);
+        if (st != RANC_OK)
+            return st;
     }
     for (int i : b.solo) {
         const ranc_status st = branches ? RANC_OK : queue_ticks(b.nets[i], b.bases[i], b.num_ticks, s, false);

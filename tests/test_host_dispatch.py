@@ -103,3 +103,23 @@ result = [plain, batch, recorded]
     # among the batch's kernels, is on the byte ring there and on the bit ring alone)
     assert batch == [0, 0, 1, 0, 1, 1, 0, 1, 0]
     assert recorded == [0, 2, 2, 0]
+
+
+@pytest.mark.parametrize("kernel", ["k_plain_whole", "k_integrate_tile"])
+def test_error_in_a_branch_of_a_batch(dry, kernel):
+    """A launch that fails in one of a batch's branches: the call's error tells
+    which launch and why, and every branch joins the caller's stream."""
+    message, rows = dry(f"""
+a, b = W.random_net(1, 4, 64, 64, 2, grid_w=2), W.random_net(2, 3, 64, 64, 2, grid_w=3)
+hs = [load(a, 3, 16, "plain"), load(b, 3, 16, "plain"), load(b, 64, 16, "mfma")]
+dry.dry_fail({kernel!r}.encode())
+try:
+    run(hs, 16)
+    result = None
+except R.RancError as e:
+    result = [str(e), log()]
+""")
+    assert "out of memory" in message and ("several ticks" if kernel == "k_plain_whole" else "branches") in message
+    branches = {r[1] for r in rows if r[0] == "wait" and r[1] != 0}
+    joins = {r[1] for r in rows if r[0] == "record" and r[1] != 0 and ["wait", 0, r[2]] in rows}
+    assert len(branches) == 3 and joins == branches
