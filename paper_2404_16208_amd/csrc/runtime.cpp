@@ -1092,7 +1092,7 @@ static void set_plain_args(const ranc_net *net, BlockArgs &a)
 }
 
 static hipError_t queue_blocks(ranc_net *net, const uint32_t *base, int num_ticks, int k0, int T, const BlockPlan &bp,
-                               hipStream_t s, bool timed)
+                               hipStream_t s, ranc_net *timer)
 {
     const Plan &p = net->p;
     BlockArgs a;
@@ -1117,11 +1117,11 @@ static hipError_t queue_blocks(ranc_net *net, const uint32_t *base, int num_tick
         a.count = p.level_first[hi + 1] - a.first;
         a.step = st;
         int slot = -1;
-        e = timed ? prof_begin(net, 0, s, &slot) : hipSuccess;
+        e = timer ? prof_begin(timer, 0, s, &slot) : hipSuccess;
         if (e == hipSuccess)
             e = p.path == RANC_PATH_MFMA ? launch_integrate_mfma_ticks(net->dn, a, p.two, s) : launch_plain_ticks(net->dn, a, s);
-        if (e == hipSuccess && timed)
-            e = prof_end(net, slot, s);
+        if (e == hipSuccess && timer)
+            e = prof_end(timer, slot, s);
     }
     return e;
 }
@@ -1147,7 +1147,7 @@ static TickForm choose_form(const ranc_net *net, int num_ticks, bool fused, Bloc
 
 // Queue a call's ticks in the form chosen, if it is not tick by tick (without
 // the tick advance).
-static hipError_t queue_several(ranc_net *net, const uint32_t *base, int num_ticks, hipStream_t s, bool timed)
+static hipError_t queue_several(ranc_net *net, const uint32_t *base, int num_ticks, hipStream_t s, ranc_net *timer)
 {
     const Plan &p = net->p;
     BlockPlan bp;
@@ -1162,11 +1162,11 @@ static hipError_t queue_several(ranc_net *net, const uint32_t *base, int num_tic
         for (; e == hipSuccess && a.k0 < num_ticks; a.k0 += a.ticks) {
             a.ticks = std::min(num_ticks - a.k0, PLAIN_WHOLE_TICKS_MAX);
             int slot = -1;
-            e = timed ? prof_begin(net, 0, s, &slot) : hipSuccess;
+            e = timer ? prof_begin(timer, 0, s, &slot) : hipSuccess;
             if (e == hipSuccess)
                 e = launch_plain_whole(net->dn, a, s);
-            if (e == hipSuccess && timed)
-                e = prof_end(net, slot, s);
+            if (e == hipSuccess && timer)
+                e = prof_end(timer, slot, s);
         }
         return e;
     }
@@ -1174,7 +1174,7 @@ static hipError_t queue_several(ranc_net *net, const uint32_t *base, int num_tic
         const int T = std::min(p.seg_ticks, num_ticks - k);
         BlockPlan b = bp;
         b.block = std::min(b.block, T);
-        e = queue_blocks(net, base, num_ticks, k, T, b, s, timed);
+        e = queue_blocks(net, base, num_ticks, k, T, b, s, timer);
     }
     return e;
 }
@@ -1209,19 +1209,21 @@ static hipError_t queue_plain_tick(ranc_net *net, const uint32_t *base, int num_
 }
 
 // Queue num_ticks ticks on stream s: per tick the integration (and on the
-// plain path the router), then the device tick advance. With `timed`, HIP
-// event pairs are recorded around each launch while profiling is on. one_tick:
-// tick by tick even where several ticks would take one launch.
-static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_ticks, hipStream_t s, bool timed,
+// plain path the router), then the device tick advance. With `timer`,
+// HIP event pairs are recorded around each launch while that handle's profiling is
+// on (the handle's own or, in a batch, the first one's). one_tick: tick by tick even
+// where several ticks would take one launch.
+static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_ticks, hipStream_t s, ranc_net *timer,
                                bool one_tick = false)
 {
     const Plan &p = net->p;
     const size_t tick_words = (size_t)p.Cin * p.W;
-    timed = timed && net->prof.on;
+    if (timer && !timer->prof.on)
+        timer = nullptr;
     BlockPlan bp;
     const bool fused = p.size[R_RING8] && net->rcfg.lanes == route_split_lanes();
     if (!one_tick && choose_form(net, num_ticks, fused, bp) != FORM_TICKS) {
-        hipError_t e = queue_several(net, base, num_ticks, s, timed);
+        hipError_t e = queue_several(net, base, num_ticks, s, timer);
         if (e == hipSuccess)
             e = launch_advance_tick(net->dn, num_ticks, s);
         return e == hipSuccess ? RANC_OK : hip_fail(e, "launching integration (several ticks)");
@@ -1232,33 +1234,33 @@ static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_tick
         ta.ext_t = base ? base + (size_t)k * tick_words : nullptr;
         ta.ext_sstride = (long long)num_ticks * tick_words;
         // A long timed run folds finished event pairs in batches.
-        if (timed && net->prof.used.size() >= 4096) {
+        if (timer && timer->prof.used.size() >= 4096) {
             hipError_t e = hipStreamSynchronize(s);
             if (e == hipSuccess)
-                e = prof_collect(net);
+                e = prof_collect(timer);
             if (e != hipSuccess)
                 return hip_fail(e, "collecting kernel timings");
         }
         int slot = -1;
-        hipError_t e = timed ? prof_begin(net, 0, s, &slot) : hipSuccess;
+        hipError_t e = timer ? prof_begin(timer, 0, s, &slot) : hipSuccess;
         if (e == hipSuccess)
             e = fused                        ? queue_plain_tick(net, base, num_ticks, k, s)
                 : p.path == RANC_PATH_MFMA   ? launch_integrate_mfma(net->dn, ta, p.two, p.spw, mfma_compact(net), s)
                 : p.path == RANC_PATH_SPARSE ? launch_integrate_sparse(net->dn, ta, p.spw, s)
                                              : launch_integrate_plain(net->dn, ta, s);
-        if (e == hipSuccess && timed)
-            e = prof_end(net, slot, s);
+        if (e == hipSuccess && timer)
+            e = prof_end(timer, slot, s);
         if (e != hipSuccess)
             return hip_fail(e, "launching integration");
         // The MFMA path delivers spikes inside the next tick's integration
         // (spike history gathered by destination); the plain path routes
         // into the scheduler ring here, unless integration did.
         if (p.path == RANC_PATH_PLAIN && !fused) {
-            e = timed ? prof_begin(net, 1, s, &slot) : hipSuccess;
+            e = timer ? prof_begin(timer, 1, s, &slot) : hipSuccess;
             if (e == hipSuccess)
                 e = launch_route(net->dn, k, net->rcfg, s);
-            if (e == hipSuccess && timed)
-                e = prof_end(net, slot, s);
+            if (e == hipSuccess && timer)
+                e = prof_end(timer, slot, s);
             if (e != hipSuccess)
                 return hip_fail(e, "launching routing");
         }
@@ -1355,7 +1357,7 @@ static ranc_status run_captured(ranc_net *net, const uint32_t *base, int num_tic
         e = hipStreamBeginCapture(net->cap_stream, hipStreamCaptureModeThreadLocal);
         if (e != hipSuccess)
             return hip_fail(e, "beginning capture");
-        ranc_status st = queue_ticks(net, base, num_ticks, net->cap_stream, false);
+        ranc_status st = queue_ticks(net, base, num_ticks, net->cap_stream, nullptr);
         hipGraph_t graph = nullptr;
         e = hipStreamEndCapture(net->cap_stream, &graph);
         if (st != RANC_OK) {
@@ -1830,7 +1832,7 @@ static ranc_status queue_batch_branches(ranc_net *lead, const Batch &b, hipStrea
                 e = launch_fold_counts(b.mf[i].n, b.num_ticks, st);
         } else if (c < ph.g_num + (int)b.solo.size()) {
             const int i = b.solo[c - ph.g_num];
-            st_solo = queue_ticks(b.nets[i], b.bases[i], b.num_ticks, st, false);
+            st_solo = queue_ticks(b.nets[i], b.bases[i], b.num_ticks, st, nullptr);
         } else if (ph.pf_num > 0 && c == ph.g_num + (int)b.solo.size()) {
             for (int k = 0; e == hipSuccess && k < b.num_ticks; ++k)
                 e = launch_plain_ticks_batch(tpl + ph.pf_first, ph.pf_num, ph.pf_units, k, st);
@@ -1872,7 +1874,7 @@ static ranc_status queue_batch_ticks(ranc_net *lead, const Batch &b, hipStream_t
             return st;
     }
     for (int i : b.solo) {
-        const ranc_status st = branches ? RANC_OK : queue_ticks(b.nets[i], b.bases[i], b.num_ticks, s, false);
+        const ranc_status st = branches ? RANC_OK : queue_ticks(b.nets[i], b.bases[i], b.num_ticks, s, timed ? lead : nullptr);
         if (st != RANC_OK)
             return st;
     }
@@ -2297,7 +2299,7 @@ ranc_status ranc_run_ticks(ranc_net *const *nets, int32_t num_nets, const uint32
             return hip_fail(e, "moving the scheduled spikes");
         ranc_status st = (flags & RANC_RUN_RESIDENT) ? run_resident(nets[0], bases[0], num_ticks, s)
                          : (flags & RANC_RUN_GRAPH)  ? run_captured(nets[0], bases[0], num_ticks, s)
-                                                     : queue_ticks(nets[0], bases[0], num_ticks, s, true);
+                                                     : queue_ticks(nets[0], bases[0], num_ticks, s, nets[0]);
         if (st == RANC_OK && (e = leave_ring(nets[0], words, s)) != hipSuccess)
             st = hip_fail(e, "moving the scheduled spikes");
         if (st == RANC_ETIMEOUT) {   // the ticks ran partially: the call counts as run
@@ -2758,11 +2760,11 @@ ranc_status ranc_autotune(ranc_net *net, const uint32_t *inputs, uint32_t flags,
         net->rcfg = c.rc;
         // one untimed pass, then a timed pass, each from the initial state
         e = reset_state(net, s);
-        if (e == hipSuccess && (st = queue_ticks(net, base, num_ticks, s, false, one_tick)) == RANC_OK)
+        if (e == hipSuccess && (st = queue_ticks(net, base, num_ticks, s, nullptr, one_tick)) == RANC_OK)
             e = reset_state(net, s);
         if (e == hipSuccess && st == RANC_OK)
             e = hipEventRecord(e0, s);
-        if (e == hipSuccess && st == RANC_OK && (st = queue_ticks(net, base, num_ticks, s, false, one_tick)) == RANC_OK)
+        if (e == hipSuccess && st == RANC_OK && (st = queue_ticks(net, base, num_ticks, s, nullptr, one_tick)) == RANC_OK)
             e = hipEventRecord(e1, s);
         if (e == hipSuccess && st == RANC_OK)
             e = hipEventSynchronize(e1);

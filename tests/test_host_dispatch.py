@@ -123,3 +123,19 @@ except R.RancError as e:
     branches = {r[1] for r in rows if r[0] == "wait" and r[1] != 0}
     joins = {r[1] for r in rows if r[0] == "record" and r[1] != 0 and ["wait", 0, r[2]] in rows}
     assert len(branches) == 3 and joins == branches
+
+
+@pytest.mark.parametrize("path", ["plain", "mfma"])
+def test_profile_of_a_batch_counts_every_launch(dry, path):
+    """The first handle's profile holds the launches of all networks of a batch, of
+    those with launches of their own too (a large plain network; a feed-forward
+    one), and theirs hold none."""
+    first, other, queued = dry(f"""
+big = W.random_net(1, 64, 128, 128, 4, grid_w=8) if {path!r} == "plain" else forward_net(17, 4, 256, 256, 4, 9, 2)
+hs = [load(W.random_net(2, 3, 64, 64, 2, grid_w=3), 2, 8, "plain"), load(big, 64 if {path!r} == "mfma" else 20, 8, {path!r})]
+R.ranc_profile_enable(hs[0], True)
+rows = run(hs, 8)
+result = [R.ranc_profile_read(h)["integrate_launches"] for h in hs] + [kernels(rows)]
+""")
+    integrations = [k for k in queued if k.startswith(("k_plain_ticks", "k_integrate"))]
+    assert first == len(integrations) > 8 and other == 0
