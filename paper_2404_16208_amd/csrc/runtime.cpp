@@ -1011,6 +1011,15 @@ static hipError_t prof_collect(ranc_net *net)
     return hipSuccess;
 }
 
+// A long timed run folds finished event pairs in batches.
+static hipError_t prof_fold(ranc_net *net, hipStream_t s)
+{
+    if (net->prof.used.size() < 4096)
+        return hipSuccess;
+    const hipError_t r = hipStreamSynchronize(s);
+    return r == hipSuccess ? prof_collect(net) : r;
+}
+
 // How a call's segment of T ticks of a feed-forward network runs: `block`
 // ticks per launch and core (0: tick by tick), the levels one after another
 // (each the whole segment) or, `skewed`, all levels in each launch with level
@@ -1223,7 +1232,9 @@ static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_tick
     BlockPlan bp;
     const bool fused = p.size[R_RING8] && net->rcfg.lanes == route_split_lanes();
     if (!one_tick && choose_form(net, num_ticks, fused, bp) != FORM_TICKS) {
-        hipError_t e = queue_several(net, base, num_ticks, s, timer);
+        hipError_t e = timer ? prof_fold(timer, s) : hipSuccess;
+        if (e == hipSuccess)
+            e = queue_several(net, base, num_ticks, s, timer);
         if (e == hipSuccess)
             e = launch_advance_tick(net->dn, num_ticks, s);
         return e == hipSuccess ? RANC_OK : hip_fail(e, "launching integration (several ticks)");
@@ -1233,16 +1244,11 @@ static ranc_status queue_ticks(ranc_net *net, const uint32_t *base, int num_tick
         ta.k = k;
         ta.ext_t = base ? base + (size_t)k * tick_words : nullptr;
         ta.ext_sstride = (long long)num_ticks * tick_words;
-        // A long timed run folds finished event pairs in batches.
-        if (timer && timer->prof.used.size() >= 4096) {
-            hipError_t e = hipStreamSynchronize(s);
-            if (e == hipSuccess)
-                e = prof_collect(timer);
-            if (e != hipSuccess)
-                return hip_fail(e, "collecting kernel timings");
-        }
+        hipError_t e = timer ? prof_fold(timer, s) : hipSuccess;
+        if (e != hipSuccess)
+            return hip_fail(e, "collecting kernel timings");
         int slot = -1;
-        hipError_t e = timer ? prof_begin(timer, 0, s, &slot) : hipSuccess;
+        e = timer ? prof_begin(timer, 0, s, &slot) : hipSuccess;
         if (e == hipSuccess)
             e = fused                        ? queue_plain_tick(net, base, num_ticks, k, s)
                 : p.path == RANC_PATH_MFMA   ? launch_integrate_mfma(net->dn, ta, p.two, p.spw, mfma_compact(net), s)

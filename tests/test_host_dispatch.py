@@ -139,3 +139,15 @@ result = [R.ranc_profile_read(h)["integrate_launches"] for h in hs] + [kernels(r
 """)
     integrations = [k for k in queued if k.startswith(("k_plain_ticks", "k_integrate"))]
     assert first == len(integrations) > 8 and other == 0
+
+
+def test_profile_of_many_calls_keeps_few_events(dry):
+    """Profiling left on over many calls of several ticks per launch: the event
+    pairs are folded into the totals from time to time and reused."""
+    calls, events = dry("""
+h = load(W.random_net(1, 4, 64, 64, 2, grid_w=2), 1, 16, "plain")
+R.ranc_profile_enable(h, True)
+rows = [r for i in range(9000) for r in run(h, 16)]
+result = [R.ranc_profile_read(h)["integrate_launches"], len({r[2] for r in rows if r[0] == "record"})]
+""")
+    assert calls == 9000 and events <= 2 * 4097
