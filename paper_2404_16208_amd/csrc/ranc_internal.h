@@ -98,7 +98,7 @@ struct DevNet {
     const uint32_t *degb;
     const uint4 *planes;
     const uint32_t *rtx_ptr, *rtx_ent;
-    const uint64_t *hist_zero;   // HG zero words (a history row with no spikes)
+    const uint64_t *hist_zero;   // zeros: a history row with no spikes (HG words), A / 32 input words of none
     const uint32_t *ecsr_ptr;    // sparse path: row starts [C][slices][A+1]
     const uint16_t *ecsr_ent;    // sparse path: row entries (neuron in slice | weight << 7)
     // state

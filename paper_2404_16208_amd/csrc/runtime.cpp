@@ -479,7 +479,9 @@ ranc_status make_plan(const ranc_net_desc *d, int32_t S, int32_t RT, int32_t pat
     p.size[R_RTXPTR] = tiled ? (C * A + 1) * 4 : 0;
     p.size[R_RTXENT] = tiled ? std::max<size_t>((size_t)E, 1) * 4 : 0;
     const size_t HG = (size_t)p.S64 / 64;
-    p.size[R_HZERO] = tiled ? HG * 8 : 0;
+    // zeros: a history row (HG words), and the A / 32 input words of a core that
+    // takes none (kern_mfma_ticks.hip)
+    p.size[R_HZERO] = tiled ? std::max<size_t>(HG * 8, W * 4) : 0;
     p.size[R_DEGB] = mf ? C * p.slices * 2 * A : 0;
     p.size[R_OUTIDX] = tiled ? C * N * 4 : 0;
     // int8 weight planes: the B source when a core's samples take several
