@@ -304,6 +304,33 @@ bool one_tile_per_workgroup(const Plan &p, int tiles)
     return tiles == 2 || p.N == 64 || p.A <= 128 || (wide && p.A <= 256);
 }
 
+// Whether the MFMA path is the faster with 32 to 63 samples, where its time goes by
+// 64-sample tiles and the plain path's by samples. It is from 2^20 neurons times
+// samples on for most shapes. us per tick, plain and MFMA, 4 types: 128 cores of
+// 256 x 256 (9 bits) x 32 samples 12.5, 11.5; 200 of 128 x 128 x 40 11.5, 8.1; 512 of 64
+// x 64 x 32 9.9, 7.4; 48 of 512 x 512 x 40 15.7, 12.1 (2 types). B tiles that are
+// large beside a core's axons take nearly twice the size: 96 of 64 x 256 (9 bits) x 40
+// 10.0, 10.7, 168 x 48 14.7, 12.7; 48 of 128 x 512 x 40 11.0, 12.5, 80 x 48 16.2, 13.1;
+// 64 of 64 x 512 (8 bits) x 32 9.8, 11.2, 128 14.1, 12.8. So do feed-forward networks
+// of wide cores, whose plain launches of several ticks are as cheap: 80 of 256 x 256
+// (9 bits) x 48 5.6, 6.5, 168 9.0, 8.0; 64 of 512 x 512 (8 bits) x 32 5.8, 7.1, 128
+// 10.2, 7.9. The largest B tiles beside the axons (64 x 512, 9 bits), and feed-forward
+// cores of 512 axons and two planes, which the MFMA path runs tick by tick, take
+// nearly full tiles: 168 of 64 x 512 x 48 22.0, 26.4, 128 x 63 21.5, 15.8, 584 x 56 77.4,
+// 62.9; 168 of 512 x 512 (9 bits) x 48 17.4, 19.2, 128 x 63 18.2, 14.6.
+bool mfma_below_a_tile(const ranc_net_desc *d, const Plan &p)
+{
+    const long long size = (long long)p.C * p.N * p.S;
+    const int planes = p.two ? 2 : 1, spread = p.N * planes / p.A;
+    if (size < AUTO_MFMA_MIN_NEURONS)
+        return false;
+    Plan q = p;
+    const bool forward = p.RT > 1 && p.N * planes >= 512 && feed_forward_levels(d, q);
+    if (spread > 8 || (forward && !mfma_ticks_supported(p.A, p.N, p.two)))
+        return (p.S >= 61 && size >= 15LL << 18) || (p.S >= 56 && size >= 1LL << 23);
+    return size >= (spread > 4 || forward ? 15LL << 17 : AUTO_MFMA_MIN_NEURONS);
+}
+
 // level: what the layout may use memory for. PLAN_FULL: RANC_PATH_AUTO may take
 // the MFMA path below 64 samples; PLAN_FORMS: rings for several ticks per launch
 // and for launches without a router; PLAN_SMALL: neither.
@@ -330,14 +357,8 @@ ranc_status make_plan(const ranc_net_desc *d, int32_t S, int32_t RT, int32_t pat
     p.grid_h = d->grid_h;
     p.two = d->weight_bits > 8;
     if (path == RANC_PATH_AUTO) {
-        // From 64 samples on (one full tile) the MFMA path, whose time goes by
-        // tiles; from 32 on where the network has a million neurons times
-        // samples. us per tick, plain and MFMA: 128 cores of 256 x 256 with 23
-        // and 40 samples 11.5, 13.8 and 15.8, 13.8; 64 cores with 32 and 63 9.6,
-        // 11.9 and 14.1, 12.4; 512 with 40 and 63 42, 27 and 59, 27; 64 of 512 x
-        // 512 with 50 34, 15; four layers of 128 cores with 48 36, 7.6 (several
-        // ticks per launch). The other way 512 of 128 x 128 with 40: 22, 25.
-        const bool mid = level >= PLAN_FULL && S >= 32 && S < 64 && (long long)p.C * p.N * S >= AUTO_MFMA_MIN_NEURONS;
+        // from 64 samples on (one full tile) the MFMA path
+        const bool mid = level >= PLAN_FULL && S >= 32 && S < 64 && mfma_below_a_tile(d, p);
         path = (S >= 64 || mid) && mfma_shape_supported(p.A, p.N, p.two) ? RANC_PATH_MFMA : RANC_PATH_PLAIN;
         p.auto_mid = mid && path == RANC_PATH_MFMA;
     }
