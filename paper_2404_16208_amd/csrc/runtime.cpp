@@ -1080,10 +1080,16 @@ template <typename Launch> static BlockPlan cheapest_blocks(const Plan &p, int T
     return best;
 }
 
-// Plain path (k_plain_ticks), measured on 256 x 256 cores: a launch takes about
-// 4 us and 1 us per tick of a block while its workgroups fit the GPU.
+// Plain path (k_plain_ticks): a launch takes about 4 us and 1 us per tick of a
+// block while its workgroups fit the GPU. Fitted to cores of 256 x 256; over 16 core
+// shapes, 2 to 8 levels of 16 to 200 cores, 1 to 60 samples and 2 to 32 ticks the form
+// taken is within 12% of the fastest and at most 6% slower than tick by tick but
+// for two ticks of smaller cores (2 levels of 200 cores of 64 x 256 x 40 samples
+// 53 us tick by tick, 59; of 256 x 256 73, 67).
 static BlockPlan choose_plain_blocks(const Plan &p, int T)
 {
+    if (T == 2 && (p.A < 256 || p.N < 256))
+        return BlockPlan();
     auto launch = [&](long long cores, int ticks) {
         const double rounds = std::max(1.0, (double)cores * p.S * p.N / (256.0 * 1024));
         return 4.0 + rounds * (1.0 * ticks + 1.0);
@@ -1091,26 +1097,40 @@ static BlockPlan choose_plain_blocks(const Plan &p, int T)
     return cheapest_blocks(p, T, T * launch(p.C, 1), launch);
 }
 
-// MFMA path. Measured on
-// 256 x 256 cores with 9-bit weights: a launch of the multi-tick kernel takes
-// about 8 us to set up and, per tick, 2.2 us while its workgroups (core,
-// slice, 32 samples) have a CU each and 3.5 us per further two per CU; a
-// tick-by-tick launch 4 us and 7 us per (core, slice, 64 samples) and CU.
+// MFMA path, in us. A tick by itself: a chain that grows with the axons and the
+// B tiles, and per 256 workgroups of 64 samples (a CU each) the potentials (512
+// bytes per neuron) and the axons. A launch of several ticks: setting up, moving
+// potentials and B tiles per 512 workgroups of 32 samples, and per tick the time of
+// one workgroup on a CU, of two, or of as many rounds of two as there are (of one
+// with 512 axons, whose LDS leaves room for no more). Fitted to 14 core shapes
+// with one plane and two, 2 to 6 levels of 16 to 200 cores, 64 to 1000 samples and 2
+// to 32 ticks: the form taken is on average 0.5% slower than the fastest of
+// tick by tick, level after level and skewed, and at most 12%. (Constants
+// measured on 256 x 256 cores alone took up to 2.6 times as long as tick by tick: 2
+// ticks of 2 levels of 200 cores of 512 x 64 x 1000 samples 397 us, 152.)
 static BlockPlan choose_blocks(const Plan &p, int T)
 {
     if (!p.levels || T < 2)
         return BlockPlan();
-    auto launch = [&](long long cores, int ticks) {
-        const long long units = cores * p.slices * ((p.S + 31) / 32);
-        return units <= 256 ? 8.0 + 2.2 * ticks : 8.0 + (3.5 * ticks + 4.0) * ((units + 511) / 512);
-    };
     if (p.path == RANC_PATH_PLAIN)
         return choose_plain_blocks(p, T);
-    double cost = T * (4.0 + 7.0 * std::max(1.0, (double)p.C * p.slices * (p.S64 / 64) / 256.0));
-    return cheapest_blocks(p, T, cost, launch);
+    const int w = p.N / p.slices;   // neurons of a workgroup
+    const bool wide = w == 256;
+    const double A = p.A;
+    const int held = p.A == 512 ? 256 : 512;   // workgroups the GPU holds
+    const double one = 0.7 + 0.0008 * A + (wide ? 0.15 : 0.0) + (p.two ? 0.05 + 0.0006 * A : 0.0);
+    const double round = wide ? 1.35 + (p.two ? A / 640 : 0.0) : 0.6 + 0.0011 * A + (p.two && p.A >= 256 ? 0.1 : 0.0);
+    auto launch = [&](long long cores, int ticks) {
+        const long long units = cores * p.slices * ((p.S + 31) / 32);
+        const double tick = units <= 256 ? one : std::max(1.0, round * ((units + held - 1) / held));
+        return 4.0 + (1.5 + 0.013 * w + 0.016 * A) * units / 512 + tick * ticks;
+    };
+    const double chain = 3.3 + 0.004 * A + 0.006 * w + (p.two && wide ? 0.2 + 0.006 * A : 0.0);
+    const double per = 0.022 * w + 0.0018 * A + (p.two && wide ? 1.0 : 0.0) + (w == 128 && p.A >= 256 ? 0.7 : 0.0);
+    const double units = (double)p.C * p.slices * (p.S64 / 64);
+    return cheapest_blocks(p, T, 0.5 + T * (chain + per * std::max(0.0, units - 64) / 256), launch);
 }
 
-// Queue ticks [k0, k0 + T) of the call (T <= seg_ticks) in blocks.
 static void set_plain_args(const ranc_net *net, BlockArgs &a)
 {
     const Plan &p = net->p;
@@ -1123,6 +1143,7 @@ static void set_plain_args(const ranc_net *net, BlockArgs &a)
     a.want_spk = net->links_on ? 1 : 0;
 }
 
+// Queue ticks [k0, k0 + T) of the call (T <= seg_ticks) in blocks.
 static hipError_t queue_blocks(ranc_net *net, const uint32_t *base, int num_ticks, int k0, int T, const BlockPlan &bp,
                                hipStream_t s, ranc_net *timer)
 {

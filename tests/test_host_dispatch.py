@@ -178,3 +178,30 @@ for C, A, N, bits, S, forward, _ in {BELOW_A_TILE!r}:
     held.clear()
 """)
     assert got == [c[-1] for c in BELOW_A_TILE]
+
+
+# (path, axons, neurons, bits, levels, cores per level, samples, ticks, whether
+# several ticks per launch are the faster form as timed, by 20% or more)
+FORMS = [("mfma", 512, 64, 8, 2, 200, 1000, 2, False), ("mfma", 512, 64, 8, 2, 200, 200, 4, False),
+         ("mfma", 256, 64, 9, 2, 200, 1000, 2, False), ("mfma", 512, 128, 8, 2, 200, 200, 2, False),
+         ("mfma", 64, 256, 9, 3, 64, 300, 4, True), ("mfma", 128, 128, 9, 3, 64, 300, 4, True),
+         ("mfma", 256, 256, 9, 3, 64, 300, 4, True), ("mfma", 512, 128, 8, 2, 16, 1000, 4, True),
+         ("mfma", 512, 128, 8, 6, 64, 64, 16, True), ("mfma", 256, 256, 9, 4, 128, 100, 32, True),
+         ("plain", 64, 256, 9, 2, 200, 40, 2, False), ("plain", 256, 256, 9, 2, 200, 40, 4, True),
+         ("plain", 512, 512, 9, 4, 32, 1, 32, True)]
+
+
+def test_ticks_per_launch_of_feed_forward_networks(dry):
+    got = dry(f"""
+from tests.test_gpu_form_coverage import layers_net
+result = []
+for path, A, N, bits, levels, per, S, T, _ in {FORMS!r}:
+    h = load(layers_net(1, levels, per, A, N, 4, bits), S, T, path)
+    rows = run(h, T)
+    # (all of a launch's cores: tick by tick)
+    grids = {{int(r[3]) for r in rows if r[0] == "launch" and r[2] == "k_plain_ticks"}}
+    result.append("k_integrate_mfma_ticks" in kernels(rows) if path == "mfma" else grids != {{levels * per}})
+    R.ranc_free(h)
+    held.clear()
+""")
+    assert got == [f[-1] for f in FORMS]
