@@ -418,8 +418,7 @@ def bench_sweep(args, torch, np):
     """Uneven design-space sweep: 64 seeded network variants (cores 16..4096,
     axons and neurons 64..512, 2-8 axon types, 4-9 bit weights) with 64
     samples each, advanced together (graph replay; per tick one launch per
-    MFMA shape class and one integration and one routing launch for the
-    plain-path networks). Each network is loaded on both the MFMA and the
+    MFMA shape class and those of the plain-path networks). Each network is loaded on both the MFMA and the
     plain path, each handle's launch shape is autotuned, and the faster of
     the two (one 64-tick call each, timed) is the per-network choice; the
     batch of those choices and the all-MFMA batch are timed and the faster is

@@ -64,8 +64,9 @@ enum {
 
 /* Integration paths (fixed at load time; they differ in device data layout). */
 enum {
-    RANC_PATH_AUTO = 0,   /* pick per shape: the MFMA path from 64 samples on, and from 32 on where the
-                             network has 2^20 neurons times samples and the workspace holds it (such
+    RANC_PATH_AUTO = 0,   /* pick per shape: the MFMA path from 64 samples on, and from 32 on where it
+                             is the faster (from 2^20 neurons times samples on for most core
+                             shapes) and the workspace holds it (such
                              a handle also takes the plain path's launch shapes, without effect, and
                              no state-resident runs); else the plain path */
     RANC_PATH_PLAIN = 1,  /* per (core, sample) workgroups, crossbar words and popcounts */
@@ -204,6 +205,10 @@ ranc_status ranc_workspace_bytes(const ranc_net_desc *desc, int32_t num_samples,
  * instance to its initial state: potentials = v_init, empty schedulers,
  * tick 0. Synchronizes `stream` before returning. *out receives a handle
  * owned by the library until ranc_free.
+ * ranc_workspace_bytes gives the size of the fastest layout. A smaller workspace
+ * loads too, without what it has no room for (the rings that several ticks per
+ * launch and launches without a router need), with the same results; below the
+ * least the call returns RANC_ENOMEM with that size in its message.
  */
 ranc_status ranc_load_network(const ranc_net_desc *desc, int32_t num_samples,
                               int32_t max_ticks_per_call, int32_t path, void *workspace,

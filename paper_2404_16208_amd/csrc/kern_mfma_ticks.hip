@@ -15,10 +15,11 @@
 // the 512-core net at 1024 samples, 5.4 TB/s, the HBM read-modify-write
 // limit). Here potentials move once per block, and a tick is bound by issue:
 // per wavefront about 230 vector instructions and 32 MFMA of 32 cycles.
-// Measured on that net, 32 ticks per call: 220 -> 66 us per tick at 1024
-// samples, of it 55 per further tick and 11 for moving the potentials and
-// setting up (whole pass 7.77 -> 2.65 ms, of it 0.62 ms raster packing); 35 ->
-// 10 us at 100 samples (1.17 -> 0.33 ms).
+// Measured on that net, 32 ticks per call: 220 -> 64 us per tick at 1024
+// samples, of it 53 per further tick and 10 for moving the potentials and
+// setting up (509 us per level); 35 -> 9 us at 100 samples. With the packed
+// output raster 7.77 -> 2.13 ms and 1.17 -> 0.29 ms per call, of it 0.62 and 0.05
+// -> 0.09 and 0.01 for packing.
 //
 // Mapping: one workgroup per (core, neuron slice, 32-sample group), of 4
 // wavefronts that own 64 neurons each (two 32-neuron blocks; 32 neurons each
@@ -28,9 +29,9 @@
 // the axon operands come from LDS in two halves, and what is only summed over
 // the block (spike words, axon spike counts) lives in LDS: a register spilled
 // to memory in the loop makes its reload wait for the history loads in flight
-// (794 us per level of 128 cores, 1024 samples and 32 ticks, against 566).
-// One workgroup of 8 wavefronts per 64 samples, whose barrier stops the whole
-// CU, took 587.
+// (794 us per level of 128 cores, 1024 samples and 32 ticks, where the form
+// without spills took 566). One workgroup of 8 wavefronts per 64 samples, whose
+// barrier stops the whole CU, took 587 then.
 // The MFMA chain of one neuron block (16 of 32 cycles each) and the vector
 // work of the other are independent, so the loop pairs them and the two pipes
 // of a SIMD run side by side; with one barrier per tick:

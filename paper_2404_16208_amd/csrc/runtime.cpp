@@ -307,8 +307,8 @@ bool one_tile_per_workgroup(const Plan &p, int tiles)
 // Whether the MFMA path is the faster with 32 to 63 samples, where its time goes by
 // 64-sample tiles and the plain path's by samples. It is from 2^20 neurons times
 // samples on for most shapes. us per tick, plain and MFMA, 4 types: 128 cores of
-// 256 x 256 (9 bits) x 32 samples 12.5, 11.5; 200 of 128 x 128 x 40 11.5, 8.1; 512 of 64
-// x 64 x 32 9.9, 7.4; 48 of 512 x 512 x 40 15.7, 12.1 (2 types). B tiles that are
+// 256 x 256 (9 bits) x 32 samples 13.5, 11.5; 200 of 128 x 128 x 40 11.5, 8.1; 512 of 64
+// x 64 x 32 11.1, 7.9; 48 of 512 x 512 x 40 15.7, 12.1 (2 types). B tiles that are
 // large beside a core's axons take nearly twice the size: 96 of 64 x 256 (9 bits) x 40
 // 10.0, 10.7, 168 x 48 14.7, 12.7; 48 of 128 x 512 x 40 11.0, 12.5, 80 x 48 16.2, 13.1;
 // 64 of 64 x 512 (8 bits) x 32 9.8, 11.2, 128 14.1, 12.8. So do feed-forward networks
@@ -546,7 +546,9 @@ ranc_status make_plan(const ranc_net_desc *d, int32_t S, int32_t RT, int32_t pat
     return RANC_OK;
 }
 
-// 32 x 32 bit transpose: bit i of word j becomes bit j of word i.
+// 32 x 32 bit transpose: bit i of word j becomes bit j of word i, by the recursive
+// block exchange of H. S. Warren, Hacker's Delight, section 7-3 (transposing a bit
+// matrix), its loop indexes included.
 static void transpose_bits(uint32_t (&a)[32])
 {
     uint32_t m = 0x0000FFFFu;
@@ -787,7 +789,7 @@ void pack_params(const ranc_net_desc *d, const Plan &p, std::vector<uint8_t> &bu
                 }
     }
     if (p.size[R_PLAINDST]) {
-        // plain path: each neuron's scheduler byte and delay (C * A <= 2^26)
+        // plain path: each neuron's scheduler byte and delay (C * A < 2^28)
         uint32_t *dst = (uint32_t *)at(R_PLAINDST);
         for (size_t i = 0; i < (size_t)C * N; ++i) {
             const int c = (int)(i / N);

@@ -462,8 +462,9 @@ class RancNet:
 def run_batch(nets, inputs, num_ticks: int, graph: bool = False, persistent: bool = False):
     """Advance several RancNets together (ranc_run_ticks with num_nets > 1):
     per tick one launch per MFMA shape class, or one persistent work-queue
-    launch for all MFMA-path nets with ``persistent``, and one integration and
-    one routing launch for all plain-path nets. ``inputs``: one entry per net,
+    launch for all MFMA-path nets with ``persistent``, and one launch for the
+    small plain-path nets; nets that run several ticks per launch and large
+    plain-path nets have launches of their own. ``inputs``: one entry per net,
     each None or an array as for :meth:`RancNet.run`; the non-None entries must
     be all numpy arrays (host) or all CUDA tensors (device)."""
     flags = (RANC_RUN_GRAPH if graph else 0) | (RANC_BATCH_PERSISTENT if persistent else 0)
