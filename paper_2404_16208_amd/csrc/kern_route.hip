@@ -400,23 +400,49 @@ __global__ void k_fill_u32(uint32_t *p, size_t count)
         p[i] = 0u;
 }
 
-hipError_t launch_reset_state(const DevNet &n, const LinkArgs &l, uint8_t *ring8, hipStream_t st)
+// The slots of both rings that can hold spikes between calls: those of the next D
+// ticks and, in the byte ring, the one before, which the next tick would clear. A
+// feed-forward network's rings have 32 more (512 cores of 256 x 256 x 63 samples: a
+// reset of all slots took 95 us, of these 41).
+__global__ __launch_bounds__(256) void k_clear_slots(DevNet n, uint8_t *ring8)
 {
+    const size_t words = (size_t)n.S * n.C * n.W;   // of the bit ring's slot; 8 times that in the byte ring's
+    const size_t total = words * (n.D + 1);
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
+        const int q = (n.tick[0] + n.Q - 1 + (int)(i / words)) % n.Q;
+        const size_t at = q * words + i % words;
+        n.ring[at] = 0u;
+        uint4 *b = reinterpret_cast<uint4 *>(ring8 + at * 32);
+        b[0] = b[1] = uint4{0u, 0u, 0u, 0u};
+    }
+}
+
+hipError_t launch_reset_state(const DevNet &n, const LinkArgs &l, uint8_t *ring8, bool all, hipStream_t st)
+{
+    if (n.Q < n.D + (ring8 ? 2 : 1))
+        return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_reset_potentials, dim3(2048), dim3(256), 0, st, n);
     const bool hist = n.vlayout != VLAYOUT_CSN;
-    const size_t ring_words = hist ? 0 : (size_t)n.Q * n.S * n.C * n.W;
+    const bool slots = !all && ring8;   // (the device tick is reset last)
+    const size_t ring_words = hist || slots ? 0 : (size_t)n.Q * n.S * n.C * n.W;
     const size_t spk_words = hist ? 0 : (size_t)n.S * n.C * n.NW;
-    const size_t hist_words = hist ? (size_t)n.Q * n.C * n.N * (n.S64 / 64) * 2 : 0;
+    // the history that the first ticks read: slots Q - D to Q - 1; the others are
+    // written before they are read (but for halves of padding samples, zero since `all`)
+    const int hist_slots = all ? n.Q : n.D;
+    const size_t slot_words = (size_t)n.C * n.N * (n.S64 / 64) * 2;
+    const size_t hist_words = hist ? hist_slots * slot_words : 0;
     const size_t raster_words = hist ? (size_t)n.RT * n.Nout * (n.S64 / 64) * 2 : (size_t)n.RT * n.S * n.Wout;
     const size_t cnt_words = (size_t)n.C * n.cnt_rows * n.S * CNT_N * 2;
     if (ring_words)
         hipLaunchKernelGGL(k_fill_u32, dim3(2048), dim3(256), 0, st, n.ring, ring_words);
-    if (ring8)   // (A is a multiple of 64)
+    if (slots)
+        hipLaunchKernelGGL(k_clear_slots, dim3(2048), dim3(256), 0, st, n, ring8);
+    else if (ring8)   // (A is a multiple of 64)
         hipLaunchKernelGGL(k_fill_u32, dim3(2048), dim3(256), 0, st, (uint32_t *)ring8, (size_t)n.Q * n.S * n.C * n.A / 4);
     if (spk_words)
         hipLaunchKernelGGL(k_fill_u32, dim3(1024), dim3(256), 0, st, n.spk, spk_words);
     if (hist_words)
-        hipLaunchKernelGGL(k_fill_u32, dim3(2048), dim3(256), 0, st, (uint32_t *)n.hist, hist_words);
+        hipLaunchKernelGGL(k_fill_u32, dim3(2048), dim3(256), 0, st, (uint32_t *)n.hist + (n.Q - hist_slots) * slot_words, hist_words);
     if (raster_words)
         hipLaunchKernelGGL(k_fill_u32, dim3(1024), dim3(256), 0, st, n.raster, raster_words);
     hipLaunchKernelGGL(k_fill_u32, dim3(1024), dim3(256), 0, st, (uint32_t *)n.cnt, cnt_words);

@@ -320,7 +320,9 @@ hipError_t launch_mfma_resident(const DevNet &n, const ResidentArgs &ra, const R
 int resident_blocks_per_cu(int A, int two_planes, int ext);   // 0: the shape is not built
 int resident_max_cores_per_wg();
 hipError_t launch_route(const DevNet &n, int k, const RouteCfg &cfg, hipStream_t st);
-hipError_t launch_reset_state(const DevNet &n, const LinkArgs &l, uint8_t *ring8, hipStream_t st);   // ring8 or nullptr
+// ring8 or nullptr; all: every slot of the rings and of the history, whatever they
+// hold (after loading), else those that can hold what is still to be delivered
+hipError_t launch_reset_state(const DevNet &n, const LinkArgs &l, uint8_t *ring8, bool all, hipStream_t st);
 hipError_t launch_advance_tick(const DevNet &n, int num_ticks, hipStream_t st);
 hipError_t launch_fold_counts(const DevNet &n, int num_ticks, hipStream_t st);
 hipError_t launch_link_counts(const DevNet &n, const LinkArgs &l, int k, hipStream_t st);

@@ -969,6 +969,7 @@ struct ranc_net {
     bool state_lost = false;           // a state-resident launch gave up: state undefined until reset
     bool ring_words = false;           // the scheduled spikes are in the bit ring, not the byte ring (enter_ring)
     bool recorded = false;             // a caller's own graph holds runs of this handle
+    bool slots_unsure = true;          // any slot of the rings may hold spikes (reset_state)
 };
 
 // MFMA path: whether this network's launches build their B tiles from the
@@ -986,10 +987,23 @@ static int auto_lanes(const ranc_net *net, const RouteCfg &rc)
     return net->p.size[R_RING8] ? route_split_lanes() : route_auto_lanes(net->dn, rc);
 }
 
-// Every instance to its initial state.
+static bool is_recording(hipStream_t s)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    return s && hipStreamIsCapturing(s, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
+}
+
+// Every instance to its initial state. A workspace just loaded, or left by a call
+// that failed, may hold spikes in any slot, as may one when a recorded reset is
+// replayed.
 static hipError_t reset_state(ranc_net *net, hipStream_t s)
 {
-    return launch_reset_state(net->dn, net->lk, net->p.size[R_RING8] ? net->ws + net->p.off[R_RING8] : nullptr, s);
+    const bool recording = is_recording(s), all = net->slots_unsure || recording;
+    const hipError_t e =
+        launch_reset_state(net->dn, net->lk, net->p.size[R_RING8] ? net->ws + net->p.off[R_RING8] : nullptr, all, s);
+    if (e == hipSuccess && !recording)
+        net->slots_unsure = false;
+    return e;
 }
 
 static hipError_t prof_begin(ranc_net *net, int kind, hipStream_t s, int *slot)
@@ -1351,11 +1365,6 @@ static hipError_t move_ring(ranc_net *net, bool words, hipStream_t s, bool recor
     if (e == hipSuccess && !recording)
         net->ring_words = words;
     return e;
-}
-static bool is_recording(hipStream_t s)
-{
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    return s && hipStreamIsCapturing(s, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
 }
 static hipError_t enter_ring(ranc_net *net, bool words, hipStream_t s)
 {
@@ -2342,13 +2351,18 @@ ranc_status ranc_run_ticks(ranc_net *const *nets, int32_t num_nets, const uint32
     if (num_nets > 1) {
         ranc_status st = run_batch(nets, num_nets, bases.data(), num_ticks, (flags & RANC_RUN_GRAPH) != 0,
                                    (flags & RANC_BATCH_PERSISTENT) != 0, s);
-        if (st != RANC_OK)
+        if (st != RANC_OK) {
+            for (int i = 0; i < num_nets; ++i)
+                nets[i]->slots_unsure = true;
             return st;
+        }
     } else {
         const bool words = wants_words(nets[0]);
         hipError_t e = enter_ring(nets[0], words, s);
-        if (e != hipSuccess)
+        if (e != hipSuccess) {
+            nets[0]->slots_unsure = true;
             return hip_fail(e, "moving the scheduled spikes");
+        }
         ranc_status st = (flags & RANC_RUN_RESIDENT) ? run_resident(nets[0], bases[0], num_ticks, s)
                          : (flags & RANC_RUN_GRAPH)  ? run_captured(nets[0], bases[0], num_ticks, s)
                                                      : queue_ticks(nets[0], bases[0], num_ticks, s, nets[0]);
@@ -2359,8 +2373,10 @@ ranc_status ranc_run_ticks(ranc_net *const *nets, int32_t num_nets, const uint32
             nets[0]->last_stream = s;
             ++nets[0]->version;
         }
-        if (st != RANC_OK)
+        if (st != RANC_OK) {
+            nets[0]->slots_unsure = true;
             return st;
+        }
     }
     for (int i = 0; i < num_nets; ++i) {
         nets[i]->tick += num_ticks;
@@ -2835,6 +2851,8 @@ ranc_status ranc_autotune(ranc_net *net, const uint32_t *inputs, uint32_t flags,
     p.spw = best_c.spw;
     net->rcfg = best_c.rc;
     net->prof.on = prof_on;
+    if (st != RANC_OK || e != hipSuccess)
+        net->slots_unsure = true;
     if (st != RANC_OK)
         return st;
     if (e == hipSuccess)

@@ -25,13 +25,15 @@ void note(const char *what, void *stream, const std::string &rest)
     log_text += head + rest + "\n";
 }
 
-int launch(const char *what, const void *f, unsigned gx, unsigned gy, void *stream)
+int launch(const char *what, const void *f, unsigned gx, unsigned gy, void *stream, void **args = nullptr)
 {
     const std::string &name = kernels[f];
     if (!fail_name.empty() && name.find(fail_name) != std::string::npos)
         return last_error = 2;   // hipErrorOutOfMemory
     ++launches;
-    note(what, stream, name + " " + std::to_string(gx) + " " + std::to_string(gy));
+    const bool fill = args && name.find("k_fill_u32") != std::string::npos;   // (its number of words)
+    note(what, stream, name + " " + std::to_string(gx) + " " + std::to_string(gy) +
+                           (fill ? " " + std::to_string(*(const size_t *)args[1]) : ""));
     return 0;
 }
 
@@ -64,7 +66,7 @@ int __hipPopCallConfiguration(Dim *g, Dim *b, size_t *shared, void **s)
     *g = c.grid; *b = c.block; *shared = c.shared; *s = c.stream;
     return 0;
 }
-int hipLaunchKernel(const void *f, Dim g, Dim, void **, size_t, void *s) { return launch("launch", f, g.x, g.y, s); }
+int hipLaunchKernel(const void *f, Dim g, Dim, void **args, size_t, void *s) { return launch("launch", f, g.x, g.y, s, args); }
 int hipLaunchCooperativeKernel(const void *f, Dim g, Dim, void **, unsigned, void *s) { return launch("launch", f, g.x, g.y, s); }
 int hipGetLastError() { const int e = last_error; last_error = 0; return e; }
 const char *hipGetErrorString(int e) { return e == 0 ? "no error" : e == 2 ? "out of memory" : "some error"; }

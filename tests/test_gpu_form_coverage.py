@@ -212,3 +212,34 @@ def test_forms_among_replays_of_a_callers_graph():
             for c, v in g.counters(s).items():
                 assert v == ref[s]["counters"][c], (s, c)
         g.close()
+
+
+@pytest.mark.parametrize("case", ["whole", "ticks", "words", "blocks", "mfma_blocks", "mfma", "sparse"])
+def test_reset_after_calls_of_every_form(case):
+    """From the state that a call leaves (spikes scheduled up to 15 ticks ahead, at
+    several ring positions) a reset gives the initial one."""
+    import torch
+    from paper_2404_16208_amd.ranc import RancNet
+    path = "mfma" if case.startswith("mfma") else "sparse" if case == "sparse" else "plain"
+    if case.endswith("blocks"):
+        net = layers_net(7, 3, 8, 128, 256, 4, max_delay=15)
+    else:
+        net = W.random_net(32, 40 if case in ("ticks", "words") else 6, 128, 128, 4, max_delay=15, grid_w=2, density=0.25,
+                           p_core=0.85, p_out=0.1, config_id=874)
+    S, T = 70 if path != "plain" else 5, 19
+    x = W.bernoulli_inputs(3, net, S, T, 0.2, config_id=874)
+    ref = oracle_results(net, x, T, [0, S - 1])
+    xd = torch.from_numpy(x.view(np.int32)).cuda()
+    g = RancNet(net, S, T, path=path, workspace_fill=0xA5)
+    if case == "words":
+        g.launch_shape(dict(g.launch_shape(), route_lanes_per_word=1))
+    for first in (0, 19, 13, 1):
+        log(f"[reset] {case} after {first} ticks")
+        if first:
+            g.run(xd[:, :first].contiguous(), first, graph=first == 13)
+        g.reset()
+        g.run(xd, T)
+        for s, r in ref.items():
+            assert_sample_equal(g, r, s, T, what=f"{case} after {first}")
+        g.reset()
+    g.close()

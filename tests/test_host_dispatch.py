@@ -205,3 +205,43 @@ for path, A, N, bits, levels, per, S, T, _ in {FORMS!r}:
     held.clear()
 """)
     assert got == [f[-1] for f in FORMS]
+
+
+@pytest.mark.parametrize("path,S", [("plain", 20), ("mfma", 64)])
+def test_reset_clears_what_can_hold_spikes(dry, path, S):
+    """A reset of a feed-forward network clears the scheduler slots (or history) of
+    the next max_delay ticks, not the slots that blocks of ticks need beside them;
+    all of them after loading, after a call that failed and when recorded."""
+    loaded, reset, failed, recorded, again = dry(f"""
+net = forward_net(17, 30, 64, 256, 4, 9, 6)
+d = R.Desc(net)
+n = R.ranc_workspace_bytes(d, {S}, 32, R.PATHS[{path!r}])
+ws = np.zeros(n + 256, np.uint8)
+h = R.ranc_load_network(d, {S}, 32, R.PATHS[{path!r}], -(-ws.ctypes.data // 256) * 256, n, 0)
+def cleared(rows):
+    return [sum(int(r[5]) for r in rows if r[2] == "k_fill_u32"), [r[2] for r in rows].count("k_clear_slots")]
+def reset(stream=0):
+    R.ranc_reset_state(h, stream)
+    return cleared(log())
+result = [cleared(log()), reset()]
+dry.dry_fail(b"k_")
+try:
+    run(h, 3)
+except R.RancError:
+    pass
+dry.dry_fail(b"")
+log()
+result.append(reset())
+dry.dry_capturing(1)
+result.append(reset(7))
+dry.dry_capturing(0)
+result.append(reset())
+""")
+    C, A, N, D = 30, 64, 256, 4
+    if path == "plain":
+        ring = (D + 1 + 32) * S * C * A
+        assert loaded[0] - reset[0] == ring // 4 + ring // 32   # (bytes, and one bit each)
+        assert [x[1] for x in (loaded, reset, failed, recorded, again)] == [0, 1, 0, 0, 1]
+    else:
+        assert loaded[0] - reset[0] == 32 * C * N * (S // 64) * 2
+    assert failed == recorded == loaded and again == reset
