@@ -404,8 +404,9 @@ ranc_status ranc_get_launch_shape(const ranc_net *net, ranc_tune *out);
  * goes to the current device's. Allocates no device memory and calls no
  * allocating HIP or library routine.
  * Errors: RANC_ENOMEM if the network, num_samples and max_ticks_per_call
- * need more than RANC_STATIC_WORKSPACE_BYTES (ranc_workspace_bytes gives the
- * need); RANC_ESTATE while another handle loaded this way on the same device
+ * need more than RANC_STATIC_WORKSPACE_BYTES in the smallest layout (the message
+ * names the need; a smaller workspace than ranc_workspace_bytes gives loads as
+ * above); RANC_ESTATE while another handle loaded this way on the same device
  * has not been freed (one handle per device at a time; ranc_free releases the
  * workspace); RANC_EUNSUPPORTED for a device index >= 64; otherwise as
  * ranc_load_network. The workspace keeps what the previous handle left in

@@ -10,12 +10,11 @@
 // axon type selects the neuron's weight). Spikes are gathered with a
 // wavefront ballot into 32-bit words; output-bus spikes go to the raster.
 //
-// Two forms. With many (core, sample) pairs (k_integrate_plain, and the batched
-// k_integrate_plain_batch) the spikes go out as words and the router kernels
-// (kern_route.hip) deliver them. With few (k_plain_ticks; a launch that does
-// not fill the GPU costs its latency, about 4 us, whatever it does) one kernel
-// does the whole tick: every firing lane stores its spike in the destination's
-// scheduler itself.
+// Two forms. On handles with the byte ring one kernel does the whole tick
+// (k_plain_ticks, and k_plain_ticks_batch): every firing lane stores its spike
+// in the destination's scheduler itself. On the others, and where a router is asked
+// for (k_integrate_plain, k_integrate_plain_batch), the spikes go out as words and
+// the router kernels (kern_route.hip) deliver them.
 #include <algorithm>
 
 #include "kern_bits.h"

@@ -1,5 +1,5 @@
-// kern_plain_whole.hip -- all ticks of a call for a small network, one
-// workgroup per sample.
+// kern_plain_whole.hip -- all ticks of a call (2^16 per launch at most) for a
+// small network, one workgroup per sample.
 //
 // A network of up to PLAIN_WHOLE_NEURONS neurons fits one CU: its crossbar
 // columns, weights, parameters and potentials stay in registers (up to 4
