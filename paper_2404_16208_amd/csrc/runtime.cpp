@@ -304,31 +304,63 @@ bool one_tile_per_workgroup(const Plan &p, int tiles)
     return tiles == 2 || p.N == 64 || p.A <= 128 || (wide && p.A <= 256);
 }
 
+// Plain path: words per axon type of the columns sorted by type, 0: natural order
+// (columns so large that they come from memory every tick, or too many words).
+int plain_sorted_columns(const ranc_net_desc *d, const Plan &p)
+{
+    int longest = 0;
+    for (int c = 0; c < p.C; ++c) {
+        int count[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        for (int a = 0; a < p.A; ++a)
+            longest = std::max(longest, ++count[d->axon_type[(size_t)c * p.A + a]]);
+    }
+    const int pw = plain_sorted_words(p.G, longest);
+    return p.G * pw <= 2 * p.W && (long long)p.C * p.N <= PLAIN_SORTED_MAX_NEURONS ? pw : 0;
+}
+
 // Whether the MFMA path is the faster with 32 to 63 samples, where its time goes by
 // 64-sample tiles and the plain path's by samples. It is from 2^20 neurons times
-// samples on for most shapes. us per tick, plain and MFMA, 4 types: 128 cores of
-// 256 x 256 (9 bits) x 32 samples 13.5, 11.5; 200 of 128 x 128 x 40 11.5, 8.1; 512 of 64
-// x 64 x 32 11.1, 7.9; 48 of 512 x 512 x 40 15.7, 12.1 (2 types). B tiles that are
-// large beside a core's axons take nearly twice the size: 96 of 64 x 256 (9 bits) x 40
-// 10.0, 10.7, 168 x 48 14.7, 12.7; 48 of 128 x 512 x 40 11.0, 12.5, 80 x 48 16.2, 13.1;
-// 64 of 64 x 512 (8 bits) x 32 9.8, 11.2, 128 14.1, 12.8. So do feed-forward networks
-// of wide cores, whose plain launches of several ticks are as cheap: 80 of 256 x 256
-// (9 bits) x 48 5.6, 6.5, 168 9.0, 8.0; 64 of 512 x 512 (8 bits) x 32 5.8, 7.1, 128
-// 10.2, 7.9. The largest B tiles beside the axons (64 x 512, 9 bits), and feed-forward
-// cores of 512 axons and two planes, which the MFMA path runs tick by tick, take
-// nearly full tiles: 168 of 64 x 512 x 48 22.0, 26.4, 128 x 63 21.5, 15.8, 584 x 56 77.4,
-// 62.9; 168 of 512 x 512 (9 bits) x 48 17.4, 19.2, 128 x 63 18.2, 14.6.
+// samples on for most shapes (us per tick, plain and MFMA, 4 types: 128 cores of 256 x
+// 256 (9 bits) x 32 samples 13.5, 11.5; 200 of 128 x 128 x 40 11.5, 8.1; 512 of 64 x 64 x
+// 32 11.1, 7.9), but:
+// - B tiles large beside a core's axons (64 x 256 and 128 x 512 with two planes, 64 x
+//   512 with one) cost: MFMA is 0.8 to 1.0 times as fast at 2^20, 0.95 to 1.14 at
+//   1.3 * 2^20, 1.03 and more from 1.5 * 2^20 on. 64 x 512 with two planes fill the GPU
+//   with 256 workgroups: up to there 0.7 at 2^20, 0.95 to 1.05 at 1.7 * 2^20, 1.2 to 1.5
+//   at 3 * 2^20 (56 samples); past it 0.65 to 0.95 with 32 and 44 samples and 1.1 to 1.5
+//   with 56 and 63 from 4.5 * 2^20 on (eight types: from 44 samples on).
+// - feed-forward networks of wide cores, whose plain launches of several ticks are
+//   cheap: 256 x 256 (9 bits) and 512 x 512 (8 bits) 0.75 to 1.0 at 2^20, 0.93 to 1.2
+//   at 1.3 * 2^20. With 512 axons and two planes the MFMA path runs them tick by
+//   tick: 512 x 256 1.2 at 2^21 x 63 samples, 1.1 at 3 * 2^20 x 56, 1.1 at 4 * 2^20 x 44;
+//   512 x 512 1.05 at 2^21 x 63, 1.1 at 6 * 2^20 x 56, 0.7 with 32.
+// The plain path's cost counts as that of a larger network where it is the higher:
+// 512 axons of one or two types (1.3 times), and columns in natural order (one AND
+// and population count per word and type, where sorted columns take at most 24: 384
+// cores of 512 x 512 with 8 types 93 us, sorted 25).
 bool mfma_below_a_tile(const ranc_net_desc *d, const Plan &p)
 {
-    const long long size = (long long)p.C * p.N * p.S;
     const int planes = p.two ? 2 : 1, spread = p.N * planes / p.A;
+    double size = (double)p.C * p.N * p.S;
     if (size < AUTO_MFMA_MIN_NEURONS)
         return false;
+    if (p.A == 512 && p.G <= 2)
+        size *= 1.3;
+    if (!plain_sorted_columns(d, p))
+        size *= std::max(1.0, p.W * p.G / 24.0);
     Plan q = p;
     const bool forward = p.RT > 1 && p.N * planes >= 512 && feed_forward_levels(d, q);
-    if (spread > 8 || (forward && !mfma_ticks_supported(p.A, p.N, p.two)))
-        return (p.S >= 61 && size >= 15LL << 18) || (p.S >= 56 && size >= 1LL << 23);
-    return size >= (spread > 4 || forward ? 15LL << 17 : AUTO_MFMA_MIN_NEURONS);
+    if (forward && !mfma_ticks_supported(p.A, p.N, p.two)) {
+        double least = 1 << 21;
+        for (int i = 0; i < p.N / 128; ++i)
+            least *= 64.0 / p.S;
+        return size >= least;
+    }
+    if (spread > 8 && p.C * mfma_slices(p.A, p.N, p.two) <= 256)
+        return size >= 3 << 19;
+    if (spread > 8)
+        return size >= 9 << 19 && p.S >= (p.G == 8 ? 40 : 52);
+    return size >= (spread > 4 || forward ? 5 << 18 : AUTO_MFMA_MIN_NEURONS);
 }
 
 // level: what the layout may use memory for. PLAN_FULL: RANC_PATH_AUTO may take
@@ -390,17 +422,7 @@ ranc_status make_plan(const ranc_net_desc *d, int32_t S, int32_t RT, int32_t pat
             p.seg_ticks = seg;
             p.Q = p.D + 1 + seg;
         }
-        // columns sorted by axon type, unless so large that they come from
-        // memory every tick
-        int longest = 0;
-        for (int c = 0; c < p.C; ++c) {
-            int count[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-            for (int a = 0; a < p.A; ++a)
-                longest = std::max(longest, ++count[d->axon_type[(size_t)c * p.A + a]]);
-        }
-        const int pw = plain_sorted_words(p.G, longest);
-        if (p.G * pw <= 2 * p.W && (long long)p.C * p.N <= PLAIN_SORTED_MAX_NEURONS)
-            p.sorted_words = pw;
+        p.sorted_words = plain_sorted_columns(d, p);
     }
     p.slices = path == RANC_PATH_MFMA ? mfma_slices(p.A, p.N, p.two)
              : path == RANC_PATH_SPARSE ? p.N / sparse_slice_width(p.N) : 1;

@@ -153,26 +153,30 @@ result = [R.ranc_profile_read(h)["integrate_launches"], len({r[2] for r in rows 
     assert calls == 9000 and events <= 2 * 4097
 
 
-# (cores, axons, neurons, bits, samples, feed-forward, path): the faster one as
+# (cores, axons, neurons, bits, samples, types, feed-forward, path): the faster one as
 # timed, on both sides of each line of the rule below 64 samples
-BELOW_A_TILE = [(200, 128, 128, 9, 42, False, "mfma"), (128, 256, 256, 9, 32, False, "mfma"), (127, 256, 256, 9, 32, False, "plain"),
-                (128, 64, 256, 9, 32, False, "plain"), (256, 64, 256, 9, 32, False, "mfma"), (128, 64, 256, 8, 32, False, "mfma"),
-                (60, 128, 512, 9, 40, False, "plain"), (128, 128, 512, 9, 32, False, "mfma"), (64, 128, 512, 8, 32, False, "mfma"),
-                (64, 64, 512, 8, 32, False, "plain"), (128, 64, 512, 8, 32, False, "mfma"), (256, 64, 512, 9, 32, False, "plain"),
-                (128, 64, 512, 9, 63, False, "mfma"), (584, 64, 512, 9, 56, False, "mfma"),
-                (88, 256, 256, 9, 48, True, "plain"), (158, 256, 256, 9, 48, True, "plain"), (168, 256, 256, 9, 48, True, "mfma"),
-                (128, 256, 256, 8, 32, True, "mfma"), (64, 512, 512, 8, 32, True, "plain"), (128, 512, 512, 8, 32, True, "mfma"),
-                (168, 512, 512, 9, 48, True, "plain"), (64, 512, 512, 9, 48, False, "mfma"), (336, 512, 128, 9, 48, True, "mfma")]
+BELOW_A_TILE = [(200, 128, 128, 9, 42, 4, False, "mfma"), (128, 256, 256, 9, 32, 4, False, "mfma"), (127, 256, 256, 9, 32, 4, False, "plain"),
+                (128, 64, 256, 9, 32, 4, False, "plain"), (205, 64, 256, 9, 32, 4, False, "mfma"), (128, 64, 256, 8, 32, 4, False, "mfma"),
+                (61, 128, 512, 9, 40, 4, False, "plain"), (103, 128, 512, 9, 32, 4, False, "mfma"), (64, 128, 512, 8, 32, 4, False, "mfma"),
+                (64, 64, 512, 8, 32, 4, False, "plain"), (103, 64, 512, 8, 32, 4, False, "mfma"),
+                (64, 64, 512, 9, 32, 4, False, "plain"), (98, 64, 512, 9, 63, 8, False, "mfma"), (124, 64, 512, 9, 63, 8, False, "mfma"),
+                (192, 64, 512, 9, 32, 4, False, "plain"), (256, 64, 512, 9, 32, 8, False, "plain"), (220, 64, 512, 9, 56, 4, False, "mfma"),
+                (373, 64, 512, 9, 44, 8, False, "mfma"), (373, 64, 512, 9, 44, 4, False, "plain"),
+                (72, 256, 256, 9, 56, 4, True, "plain"), (116, 256, 256, 9, 56, 4, True, "mfma"), (164, 256, 256, 9, 32, 4, True, "mfma"),
+                (64, 512, 512, 8, 32, 4, True, "plain"), (64, 512, 512, 8, 32, 2, True, "mfma"), (84, 512, 512, 8, 32, 4, True, "mfma"),
+                (128, 512, 512, 9, 63, 4, True, "mfma"), (256, 512, 512, 9, 32, 4, True, "plain"), (184, 512, 512, 9, 44, 4, True, "plain"),
+                (220, 512, 256, 9, 56, 4, True, "mfma"), (256, 512, 256, 9, 32, 4, True, "plain"),
+                (64, 512, 512, 9, 48, 4, False, "mfma"), (336, 512, 128, 9, 48, 4, True, "mfma")]
 
 
 def test_automatic_path_below_a_tile(dry):
     got = dry(f"""
-def net(C, A, N, bits, forward):
-    n = W.random_net(1, C, A, N, 4, weight_bits=bits, grid_w=C, density=0.0, p_core=0.0 if forward else 0.5, config_id=873)
+def net(C, A, N, bits, G, forward):
+    n = W.random_net(1, C, A, N, G, weight_bits=bits, grid_w=C, density=0.0, p_core=0.0 if forward else 0.5, config_id=873)
     return n
 result = []
-for C, A, N, bits, S, forward, _ in {BELOW_A_TILE!r}:
-    h = load(net(C, A, N, bits, forward), S, 16, "auto")
+for C, A, N, bits, S, G, forward, _ in {BELOW_A_TILE!r}:
+    h = load(net(C, A, N, bits, G, forward), S, 16, "auto")
     result.append({{1: "plain", 2: "mfma"}}[R.ranc_get_path(h)])
     R.ranc_free(h)
     held.clear()
