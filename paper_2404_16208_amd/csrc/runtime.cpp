@@ -1137,15 +1137,18 @@ static BlockPlan choose_plain_blocks(const Plan &p, int T)
 
 // MFMA path, in us. A tick by itself: a chain that grows with the axons and the
 // B tiles, and per 256 workgroups of 64 samples (a CU each) the potentials (512
-// bytes per neuron) and the axons. A launch of several ticks: setting up, moving
+// bytes per neuron) and the axons. A launch of several ticks: that chain once, moving
 // potentials and B tiles per 512 workgroups of 32 samples, and per tick the time of
 // one workgroup on a CU, of two, or of as many rounds of two as there are (of one
 // with 512 axons, whose LDS leaves room for no more). Fitted to 14 core shapes
 // with one plane and two, 2 to 6 levels of 16 to 200 cores, 64 to 1000 samples and 2
 // to 32 ticks: the form taken is on average 0.5% slower than the fastest of
-// tick by tick, level after level and skewed, and at most 12%. (Constants
-// measured on 256 x 256 cores alone took up to 2.6 times as long as tick by tick: 2
-// ticks of 2 levels of 200 cores of 512 x 64 x 1000 samples 397 us, 152.)
+// tick by tick, level after level and skewed, and on 260 random layered networks of 256
+// x 256 cores 0.9%, at most 36% (6 levels of 108 cores x 540 samples x 16 ticks, level
+// after level 1699 us, skewed 1250); next to tick by tick at most 9% (2 levels of 200
+// cores of 512 x 128 x 64 samples x 4 ticks, 54.6 us, 59.4). (Constants measured on 256 x
+// 256 cores alone took up to 2.6 times as long as tick by tick: 2 ticks of 2 levels of
+// 200 cores of 512 x 64 x 1000 samples 397 us, 152.)
 static BlockPlan choose_blocks(const Plan &p, int T)
 {
     if (!p.levels || T < 2)
@@ -1158,15 +1161,15 @@ static BlockPlan choose_blocks(const Plan &p, int T)
     const int held = p.A == 512 ? 256 : 512;   // workgroups the GPU holds
     const double one = 0.7 + 0.0008 * A + (wide ? 0.15 : 0.0) + (p.two ? 0.05 + 0.0006 * A : 0.0);
     const double round = wide ? 1.35 + (p.two ? A / 640 : 0.0) : 0.6 + 0.0011 * A + (p.two && p.A >= 256 ? 0.1 : 0.0);
+    const double chain = 3.3 + 0.004 * A + 0.006 * w + (p.two && wide ? 0.2 + 0.006 * A : 0.0);
     auto launch = [&](long long cores, int ticks) {
         const long long units = cores * p.slices * ((p.S + 31) / 32);
         const double tick = units <= 256 ? one : std::max(1.0, round * ((units + held - 1) / held));
-        return 4.0 + (1.5 + 0.013 * w + 0.016 * A) * units / 512 + tick * ticks;
+        return chain + (1.5 + 0.013 * w + 0.016 * A) * units / 512 + tick * ticks;
     };
-    const double chain = 3.3 + 0.004 * A + 0.006 * w + (p.two && wide ? 0.2 + 0.006 * A : 0.0);
     const double per = 0.022 * w + 0.0018 * A + (p.two && wide ? 1.0 : 0.0) + (w == 128 && p.A >= 256 ? 0.7 : 0.0);
     const double units = (double)p.C * p.slices * (p.S64 / 64);
-    return cheapest_blocks(p, T, 0.5 + T * (chain + per * std::max(0.0, units - 64) / 256), launch);
+    return cheapest_blocks(p, T, 3.0 + T * (chain + per * std::max(0.0, units - 64) / 256), launch);
 }
 
 static void set_plain_args(const ranc_net *net, BlockArgs &a)
